@@ -63,7 +63,7 @@ struct Engine {
     size_t ws_need = 0;
     size_t off_zbase = 0;  // per-instance zeros: dense output on one instance's own grid
     std::vector<int> cb_start, cb_count;  // conversion blocks of each instance
-    size_t off_f0 = 0, off_f1 = 0, off_om = 0, off_snap = 0, off_rec = 0, off_inst = 0, off_dbase = 0, off_sblk = 0,
+    size_t off_f0 = 0, off_f1 = 0, off_om = 0, off_snap = 0, off_rec = 0, off_srec = 0, off_inst = 0, off_dbase = 0, off_sblk = 0,
            off_sinst = 0,
            off_cblk = 0, off_mblk = 0, off_rng = 0, off_part = 0, off_res = 0;
     int64_t cap_sblk = 0, cap_cblk = 0, cap_mblk = 0;
@@ -80,10 +80,13 @@ struct Engine {
 
     static constexpr int kXcds = 8;  // MI355X: 8 XCDs, each with its own L2
     int waves = 4, spw = 1, xcd = 1;
-    // Rows per y slab of the one-instance step list (0: grid order); set at creation.
-    int slab_rows = 0;
-    // Alternate the direction in which one-step launches walk the segment list.
-    int alt_order = 1;
+    // The one-instance step list as kXcds slabs of consecutive rows in y (set at
+    // creation; otherwise grid order), and the first list entry of every slab's planes.
+    bool slabs = false;
+    std::vector<int> zstart;
+    // Blocks of planes stepped several times in a row (plan_blocks): their number (1:
+    // whole steps) and the steps a block takes before the next one's turn.
+    int nblocks = 1, block_steps = 1;
     // Two steps per launch (one instance only): rows per tile (0 = off), planes per chunk.
     int t2_by = 0, t2_zc = 32;
     // Batches run as consecutive groups of instances whose combined working set
@@ -91,7 +94,7 @@ struct Engine {
     // stays in the 256 MB last-level cache (Infinity Cache) while it steps; 0 runs
     // every instance together.
     int64_t group_bytes = int64_t(192) << 20;
-    int step_nblk = 0, step_nent = 0, meas_nblk = 0, conv_nblk = 0;
+    int step_nent = 0, meas_nblk = 0, conv_nblk = 0;
     std::vector<int> live;
     std::vector<RunState> rs;
 
@@ -100,7 +103,7 @@ struct Engine {
     // g_valid is cleared whenever the launch form or tables change; both slots are
     // re-captured lazily after that.
     hipGraphExec_t gexec[2] = {nullptr, nullptr};
-    int g_nblk[2] = {-1, -1}, g_k[2] = {-1, -1};
+    int g_k[2] = {-1, -1};
     bool g_slot[2] = {false, false};
     bool g_valid = false;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;  // bracket the step launches of a window
@@ -146,6 +149,7 @@ struct Engine {
         off_om = knudsen ? take(sizeof(float) * stride) : 0;
         off_snap = take(sizeof(float) * stride);
         off_rec = take(sizeof(SegRec) * nseg_total);
+        off_srec = take(sizeof(SegRec) * nseg_total);
         off_inst = take(sizeof(InstDev) * ninst);
         off_dbase = take(sizeof(int64_t) * ninst);
         off_zbase = take(sizeof(int64_t) * ninst);
@@ -198,20 +202,27 @@ struct Engine {
         // same row in z -+ 1) were touched a slab plane earlier, a few hundred
         // segments back, still in that XCD's L2.  In grid order an XCD steps a slab
         // of whole planes, and the plane before is too far back for its L2.
-        if (live.size() == 1 && slab_rows > 0) {
+        zstart.clear();
+        if (live.size() == 1 && slabs) {
             const Prepared &p = P[live[0]];
-            const int64_t nx = p.nx, ny = p.ny, nz = p.nz, plane = ny * nx;
-            const int64_t base = seg_base[live[0]], yb = slab_rows;
-            auto key = [&](uint32_t gs) {  // (slab of the window's first row, plane, grid index)
-                const int64_t v0 = p.win_v0[(int64_t)gs - base];
-                const int64_t row = v0 / nx, y = row % ny, z = row / ny;
-                return ((y / yb) * nz + z) * plane + (v0 - z * plane);
+            const int64_t nx = p.nx, ny = p.ny, nz = p.nz, base = seg_base[live[0]];
+            auto slab_plane = [&](uint32_t g) {  // (slab of the window's first row, plane)
+                const int64_t row = p.win_v0[(int64_t)g - base] / nx;
+                return (row % ny * kXcds / ny) * nz + row / ny;
             };
-            std::sort(sb.begin(), sb.end(), [&](uint32_t a, uint32_t b) { return key(a) < key(b); });
+            zstart.assign(kXcds * nz + 1, 0);
+            std::vector<int> key(sb.size());
+            for (size_t k = 0; k < sb.size(); ++k) {
+                key[k] = (int)slab_plane(sb[k]);
+                ++zstart[key[k] + 1];
+            }
+            for (int64_t k = 0; k < kXcds * nz; ++k) zstart[k + 1] += zstart[k];
+            std::vector<int> at(zstart.begin(), zstart.end() - 1);
+            std::vector<uint32_t> sorted(sb.size());
+            for (size_t k = 0; k < sb.size(); ++k) sorted[at[key[k]]++] = sb[k];
+            sb.swap(sorted);
         }
         step_nent = (int)sb.size();
-        const int per = waves * spw;
-        step_nblk = (step_nent + per - 1) / per;
         // measure table and per-instance partial ranges
         std::vector<int4> mb;
         std::vector<int2> rg(ninst, make_int2(0, 0));
@@ -231,6 +242,7 @@ struct Engine {
         if (e == hipSuccess && !mb.empty())
             e = hipMemcpyAsync(at<int4>(off_mblk), mb.data(), sizeof(int4) * mb.size(), hipMemcpyHostToDevice, st);
         if (e == hipSuccess) e = hipMemcpyAsync(at<int2>(off_rng), rg.data(), sizeof(int2) * ninst, hipMemcpyHostToDevice, st);
+        if (e == hipSuccess) e = launch_order(L, at<uint32_t>(off_sblk), step_nent, at<SegRec>(off_srec), st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);  // host vectors go out of scope
         g_valid = false;
         return e;
@@ -334,6 +346,7 @@ struct Engine {
         csnap = at<float>(off_snap);
         L.rec = at<SegRec>(off_rec);
         L.omega = knudsen ? at<float>(off_om) : nullptr;
+        L.srec = at<SegRec>(off_srec);
         L.inst = at<InstDev>(off_inst);
         L.stride = (uint32_t)stride;
         // metadata (host staging, then one synchronisation)
@@ -396,13 +409,69 @@ struct Engine {
         s.waves = waves;
         s.spw = spw;
         s.xcd = xcd;
-        s.nblk = step_nblk;
         s.nent = step_nent;
-        s.list = at<uint32_t>(off_sblk);
         s.list_inst = at<uint32_t>(off_sinst);
         s.single = ninst == 1 ? 1 : 0;
+        int most = step_nent;
+        if (xcd) {  // contiguous eighths of the list
+            most = 0;
+            for (int x = 0; x < kXcds; ++x) {
+                const int a = (int)((int64_t)step_nent * x / kXcds), b = (int)((int64_t)step_nent * (x + 1) / kXcds);
+                s.rng[x] = {a, b - a, 0, 0};
+                most = std::max(most, b - a);
+            }
+        }
+        set_grid(s, most);
         return s;
     }
+    void set_grid(StepLaunch &s, int most) const {
+        const int per = waves * spw;
+        s.nblk = (xcd ? kXcds : 1) * ((most + per - 1) / per);
+    }
+
+    // Planes za <= z < zb only (zb beyond nz: the rest from plane 0 on); each XCD its slab.
+    void set_planes(StepLaunch &s, int za, int zb) const {
+        const int nz = P[0].nz;
+        int most = 0;
+        for (int x = 0; x < kXcds; ++x) {
+            const int *zs = zstart.data() + (int64_t)x * nz;
+            StepLaunch::Range &r = s.rng[x];
+            r.s0 = zs[za];
+            r.n0 = zs[std::min(zb, nz)] - zs[za];
+            r.s1 = zs[0];
+            r.n1 = zb > nz ? zs[zb - nz] - zs[0] : 0;
+            most = std::max(most, r.n0 + r.n1);
+        }
+        set_grid(s, most);
+    }
+
+    // Where both lattices are larger than the last-level cache (256 MB), a step streams
+    // them from HBM.  The grid is then cut into blocks of planes small enough for that
+    // cache, and a block takes several steps before the next block's turn.  Step t of
+    // a round covers the block's planes moved down by t, so that every plane a step
+    // pulls from has taken its steps and none is overwritten early: with two lattices a
+    // value lives until the step after next of its own plane.  The first block keeps
+    // its lower end clear of the wrap (planes t on), the last one makes up for it past
+    // the periodic end.
+    // A block of ~175 MB leaves room for the planes it moves through: us per step at
+    // 256^3 NPMC reactive (487 MB) 103.0 whole, 95.8 / 90.4 / 93.6 in 2 / 3 / 4 blocks;
+    // 256^3 Pt D_eff (685 MB) 122.6, 122.3 / 114.8 / 118.3 in 3 / 4 / 5; 192^3 Pt D_eff
+    // (289 MB) 54.0, 47.3 / 50.3 in 2 / 3; 176^3 (222 MB, nearly cached) 34.9 whole,
+    // 37.4 in 2.  Rounds of a quarter of a block's planes: 8, 16, 24, 32 steps took 97.9,
+    // 92.7, 92.3, 93.0 us at 256^3 in 3 blocks of 85 planes.
+    static constexpr int64_t kWholeBytes = int64_t(240) << 20, kBlockBytes = int64_t(167) << 20;
+    void plan_blocks() {
+        nblocks = block_steps = 1;
+        if (!slabs || ninst != 1) return;
+        const int64_t bytes = working_bytes(0);
+        const int nz = P[0].nz;
+        if (bytes <= kWholeBytes) return;
+        const int64_t n = (bytes + kBlockBytes - 1) / kBlockBytes;
+        if (nz / n < 8) return;  // too few planes in a block to move through
+        nblocks = (int)n;
+        block_steps = std::min<int>(32, (int)(nz / n / 4));
+    }
+    bool blocked() const { return nblocks > 1 && xcd && !zstart.empty(); }
 
     bool two_step() const { return t2_by > 0 && ninst == 1; }
     // the two-step kernel tiles rows of segments: the row layout only (Prepared)
@@ -434,8 +503,28 @@ struct Engine {
             }
         }
         StepLaunch s = step_launch();
+        if (blocked() && n - k > 1) {
+            const int nz = P[0].nz;
+            const int64_t rounds = (n - k + block_steps - 1) / block_steps;
+            for (int64_t r = rounds; r > 0; --r) {
+                const int T = (int)((n - k + r - 1) / r);
+                for (int c = 0; c < nblocks; ++c)
+                    for (int t = 0; t < T; ++t) {
+                        const int za = c == 0 ? t : nz * c / nblocks - t;
+                        const int zb = c == nblocks - 1 ? nz + t : nz * (c + 1) / nblocks - t;
+                        set_planes(s, za, zb);
+                        s.reverse = t & 1;
+                        const int from = cur ^ (t & 1);
+                        hipError_t e = launch_step(L, s, knudsen, react, f[from], f[from ^ 1], st);
+                        if (e != hipSuccess) return e;
+                    }
+                cur ^= T & 1;
+                k += T;
+            }
+            return hipSuccess;
+        }
         for (; k < n; ++k) {
-            s.reverse = alt_order ? (int)(k & 1) : 0;
+            s.reverse = (int)(k & 1);
             hipError_t e = launch_step(L, s, knudsen, react, f[cur], f[cur ^ 1], st);
             if (e != hipSuccess) return e;
             cur ^= 1;
@@ -482,7 +571,6 @@ struct Engine {
         (void)hipGraphDestroy(graph);
         if (e != hipSuccess) return e;
         g_slot[from] = true;
-        g_nblk[from] = step_nblk;
         g_k[from] = K0;
         return hipSuccess;
     }
@@ -507,7 +595,7 @@ struct Engine {
         const bool fl = flips(K0) != 0;
         for (int k = 0; k < ((fl && reps > 1) ? 2 : 1); ++k) {
             const int from = cur ^ k;
-            if (!g_slot[from] || g_nblk[from] != step_nblk || g_k[from] != K0) {
+            if (!g_slot[from] || g_k[from] != K0) {
                 hipError_t e = capture(K0, from);
                 if (e != hipSuccess) return e;
             }
@@ -806,9 +894,9 @@ int make_engine(int n, const lbm_grid *grids, const uint8_t *const *phases, cons
     E->react = E->mode == LBM_MODE_REACT;
     E->check_every = params[0].check_every;
     // one y slab of the step list per XCD, when the slabs are at least two rows
-    if (n == 1 && E->P[0].ny >= 2 * Engine::kXcds)
-        E->slab_rows = (E->P[0].ny + Engine::kXcds - 1) / Engine::kXcds;
+    E->slabs = n == 1 && E->P[0].ny >= 2 * Engine::kXcds;
     E->layout();
+    E->plan_blocks();
     // segment indices are 32-bit; population byte offsets are 32-bit (buffer resources)
     if (E->nseg_total > (int64_t)INT32_MAX || 28 * E->stride >= ((int64_t)1 << 32) - 64) return LBM_ERR_INVALID_ARG;
     E->rs.assign(n, RunState{});

@@ -50,6 +50,7 @@ enum { Q_JIN = 0, Q_JOUT, Q_JINT, Q_RATE, Q_MASS, Q_DCMAX, Q_CMAX, Q_BAD, NQ };
 
 struct Lattice {
     const SegRec *rec;        // per segment of every instance
+    const SegRec *srec;       // the records of the step list, in its order
     const float *omega;       // per fluid voxel 1/tau (Knudsen problems), else null
     const InstDev *inst;
     uint32_t stride;          // fluid voxels rounded up to 64; a lattice is 7 * stride floats in blocks of
@@ -62,7 +63,11 @@ struct StepLaunch {
     int32_t xcd;              // XCD-aware block order
     int32_t nblk;             // workgroups
     int32_t nent;             // entries of the list
-    const uint32_t *list;     // segments with fluid of the live instances, in grid order
+    // XCD-aware order: XCD x walks rng[x], n0 entries from s0 and then n1 from s1 (the
+    // planes past the periodic end of a range of planes).
+    struct Range {
+        int32_t s0, n0, s1, n1;
+    } rng[8];
     const uint32_t *list_inst;// instance of each list entry (several instances), so a wave can load
                               // its instance constants in parallel with its segment record
     int32_t single;           // 1: one instance (its constants load without waiting for the record)
@@ -91,6 +96,8 @@ struct MeasureLaunch {
     float *csnap;             // per fluid voxel concentration snapshot
 };
 
+// srec[e] = the record of segment list[e] (upload of the step list)
+hipError_t launch_order(const Lattice &L, const uint32_t *list, int32_t n, SegRec *srec, hipStream_t st);
 hipError_t launch_step(const Lattice &L, const StepLaunch &S, bool knudsen, bool react, const float *fin,
                        float *fout, hipStream_t st);
 // Two steps from fin to fout (instance 0 of L only).

@@ -71,16 +71,6 @@ __device__ __forceinline__ int logical_block(int b, int nblk, int remap) {
     return x * q + min(x, r) + (b >> 3);
 }
 
-// The same renumbering with each XCD walking its eighth backwards.  Steps
-// alternate between the two, so a step starts on the segments the previous step
-// touched last: their lines are still in that XCD's L2 and in the last-level cache.
-__device__ __forceinline__ int logical_block_reversed(int b, int nblk, int remap) {
-    if (!remap || nblk < 8) return nblk - 1 - b;
-    const int q = nblk >> 3, r = nblk & 7;
-    const int x = b & 7, len = q + (x < r ? 1 : 0);
-    return x * q + min(x, r) + (len - 1 - (b >> 3));
-}
-
 // x of a lane of a segment (lanes from brk on lie on the next row)
 __device__ __forceinline__ int lane_x(const SegRec &R, int lane) {
     return lane < (int)R.brk ? (int)R.x0 + lane : lane - (int)R.brk;
@@ -199,17 +189,22 @@ __device__ __forceinline__ void collide_store(const SegRec &R, const InstDev &I,
 
 // Fused pull stream + collide.  Each wave takes SPW consecutive list entries (row
 // segments holding fluid) and issues all their loads before any arithmetic, so a
-// wave keeps SPW x 8 loads in flight.
+// wave keeps SPW x 8 loads in flight.  Workgroups reach the 8 XCDs round robin; with
+// the XCD-aware order XCD x walks its own part of the list (rng[x]), so neighbour rows
+// share its L2.  The records lie in list order: one scalar load less in front of the
+// gather than through a list of segment numbers (105.2 -> 103.0 us per step at 256^3).
 template <int WAVES, int SPW, bool KNUDSEN, bool REACT, bool SINGLE>
 __global__ __launch_bounds__(WAVES * 64) void k_step(Lattice L, StepLaunch S, const float *__restrict__ fin,
                                                     float *__restrict__ fout) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int b = S.reverse ? logical_block_reversed(blockIdx.x, S.nblk, S.xcd) : logical_block(blockIdx.x, S.nblk, S.xcd);
+    const StepLaunch::Range rng = S.rng[blockIdx.x & 7];
+    const int nent = S.xcd ? rng.n0 + rng.n1 : S.nent;
+    const int base = ((int)(S.xcd ? blockIdx.x >> 3 : blockIdx.x) * WAVES + wave) * SPW;
+    if (base >= nent) return;
     const uint32_t S4 = 4u * L.stride;
     const __amdgpu_buffer_rsrc_t rin = rsrc(fin, 7u * S4), rout = rsrc(fout, 7u * S4);
     const __amdgpu_buffer_rsrc_t rom = rsrc(L.omega, KNUDSEN ? S4 : 0u);
-    const int base = (b * WAVES + wave) * SPW;
     const SegRec *R[SPW];
     const InstDev *Ip[SPW];
     bool act[SPW];
@@ -217,9 +212,11 @@ __global__ __launch_bounds__(WAVES * 64) void k_step(Lattice L, StepLaunch S, co
     uint32_t j4[SPW];
 #pragma unroll
     for (int k = 0; k < SPW; ++k) {
-        const bool valid = base + k < S.nent;  // wave-uniform
-        const int idx = valid ? base + k : 0;
-        R[k] = &L.rec[S.list[idx]];
+        const bool valid = base + k < nent;  // wave-uniform
+        int idx = valid ? base + k : 0;
+        if (S.reverse) idx = nent - 1 - idx;
+        if (S.xcd) idx = idx < rng.n0 ? rng.s0 + idx : rng.s1 + (idx - rng.n0);
+        R[k] = &L.srec[idx];
         Ip[k] = &L.inst[SINGLE ? 0 : S.list_inst[idx]];  // independent of the record
         act[k] = valid && bit(R[k]->m, lane);
         gather<KNUDSEN>(*R[k], rin, rom, act[k], r[k], j4[k]);
@@ -560,6 +557,13 @@ __device__ __forceinline__ void for_lanes(const Lattice &L, const int2 *blk, Fn 
     fn(t.x, I, v, j, (double)react_n(R, lane));
 }
 
+__global__ __launch_bounds__(256) void k_order(Lattice L, const uint32_t *list, int n, uint64_t *srec) {
+    constexpr int W = sizeof(SegRec) / 8;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= (int64_t)n * W) return;
+    srec[i] = reinterpret_cast<const uint64_t *>(L.rec + list[i / W])[i % W];
+}
+
 __global__ __launch_bounds__(256) void k_init_eq(Lattice L, const int2 *blk, int react, const float *c_dense,
                                                 const int64_t *dbase, float *f, float *csnap) {
     for_lanes(L, blk, [&](int inst, const InstDev &I, int64_t v, int64_t j, double n) {
@@ -714,6 +718,15 @@ hipError_t launch_init_eq(const Lattice &L, int32_t nblk, const int2 *blk, bool 
     if (nblk <= 0) return hipSuccess;
     (void)hipGetLastError();
     hipLaunchKernelGGL(k_init_eq, dim3(nblk), dim3(256), 0, st, L, blk, react ? 1 : 0, c_dense, dense_base, f, csnap);
+    return hipGetLastError();
+}
+
+hipError_t launch_order(const Lattice &L, const uint32_t *list, int32_t n, SegRec *srec, hipStream_t st) {
+    if (n <= 0) return hipSuccess;
+    (void)hipGetLastError();
+    const int64_t words = (int64_t)n * (int64_t)(sizeof(SegRec) / 8);
+    hipLaunchKernelGGL(k_order, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, st, L, list, n,
+                       reinterpret_cast<uint64_t *>(srec));
     return hipGetLastError();
 }
 
