@@ -69,8 +69,7 @@ constexpr int ROW[kQ] = {4, 4, 4, 1, 7, 3, 5, 1, 7, 1, 7, 3, 5, 3, 5, 0, 2, 6, 8
 struct D19Args {
     const float *__restrict__ fin;
     float *__restrict__ fout;
-    const D19Rec *__restrict__ rec;
-    const uint32_t *__restrict__ list;  // segments holding simulated voxels
+    const D19Rec *__restrict__ rec;     // segments holding simulated voxels, in walking order
     const float *__restrict__ omega;    // compact
     const float *__restrict__ kn;       // k n, compact (reactive problem only)
     const float *__restrict__ src;      // a given source per voxel (dense), or null
@@ -83,7 +82,12 @@ struct D19Args {
     double c_in, c_out;
     int react_outlet;                   // 1: zero-gradient outlet (no open links at x = nx - 1)
     int open_inlet;                     // 1: open links at x = 0 (0 for the potential problem)
-    int reverse;                        // 1: each XCD walks its eighth of the list backwards
+    int reverse;                        // 1: each XCD walks its part of the records backwards
+    // A step without measurement: XCD x walks n0 records from s0, then n1 from s1 (the
+    // planes past the periodic end of a range of planes).
+    struct Range {
+        int s0, n0, s1, n1;
+    } rng[8];
 };
 
 // Blocks are dealt round-robin to the 8 XCDs; give XCD k the k-th contiguous
@@ -147,13 +151,25 @@ template <bool REACT, bool MEASURE>
 __global__ __launch_bounds__(kBlock) void k_d3q19(D19Args a) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // lb: the logical block, which also indexes the partial sums, so that a measured
-    // step sums the same blocks in the same order in either direction
-    const int64_t lb = a.reverse ? xcd_block_reversed(blockIdx.x, a.nblk) : xcd_block(blockIdx.x, a.nblk);
-    const int64_t e = lb * (kBlock / 64) + wave;
+    // lb: the logical block of a measured step, which also indexes the partial sums, so
+    // that it sums the same blocks in the same order in either direction
+    int64_t lb = 0, e;
+    bool some;
+    if constexpr (MEASURE) {
+        lb = a.reverse ? xcd_block_reversed(blockIdx.x, a.nblk) : xcd_block(blockIdx.x, a.nblk);
+        e = lb * (kBlock / 64) + wave;
+        some = e < a.nent;
+    } else {
+        const D19Args::Range r = a.rng[blockIdx.x & 7];
+        const int n = r.n0 + r.n1;
+        int k = (int)(blockIdx.x >> 3) * (kBlock / 64) + wave;
+        some = k < n;
+        if (a.reverse) k = n - 1 - k;
+        e = k < r.n0 ? r.s0 + k : r.s1 + (k - r.n0);
+    }
     double acc[kRed] = {0, 0, 0, 0, 0, 0, 0, 0};
-    if (e < a.nent) {
-        const D19Rec &R = a.rec[a.list[e]];
+    if (some) {
+        const D19Rec &R = a.rec[e];
         const uint64_t mown = R.m[4];
         if (bit64(mown, lane)) {
             const int x = lane < (int)R.brk ? (int)R.x0 + lane : lane - (int)R.brk;
@@ -247,27 +263,26 @@ __global__ __launch_bounds__(kBlock) void k_d3q19(D19Args a) {
     }
 }
 
-// Fixed-order final reduction of the per-block partials (one block).
+// Fixed-order final reduction of the per-block partials, one block per quantity (one
+// block for all eight took 151 us at 192^3, most of it load latency).
 __global__ __launch_bounds__(kBlock) void k_d3q19_reduce(const double *__restrict__ part, int nblk,
                                                          double *__restrict__ out) {
     __shared__ double red[kBlock / 64];
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    for (int k = 0; k < kRed; ++k) {
-        const bool mx = k == 5 || k == 6;
-        double s = 0.0;
-        for (int b = threadIdx.x; b < nblk; b += kBlock) {
-            const double p = part[(int64_t)b * kRed + k];
-            s = mx ? fmax(s, p) : s + p;
-        }
-        s = mx ? wave_max(s) : wave_sum(s);
-        if (lane == 0) red[wv] = s;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            double t = red[0];
-            for (int w = 1; w < kBlock / 64; ++w) t = mx ? fmax(t, red[w]) : t + red[w];
-            out[k] = t;
-        }
-        __syncthreads();
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, k = blockIdx.x;
+    const bool mx = k == 5 || k == 6;
+    double s = 0.0;
+#pragma unroll 8
+    for (int b = threadIdx.x; b < nblk; b += kBlock) {
+        const double p = part[(int64_t)b * kRed + k];
+        s = mx ? fmax(s, p) : s + p;
+    }
+    s = mx ? wave_max(s) : wave_sum(s);
+    if (lane == 0) red[wv] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = red[0];
+        for (int w = 1; w < kBlock / 64; ++w) t = mx ? fmax(t, red[w]) : t + red[w];
+        out[k] = t;
     }
 }
 
@@ -337,11 +352,12 @@ struct lbm19_solver {
     double d0_lat = 0, ab_in = 0, ab_out = 0;
     std::vector<uint32_t> mask;    // dense per-voxel bits (pull sources, open links), for the potential solve
     std::vector<int32_t> cidx;     // dense voxel -> compact index, -1 off the simulated voxels
-    std::vector<D19Rec> rec;       // per row segment
-    std::vector<uint32_t> list;    // segments holding simulated voxels
+    std::vector<D19Rec> rec;       // segments holding simulated voxels, in walking order
+    std::vector<int> zstart;       // first record of every slab's planes (empty: no slabs)
+    int nblocks = 1, block_steps = 1;  // blocks of planes, and the steps each takes in a row (plan_blocks)
     std::vector<float> om_c, kn_c; // compact 1/tau and k n
     // workspace carve-up
-    size_t off_f[2] = {0, 0}, off_mask = 0, off_cidx = 0, off_rec = 0, off_list = 0, off_om = 0, off_kn = 0,
+    size_t off_f[2] = {0, 0}, off_mask = 0, off_cidx = 0, off_rec = 0, off_om = 0, off_kn = 0,
            off_cs = 0, off_part = 0, off_red = 0, need = 0;
     char *ws = nullptr;
     hipStream_t st = nullptr;
@@ -360,7 +376,6 @@ struct lbm19_solver {
         a.fin = at<float>(off_f[cur]);
         a.fout = at<float>(off_f[cur ^ 1]);
         a.rec = at<D19Rec>(off_rec);
-        a.list = at<uint32_t>(off_list);
         a.omega = at<float>(off_om);
         a.kn = react ? at<float>(off_kn) : nullptr;
         a.src = src;
@@ -383,24 +398,100 @@ struct lbm19_solver {
         return a;
     }
 
-    hipError_t launch(bool measure) {
-        const D19Args a = args(measure);
-        if (nblk > 0) {
-            if (react) {
-                if (measure)
-                    k_d3q19<true, true><<<nblk, kBlock, 0, st>>>(a);
-                else
-                    k_d3q19<true, false><<<nblk, kBlock, 0, st>>>(a);
+    // The records of planes za <= z < zb (zb beyond nz: the rest from plane 0 on), two
+    // XCDs to a slab; without slabs every record, an eighth to each XCD.  Returns the
+    // step's workgroups.
+    int set_planes(D19Args &a, int za, int zb) const {
+        int most = 0;
+        for (int x = 0; x < 8; ++x) {
+            D19Args::Range &r = a.rng[x];
+            if (zstart.empty()) {
+                const int lo = (int)(nent * x / 8), hi = (int)(nent * (x + 1) / 8);
+                r = {lo, hi - lo, 0, 0};
             } else {
-                if (measure)
-                    k_d3q19<false, true><<<nblk, kBlock, 0, st>>>(a);
-                else
-                    k_d3q19<false, false><<<nblk, kBlock, 0, st>>>(a);
+                const int *zs = zstart.data() + (int64_t)(x / 2) * P.nz;
+                const int n0 = zs[std::min(zb, P.nz)] - zs[za], n1 = zb > P.nz ? zs[zb - P.nz] - zs[0] : 0;
+                const int lo = x & 1 ? (n0 + n1) / 2 : 0, hi = x & 1 ? n0 + n1 : (n0 + n1) / 2;
+                r = {zs[za] + std::min(lo, n0), std::min(hi, n0) - std::min(lo, n0),
+                     zs[0] + std::max(lo - n0, 0), std::max(hi - n0, 0) - std::max(lo - n0, 0)};
             }
+            most = std::max(most, r.n0 + r.n1);
+        }
+        return 8 * ((most + kBlock / 64 - 1) / (kBlock / 64));
+    }
+
+    // Blocks of planes that take several steps while they are in the last-level cache
+    // (see the D3Q7 engine's plan_blocks: the same shift of a block's planes by one per
+    // step, since a pull reaches one plane up and down).  us per step: 192^3 Pt reactive
+    // (755 MB) 158.7 whole, 155.8 / 140.2 / 145.4 in 3 / 4 / 5 blocks; 256^3 NPMC
+    // reactive (1.24 GB) 292.8, 292.2 / 273.0 / 273.8 in 5 / 6 / 7; 160^3 Pt D_eff
+    // (433 MB) 96.0, 81.3 / 87.0 in 2 / 3; 144^3 (310 MB) 73.1, 64.1 in 2; 128^3 (217 MB,
+    // cached) 38.2, 41.1 in 2.  Rounds of 8 to 16 steps differ by 1-2%, of 20 by up to 5%.
+    void plan_blocks() {
+        nblocks = block_steps = 1;
+        if (zstart.empty()) return;
+        const int64_t bytes = nf * (2 * 4 * kQ + 8) + nent * (int64_t)sizeof(D19Rec);
+        const int64_t whole = int64_t(240) << 20, block = int64_t(210) << 20;
+        const int64_t n = (bytes + block - 1) / block;
+        if (bytes <= whole || P.nz / n < 8) return;  // cached, or too few planes to move through
+        nblocks = (int)n;
+        block_steps = std::min<int>(12, (int)(P.nz / n / 4));
+    }
+
+    hipError_t launch_planes(D19Args &a, int za, int zb) {
+        const int grid = set_planes(a, za, zb);
+        if (grid <= 0) return hipSuccess;
+        if (react)
+            k_d3q19<true, false><<<grid, kBlock, 0, st>>>(a);
+        else
+            k_d3q19<false, false><<<grid, kBlock, 0, st>>>(a);
+        return hipGetLastError();
+    }
+
+    // n steps without measurement
+    hipError_t run_steps(int64_t n) {
+        hipError_t e = hipSuccess;
+        while (n > 0 && e == hipSuccess) {
+            if (nblocks == 1 || n == 1) {
+                D19Args a = args(false);
+                e = launch_planes(a, 0, P.nz);
+                cur ^= 1;
+                ++steps;
+                --n;
+                continue;
+            }
+            const int64_t rounds = (n + block_steps - 1) / block_steps;
+            const int T = (int)((n + rounds - 1) / rounds), nz = P.nz;
+            for (int c = 0; c < nblocks && e == hipSuccess; ++c)
+                for (int t = 0; t < T && e == hipSuccess; ++t) {
+                    D19Args a = args(false);
+                    a.reverse = t & 1;
+                    if (t & 1) {
+                        a.fin = at<float>(off_f[cur ^ 1]);
+                        a.fout = at<float>(off_f[cur]);
+                    }
+                    e = launch_planes(a, c == 0 ? t : nz * c / nblocks - t,
+                                      c == nblocks - 1 ? nz + t : nz * (c + 1) / nblocks - t);
+                }
+            cur ^= T & 1;
+            steps += T;
+            n -= T;
+        }
+        return e;
+    }
+
+    // one measured step
+    hipError_t launch_measured() {
+        const D19Args a = args(true);
+        if (nblk > 0) {
+            if (react)
+                k_d3q19<true, true><<<nblk, kBlock, 0, st>>>(a);
+            else
+                k_d3q19<false, true><<<nblk, kBlock, 0, st>>>(a);
         }
         hipError_t e = hipGetLastError();
-        if (e == hipSuccess && measure) {
-            k_d3q19_reduce<<<1, kBlock, 0, st>>>(at<double>(off_part), nblk, at<double>(off_red));
+        if (e == hipSuccess) {
+            k_d3q19_reduce<<<kRed, kBlock, 0, st>>>(at<double>(off_part), nblk, at<double>(off_red));
             e = hipGetLastError();
         }
         cur ^= 1;
@@ -410,7 +501,7 @@ struct lbm19_solver {
 
     // one measured step; fills `last` from the reduction
     int measure_step(int64_t window) {
-        hipError_t e = launch(true);
+        hipError_t e = launch_measured();
         if (e == hipSuccess) e = hipMemcpyAsync(red, at<double>(off_red), sizeof(red), hipMemcpyDeviceToHost, st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);
         if (e != hipSuccess) return cl::record_error(e, "lbm19 measure");
@@ -536,10 +627,10 @@ static int create19(const lbm_grid *g, const uint8_t *phase, const lbm_params *p
         // segments: the windows of the D3Q7 layout (Prepared::win_v0, win_len)
         const int64_t nseg = (int64_t)P.win_v0.size();
         const int64_t plane = (int64_t)ny * nx;
-        s->rec.assign(nseg, D19Rec{});
-        s->list.clear();
+        std::vector<D19Rec> rec;
+        rec.reserve(nseg);
         for (int64_t g = 0; g < nseg; ++g) {
-            D19Rec &R = s->rec[g];
+            D19Rec R{};
             const int64_t v0 = P.win_v0[g];
             const int len = P.win_len[g];
             const int64_t row = v0 / nx;
@@ -563,21 +654,28 @@ static int create19(const lbm_grid *g, const uint8_t *phase, const lbm_params *p
                 if (x0 > 0 && sim(w0 - 1)) R.edges |= 1u << (2 * k);
                 if (len == 64 && x63 < nx - 1 && sim(w0 + 64)) R.edges |= 1u << (2 * k + 1);
             }
-            if (R.m[4]) s->list.push_back((uint32_t)g);
+            if (R.m[4]) rec.push_back(R);
         }
-        // Walk the list as four y slabs, each plane by plane: with the XCD-aware block
+        // Walk the records as four y slabs, each plane by plane: with the XCD-aware block
         // order each XCD then steps half a slab, and the rows a segment pulls from
         // (y -+ 1, z -+ 1 and the four yz diagonals) were touched a slab plane
         // earlier, still in its L2 (4 slabs measured faster than 8 or 16 here).
         if (ny >= 8) {
-            const int64_t yb = (ny + 3) / 4;
-            auto key = [&](uint32_t g) {  // (slab of the window's first row, plane, grid index)
-                const int64_t v0 = s->rec[g].v0, row = v0 / nx, y = row % ny, z = row / ny;
-                return ((y / yb) * nz + z) * plane + (v0 - z * plane);
+            auto slab_plane = [&](const D19Rec &R) {  // (slab of the window's first row, plane)
+                const int64_t row = R.v0 / nx;
+                return (row % ny * 4 / ny) * nz + row / ny;
             };
-            std::sort(s->list.begin(), s->list.end(), [&](uint32_t a, uint32_t b) { return key(a) < key(b); });
+            s->zstart.assign(4 * (size_t)nz + 1, 0);
+            for (const D19Rec &R : rec) ++s->zstart[slab_plane(R) + 1];
+            for (int k = 0; k < 4 * nz; ++k) s->zstart[k + 1] += s->zstart[k];
+            std::vector<int> at(s->zstart.begin(), s->zstart.end() - 1);
+            s->rec.assign(rec.size(), D19Rec{});
+            for (const D19Rec &R : rec) s->rec[at[slab_plane(R)]++] = R;
+        } else {
+            s->rec.swap(rec);
         }
-        s->nent = (int64_t)s->list.size();
+        s->nent = (int64_t)s->rec.size();
+        s->plan_blocks();
         s->nblk = (int)((s->nent + kBlock / 64 - 1) / (kBlock / 64));
         s->om_c.assign(std::max<int64_t>(nf, 1), 0.f);
         s->kn_c.assign(s->react ? std::max<int64_t>(nf, 1) : 0, 0.f);
@@ -588,7 +686,7 @@ static int create19(const lbm_grid *g, const uint8_t *phase, const lbm_params *p
             if (s->react && ((P.params.reactive_fluids >> P.phase[v]) & 1u))
                 s->kn_c[j] = (float)(P.params.k_lat * P.n_cat[v]);
         }
-        // workspace: two lattices, the dense bits and compact map, records, list,
+        // workspace: two lattices, the dense bits and compact map, records,
         // 1/tau, k n, C snapshot, partials, result
         size_t o = 0;
         auto take = [&](size_t bytes) {
@@ -601,8 +699,7 @@ static int create19(const lbm_grid *g, const uint8_t *phase, const lbm_params *p
         s->off_f[1] = take(fb);
         s->off_mask = take(4 * (size_t)s->N);
         s->off_cidx = take(4 * (size_t)s->N);
-        s->off_rec = take(sizeof(D19Rec) * (size_t)nseg);
-        s->off_list = take(4 * std::max<size_t>(s->list.size(), 1));
+        s->off_rec = take(sizeof(D19Rec) * s->rec.size());
         s->off_om = take(4 * (size_t)std::max<int64_t>(nf, 1));
         s->off_kn = s->react ? take(4 * (size_t)std::max<int64_t>(nf, 1)) : 0;
         s->off_cs = take(4 * (size_t)std::max<int64_t>(nf, 1));
@@ -956,7 +1053,6 @@ int lbm19_bind(lbm19_solver *s, void *ws, size_t bytes, void *stream) {
     up(s->off_mask, s->mask.data(), 4 * s->mask.size());
     up(s->off_cidx, s->cidx.data(), 4 * s->cidx.size());
     up(s->off_rec, s->rec.data(), sizeof(D19Rec) * s->rec.size());
-    up(s->off_list, s->list.data(), 4 * s->list.size());
     up(s->off_om, s->om_c.data(), 4 * s->om_c.size());
     if (s->react) up(s->off_kn, s->kn_c.data(), 4 * s->kn_c.size());
     if (e == hipSuccess) e = hipStreamSynchronize(s->st);
@@ -984,11 +1080,7 @@ int lbm19_set_initial_concentration(lbm19_solver *s, const float *c_dev) {
 int lbm19_step(lbm19_solver *s, int64_t nsteps) {
     if (!s || nsteps < 0) return LBM_ERR_INVALID_ARG;
     if (!s->ws) return LBM_ERR_UNBOUND;
-    for (int64_t k = 0; k < nsteps; ++k) {
-        const hipError_t e = s->launch(false);
-        if (e != hipSuccess) return cl::record_error(e, "lbm19_step");
-    }
-    return LBM_OK;
+    return cl::record_error(s->run_steps(nsteps), "lbm19_step");
 }
 
 int lbm19_measure(lbm19_solver *s, lbm_run_info *info) {

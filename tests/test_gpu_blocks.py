@@ -13,6 +13,8 @@ pytestmark = pytest.mark.gpu
 # (nz, ny, nx), mode, Knudsen, steps: about 5 M simulated voxels, two or three blocks
 D7 = [((16, 530, 640), "deff", 1, 7), ((61, 131, 700), "react", 0, 38), ((187, 99, 320), "react", 1, 33),
       ((212, 203, 192), "deff", 0, 120)]
+# D3Q19: about 2 M simulated voxels
+D19 = [((16, 350, 400), "deff", 9), ((73, 131, 256), "react", 26), ((150, 121, 130), "react", 31)]
 
 
 def _map(shape, seed):
@@ -46,3 +48,21 @@ def test_d3q7_blocks_equal_whole_steps(hip, shape, mode, knudsen, steps):
     for _ in range(40):
         b.step(1)
     assert torch.equal(a.populations(), b.populations())
+
+
+@pytest.mark.parametrize("shape,mode,steps", D19)
+def test_d3q19_blocks_equal_whole_steps(hip, shape, mode, steps):
+    import torch
+
+    ph = _map(shape, shape[1])
+    a = hip.Solver19(ph, _params(hip, mode, 1))
+    assert 152 * a.info.n_active > 240 << 20
+    b = hip.Solver19(ph, _params(hip, mode, 1))
+    c0 = torch.rand(a.shape, generator=torch.Generator().manual_seed(2))
+    for s in (a, b):
+        s.set_initial_concentration(c0)
+    a.step(steps)
+    for _ in range(steps):
+        b.step(1)
+    assert torch.equal(a.populations(), b.populations())
+    assert a.measure().as_dict() == b.measure().as_dict()
