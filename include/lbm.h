@@ -339,7 +339,7 @@ void lbm_batch_destroy(lbm_batch *b);
  * or the x = nx - 1 face (faces & 2); 0 elsewhere.  This is lbm_create's
  * simulated-voxel mask when pass is the transport phase and faces are the
  * Dirichlet faces.  *cycles (may be NULL) receives the number of sweep cycles
- * (three line sweeps each) until nothing changed. */
+ * (the grid swept along all three axes each) until nothing changed. */
 int lbm_pore_size_device(const uint8_t *pore_dev, int32_t nx, int32_t ny, int32_t nz, double *dp_dev, void *stream);
 int lbm_reach_device(const uint8_t *pass_dev, int32_t nx, int32_t ny, int32_t nz, int32_t faces, uint8_t *hit_dev,
                      int32_t *cycles, void *stream);
