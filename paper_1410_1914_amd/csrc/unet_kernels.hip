@@ -6,6 +6,7 @@
 
 #include <cstdint>
 #include <algorithm>
+#include <type_traits>
 
 #include "../../include/unet.h"
 
@@ -598,6 +599,198 @@ __global__ __launch_bounds__(256) void k_wgrad(const uint16_t *x, int ldx, int o
     if (db && blockIdx.x == 0 && tid < 16 * NCO) atomicAdd(&db[co0 + tid], bacc);
 }
 
+// The same for inputs that can be copied into LDS (16-byte aligned, below 2 GiB): a
+// workgroup marches through a run of planes of one tile of 8 rows of 32 voxels, for 16
+// input channels, 16 NCO output channels and all 27 taps.  Input planes (halo included)
+// sit in a four-slot ring and gradient planes in a two-slot one, copied straight from
+// global memory in their own layout (voxel by voxel, 16 channels) under the products of
+// the plane before; each input plane is copied once per run, not once per tap.  The
+// reduction runs over voxels, so both operands are needed voxel-fastest: the LDS
+// transpose read (4 voxels of a channel per lane) does that on the way to the
+// registers.  A row of 32 voxels is one MFMA's K, in the order 4 (l / 16) + j and 16 +
+// 4 (l / 16) + j for j = 0 .. 3, the same for both operands.  The taps are shared out to
+// the four waves (7, 7, 7, 6), the last one's spare product sums the gradient itself (db).
+// Bound by the copies (35 of 41 us for 16 -> 16 at 96^3 with the products taken out).
+// Staging both operands transposed by 2-byte LDS writes, once per group of taps, took
+// 388 us there; the 14 layers of a 96^3 step went from 2.19 ms to 0.44.
+struct WgradArgs {
+    const uint16_t *x, *dy;
+    float *dw, *db;
+    int ldx, offx, ldd, offd;
+    int nz, ny, nx, cin, cout, kpad, zr;
+    uint32_t xbytes, xplane, dbytes, dplane;
+};
+constexpr int kWX = 32, kWY = 8;                 // a tile's voxels in each plane
+constexpr int kWBX = kWX + 2, kWBY = kWY + 2;    // with the halo
+constexpr int kWPlane = kWBX * kWBY * kCC;       // elements of an input plane in LDS
+constexpr int kWD = kWX * kWY * kCC;             // elements of 16 channels of a gradient plane
+
+typedef short s16x4 __attribute__((__vector_size__(4 * sizeof(short))));
+typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
+
+// 32 voxels x 16 channels at p (voxel-major): this lane's channel l % 16 of its 8 voxels
+__device__ __forceinline__ bf16x8 read_transposed(const uint16_t *p, int lane) {
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 4 * lane));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4 *)(p + 16 * kCC + 4 * lane));
+    typedef short s16x8 __attribute__((__vector_size__(8 * sizeof(short))));
+    const s16x8 v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+template <int NCO, int WAVE, bool RAGGED>
+__device__ __forceinline__ void wgrad_plane(const uint16_t *x0, const uint16_t *x1, const uint16_t *x2, const uint16_t *d,
+                                            int rows, int lane, const uint4 &keep, f32x4 (&acc)[7][NCO]) {
+    for (int r = 0; r < rows; ++r) {
+        bf16x8 A[NCO];
+#pragma unroll
+        for (int c = 0; c < NCO; ++c) A[c] = read_transposed(d + c * kWD + r * kWX * kCC, lane);
+#pragma unroll
+        for (int i = 0; i < 7; ++i) {
+            constexpr int kOne = 0x3f803f80;  // two BF16 ones
+            const int tap = 7 * WAVE + i;
+            bf16x8 B;
+            if (tap < 27) {
+                const uint16_t *plane = tap / 9 == 0 ? x0 : tap / 9 == 1 ? x1 : x2;
+                B = read_transposed(plane + ((r + (tap / 3) % 3) * kWBX + tap % 3) * kCC, lane);
+                if (RAGGED) {  // voxels past the row's end: the gradient there is zero, the input may not be finite
+                    uint4 u = __builtin_bit_cast(uint4, B);
+                    u = make_uint4(u.x & keep.x, u.y & keep.y, u.z & keep.z, u.w & keep.w);
+                    B = __builtin_bit_cast(bf16x8, u);
+                }
+            } else {
+                B = __builtin_bit_cast(bf16x8, make_uint4(kOne, kOne, kOne, kOne));
+            }
+#pragma unroll
+            for (int c = 0; c < NCO; ++c) acc[i][c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[c], B, acc[i][c], 0, 0, 0);
+        }
+    }
+}
+
+template <int NCO>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_wgrad_zm(WgradArgs a) {
+    __shared__ __attribute__((aligned(16))) uint16_t s0[kWPlane], s1[kWPlane], s2[kWPlane], s3[kWPlane];
+    __shared__ __attribute__((aligned(16))) uint16_t g0[NCO * kWD], g1[NCO * kWD];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // workgroups reach the 8 XCDs round robin; each XCD takes a contiguous eighth of the
+    // order slice, x tile, y tile, run, so that one L2 serves the slices of a tile
+    const int nxt = (a.nx + kWX - 1) / kWX, nyt = (a.ny + kWY - 1) / kWY, nci = a.cin / 16, nsl = nci * (a.cout / (16 * NCO));
+    int t = (int)blockIdx.x;
+    {
+        const int n = (int)gridDim.x, per = n / 8, extra = n % 8, xcd = t % 8;
+        t = xcd * per + min(xcd, extra) + t / 8;
+    }
+    const int slice = t % nsl;
+    t /= nsl;
+    const int ci0 = slice % nci * 16, co0 = slice / nci * 16 * NCO;
+    const int x0 = t % nxt * kWX, y0 = t / nxt % nyt * kWY, z0 = t / (nxt * nyt) * a.zr;
+    const int n = min(a.zr, a.nz - z0), rows = min(kWY, a.ny - y0);
+    const bool ragged = x0 + kWX > a.nx;
+    uint32_t km[4];  // which of this lane's 8 voxels lie inside the row
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+        const int v = x0 + 16 * (k >> 1) + 4 * (lane >> 4) + 2 * (k & 1);
+        km[k] = (v < a.nx ? 0xffffu : 0u) | (v + 1 < a.nx ? 0xffff0000u : 0u);
+    }
+    const uint4 keep = make_uint4(km[0], km[1], km[2], km[3]);
+    const __amdgpu_buffer_rsrc_t rx =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.x), (short)0, (int)a.xbytes, kRawBuffer);
+    const __amdgpu_buffer_rsrc_t rd =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.dy), (short)0, (int)a.dbytes, kRawBuffer);
+    // this thread's byte offsets within a plane: input entries (16 bytes, two per voxel)
+    // and gradient entries, kNoOff (zeros) outside the grid
+    constexpr int kXE = 2 * kWBX * kWBY, kXI = (kXE + 255) / 256;
+    uint32_t xo[kXI], go[2];
+#pragma unroll
+    for (int it = 0; it < kXI; ++it) {
+        const int e = tid + 256 * it, v = e >> 1, xx = x0 + v % kWBX - 1, yy = y0 + v / kWBX - 1;
+        const bool in = xx >= 0 && xx < a.nx && yy >= 0 && yy < a.ny;
+        xo[it] = in ? 2u * (uint32_t)((yy * a.nx + xx) * a.ldx + a.offx + ci0 + 8 * (e & 1)) : kNoOff;
+    }
+#pragma unroll
+    for (int it = 0; it < 2; ++it) {
+        const int e = tid + 256 * it, v = e >> 1, xx = x0 + v % kWX, yy = y0 + v / kWX;
+        go[it] = xx < a.nx && yy < a.ny ? 2u * (uint32_t)((yy * a.nx + xx) * a.ldd + a.offd + co0 + 8 * (e & 1)) : kNoOff;
+    }
+    auto copy_x = [&](int zz, uint16_t *slot) __attribute__((always_inline)) {
+        const bool zin = zz >= 0 && zz < a.nz;
+        const uint32_t zoff = zin ? (uint32_t)zz * a.xplane : 0u;
+#pragma unroll
+        for (int it = 0; it < kXI; ++it) {
+            const int e0 = 256 * it + 64 * wave;
+            if (e0 >= kXE) break;  // wave-uniform
+            if (e0 + lane < kXE)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(slot + 8 * e0), 16, zin ? xo[it] : kNoOff, zoff, 0, 0);
+        }
+    };
+    auto copy_g = [&](int zz, uint16_t *slot) __attribute__((always_inline)) {
+        const uint32_t zoff = (uint32_t)zz * a.dplane;
+#pragma unroll
+        for (int c = 0; c < NCO; ++c)
+#pragma unroll
+            for (int it = 0; it < 2; ++it)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(rd, (lds_void *)(slot + c * kWD + 8 * (256 * it + 64 * wave)), 16,
+                                                         go[it] == kNoOff ? kNoOff : go[it] + 32u * c, zoff, 0, 0);
+    };
+    auto ring = [&](int i) -> uint16_t * {
+        i &= 3;
+        return i == 0 ? s0 : i == 1 ? s1 : i == 2 ? s2 : s3;
+    };
+    f32x4 acc[7][NCO];
+#pragma unroll
+    for (int i = 0; i < 7; ++i)
+#pragma unroll
+        for (int c = 0; c < NCO; ++c) acc[i][c] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    copy_x(z0 - 1, s0);
+    copy_x(z0, s1);
+    copy_x(z0 + 1, s2);
+    copy_g(z0, g0);
+    for (int p0 = 0; p0 < n; p0 += 4) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {  // plane z0 + p: input slots k, k + 1, k + 2, gradient slot k & 1
+            const int p = p0 + k;
+            if (p >= n) break;
+            __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);  // this wave's copies; the barrier waits for the others'
+            __syncthreads();
+            if (p + 1 < n) {
+                copy_x(z0 + p + 2, ring(k + 3));
+                copy_g(z0 + p + 1, k & 1 ? g0 : g1);
+            }
+            const uint16_t *d = k & 1 ? g1 : g0;
+            auto plane = [&](auto w) __attribute__((always_inline)) {
+                if (ragged)
+                    wgrad_plane<NCO, decltype(w)::value, true>(ring(k), ring(k + 1), ring(k + 2), d, rows, lane, keep, acc);
+                else
+                    wgrad_plane<NCO, decltype(w)::value, false>(ring(k), ring(k + 1), ring(k + 2), d, rows, lane, keep, acc);
+            };
+            if (wave == 0)
+                plane(std::integral_constant<int, 0>{});
+            else if (wave == 1)
+                plane(std::integral_constant<int, 1>{});
+            else if (wave == 2)
+                plane(std::integral_constant<int, 2>{});
+            else
+                plane(std::integral_constant<int, 3>{});
+        }
+    }
+    const int m = lane & 15, q = lane >> 4;
+#pragma unroll
+    for (int i = 0; i < 7; ++i) {
+        const int tap = 7 * wave + i;
+#pragma unroll
+        for (int c = 0; c < NCO; ++c)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int co = co0 + 16 * c + 4 * q + j;
+                const float v = acc[i][c][j];
+                if (tap < 27) {
+                    if (v != 0.f) atomicAdd(&a.dw[(int64_t)co * a.kpad + tap * a.cin + ci0 + m], v);
+                } else if (a.db && ci0 == 0 && m == 0) {
+                    atomicAdd(&a.db[co], v);
+                }
+            }
+    }
+}
+
 // ------------------------------------------------------------------ elementwise layers
 
 __global__ void k_relu_bwd(const uint16_t *y, int ldy, int offy, uint16_t *d, int ldd, int offd, int64_t nvox, int c) {
@@ -994,6 +1187,30 @@ int unet_conv3d_wgrad(const uint16_t *x, int32_t ldx, int32_t offx, const uint16
         return -1;
     if (cin % 16 || cout % 16 || ldx % 8 || offx % 8 || lddy % 8 || offdy % 8) return -1;
     const int64_t nvox = (int64_t)nz * ny * nx;
+    const int64_t xplane = 2 * (int64_t)ny * nx * ldx, dplane = 2 * (int64_t)ny * nx * lddy;
+    if (((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(dy)) & 15) == 0 && xplane * nz <= kMaxX &&
+        dplane * nz <= kMaxX) {
+        const int two = cout % 32 == 0 ? 2 : 1;
+        const int64_t tiles = (int64_t)((nx + kWX - 1) / kWX) * ((ny + kWY - 1) / kWY) * (cin / 16) * (cout / (16 * two));
+        // Runs per tile: about one workgroup per CU, up to two where the runs stay 24 planes
+        // long (a run copies two planes beyond its own and adds its sums atomically).  The 14
+        // layers of a 96^3 step: 514 / 444 / 477 / 515 / 675 us with 128 / 256 / 384 / 512 /
+        // 768 workgroups each; the 48 -> 16 layer alone 115 / 78 / 56 / 74 / 61.
+        const int64_t runs = std::max(std::max<int64_t>(1, 256 / tiles), std::min<int64_t>(512 / tiles, nz / 24));
+        int64_t zr = (nz + runs - 1) / runs;
+        if (nx <= kWX && ny <= kWY) zr = std::max<int64_t>(zr, (nz + 1) / 2);  // two runs: their sum has no order
+        const int64_t blocks = tiles * ((nz + zr - 1) / zr);
+        if (blocks <= 0x7fffffff) {
+            const WgradArgs a{x, dy, dw, db, ldx, offx, lddy, offdy, nz, ny, nx, cin, cout, kpad_of(cin), (int)zr,
+                              (uint32_t)(xplane * nz), (uint32_t)xplane, (uint32_t)(dplane * nz), (uint32_t)dplane};
+            (void)hipGetLastError();
+            if (two == 2)
+                hipLaunchKernelGGL(k_wgrad_zm<2>, dim3((unsigned)blocks), dim3(256), 0, static_cast<hipStream_t>(stream), a);
+            else
+                hipLaunchKernelGGL(k_wgrad_zm<1>, dim3((unsigned)blocks), dim3(256), 0, static_cast<hipStream_t>(stream), a);
+            return status(hipGetLastError());
+        }
+    }
     const int nco = cout % 64 == 0 ? 4 : (cout % 32 == 0 ? 2 : 1);
     // enough workgroups to fill the device: the voxel range per workgroup shrinks
     // for layers with few (k, channel) tiles
