@@ -9,6 +9,7 @@
 #include <type_traits>
 
 #include "../../include/unet.h"
+#include "unet_kernels.h"
 
 namespace {
 
@@ -68,9 +69,20 @@ struct ConvArgs {
     // which are then not stored.
     const float *hw, *hb, *hbase;
     float *hout;
+    // The ReLU mask of the tensor written (backward): y is zeroed where m is not positive.
+    const uint16_t *m;
+    int ldm, offm;
 };
 
 typedef __attribute__((address_space(3))) void lds_void;
+
+// four BF16 values with those zeroed whose mask value is not positive (not > 0: negative,
+// zero or NaN)
+__device__ __forceinline__ uint32_t mask_pair(uint32_t v, uint32_t m) {
+    const bool lo = __uint_as_float(m << 16) > 0.f, hi = __uint_as_float(m & 0xffff0000u) > 0.f;
+    return (lo ? v & 0xffffu : 0u) | (hi ? v & 0xffff0000u : 0u);
+}
+__device__ __forceinline__ uint2 mask4(uint2 v, uint2 m) { return make_uint2(mask_pair(v.x, m.x), mask_pair(v.y, m.y)); }
 
 // dword 3 of a raw (untyped, unswizzled) buffer resource on the gfx9 family
 constexpr int kRawBuffer = 0x00020000;
@@ -264,8 +276,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
                     v[i] = acc[p][t][n][i] + bias[i];
                     if (a.relu) v[i] = fmaxf(v[i], 0.f);
                 }
-                const uint2 o = make_uint2((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
-                                           (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
+                uint2 o = make_uint2((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
+                                     (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
+                if (a.m) o = mask4(o, *reinterpret_cast<const uint2 *>(a.m + vm * a.ldm + a.offm + c));
                 *reinterpret_cast<uint2 *>(a.y + vm * a.ldy + a.offy + c) = o;
                 if (a.y32) *reinterpret_cast<float4 *>(a.y32 + vm * a.cout + c) = make_float4(v[0], v[1], v[2], v[3]);
             }
@@ -284,7 +297,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // issued, so a barrier (which waits for the copies) never waits for fresh stores.
 // One plane of accumulators, 240 VGPRs: two workgroups per CU.  HEAD: the head is
 // applied in the epilogue and only its FP32 output is stored.
-template <bool HEAD>
+template <bool HEAD, bool MASK>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_zm(ConvArgs a, int zr) {
     __shared__ __attribute__((aligned(16))) uint16_t s0[kPlane * kVS], s1[kPlane * kVS], s2[kPlane * kVS],
         s3[kPlane * kVS];
@@ -388,6 +401,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
                     if (xx < a.nx) hbase[t4] = a.hbase[((int64_t)(z0 + p) * a.ny + yy) * a.nx + xx];
                 }
             }
+            uint2 mask[4];  // MASK: this plane's ReLU mask, loaded early for the same reason
+            if (MASK && yy < a.ny) {
+#pragma unroll
+                for (int t4 = 0; t4 < 4; ++t4) {
+                    const int xx = x0 + 16 * t4 + m;
+                    const int64_t vm = ((int64_t)(z0 + p) * a.ny + yy) * a.nx + xx;
+                    mask[t4] = xx < a.nx ? *reinterpret_cast<const uint2 *>(a.m + vm * a.ldm + a.offm + c) : make_uint2(0u, 0u);
+                }
+            }
             flush();
             if (p + 2 <= n) copy_plane(z0 + p + 2, ring(k + 3));
             // The slot a lane reads is fixed per chunk except where the chunk's two taps
@@ -437,8 +459,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
                     v[i] = acc[t4][i] + bias[i];
                     if (a.relu) v[i] = fmaxf(v[i], 0.f);
                 }
-                const uint2 o = make_uint2((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
-                                           (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
+                uint2 o = make_uint2((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
+                                     (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
+                if (MASK) o = mask4(o, mask[t4]);
                 if (HEAD) {
                     // the head's sum in channel order, as unet_head_fwd forms it from the
                     // stored BF16 values: lanes of group kb add channels 4 kb .. 4 kb + 3
@@ -487,6 +510,18 @@ __global__ void k_wtrans(const uint16_t *w, uint16_t *wt, int cin, int cout, int
         v = w[(int64_t)co * kpad_in + (26 - tp) * cin + ci];
     }
     wt[i] = v;
+}
+
+// The same for the layers of a table, one after another (blockIdx.y the layer).
+__global__ void k_wtrans_all(const uint16_t *w, uint16_t *wt, unet::TransTable t) {
+    const int l = blockIdx.y, cin = t.cin[l], cout = t.cout[l], kpad_in = kpad_of(cin), kpad_out = kpad_of(cout);
+    const uint16_t *src = w + t.w_off[l];
+    uint16_t *dst = wt + t.wt_off[l];
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (int64_t)cin * kpad_out;
+         i += (int64_t)gridDim.x * blockDim.x) {
+        const int ci = (int)(i / kpad_out), kk = (int)(i % kpad_out), tp = kk / cout, co = kk % cout;
+        dst[i] = kk < 27 * cout ? src[(int64_t)co * kpad_in + (26 - tp) * cin + ci] : (uint16_t)0;
+    }
 }
 
 // ------------------------------------------------------------------ conv3d weight gradient
@@ -901,6 +936,60 @@ __global__ void k_up_fwd8(const uint16_t *x, int ldx, int offx, uint16_t *y, int
         *reinterpret_cast<const uint4 *>(x + p * ldx + offx + 8 * g);
 }
 
+__device__ __forceinline__ uint4 f_to_bf8(const float (&f)[8]) {
+    uint32_t w[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = (uint32_t)f2bf(f[2 * k]) | (uint32_t)f2bf(f[2 * k + 1]) << 16;
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+__device__ __forceinline__ uint4 mask8(uint4 v, uint4 m) {
+    return make_uint4(mask_pair(v.x, m.x), mask_pair(v.y, m.y), mask_pair(v.z, m.z), mask_pair(v.w, m.w));
+}
+
+// Pooling's and upsampling's adjoints on runs of 8 channels, with an optional ReLU mask m
+// on what is written.  Bound by memory: pooling's reads and writes the fine tensor and
+// reads the mask.  The one-channel kernels moved 2 bytes per thread and the mask was a
+// pass of its own (13 us): 23.5 + 13 -> 15.8 us and 9.4 + 13 -> 9.3 us, means of the three
+// calls of a 96^3 step.
+__global__ void k_pool_bwd8(const uint16_t *dy, int ldy, int offy, uint16_t *dx, int ldx, int offx, const uint16_t *m,
+                            int ldm, int offm, uint32_t nz, uint32_t ny, uint32_t nx, uint32_t c8) {
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if ((uint64_t)i >= (uint64_t)nz * ny * nx * c8) return;
+    const uint32_t g = i % c8, v = i / c8;
+    const uint32_t xx = v % nx, yy = (v / nx) % ny, zz = v / (nx * ny);
+    const uint64_t p = ((uint64_t)(zz / 2) * (ny / 2) + yy / 2) * (nx / 2) + xx / 2;
+    uint4 *o = reinterpret_cast<uint4 *>(dx + (uint64_t)v * ldx + offx + 8 * g);
+    float a[8], b[8];
+    bf8_to_f(*o, a);
+    bf8_to_f(*reinterpret_cast<const uint4 *>(dy + p * ldy + offy + 8 * g), b);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) a[k] += 0.125f * b[k];
+    uint4 r = f_to_bf8(a);
+    if (m) r = mask8(r, *reinterpret_cast<const uint4 *>(m + (uint64_t)v * ldm + offm + 8 * g));
+    *o = r;
+}
+
+__global__ void k_up_bwd8(const uint16_t *dy, int ldy, int offy, uint16_t *dx, int ldx, int offx, const uint16_t *m,
+                          int ldm, int offm, uint32_t nz, uint32_t ny, uint32_t nx, uint32_t c8) {
+    const uint32_t hy = ny / 2, hx = nx / 2;
+    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+    if ((uint64_t)i >= (uint64_t)(nz / 2) * hy * hx * c8) return;
+    const uint32_t g = i % c8, p = i / c8;
+    const uint32_t X = p % hx, Y = (p / hx) % hy, Z = p / (hx * hy);
+    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int d = 0; d < 8; ++d) {
+        const uint64_t v = ((uint64_t)(2 * Z + (d >> 2)) * ny + 2 * Y + ((d >> 1) & 1)) * nx + 2 * X + (d & 1);
+        float f[8];
+        bf8_to_f(*reinterpret_cast<const uint4 *>(dy + v * ldy + offy + 8 * g), f);
+#pragma unroll
+        for (int k = 0; k < 8; ++k) s[k] += f[k];
+    }
+    uint4 r = f_to_bf8(s);
+    if (m) r = mask8(r, *reinterpret_cast<const uint4 *>(m + (uint64_t)p * ldm + offm + 8 * g));
+    *reinterpret_cast<uint4 *>(dx + (uint64_t)p * ldx + offx + 8 * g) = r;
+}
+
 __global__ void k_head_fwd8(const uint16_t *x, int ldx, const float *w, const float *b, const float *base, float *out,
                             int64_t nvox, int c8) {
     const int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -967,6 +1056,50 @@ __global__ __launch_bounds__(256) void k_head_bwd(const uint16_t *x, int ldx, co
     }
     const float s = block_sum(gsum, red);
     if (threadIdx.x == 0) atomicAdd(db, s);
+}
+
+// The same for 16 channels in 16-byte pieces, one reduction per workgroup for all 17 sums
+// (252 -> 23 us at 96^3: the general form reads and writes 2 bytes at a time and reduces
+// channel after channel).  RELU: dx is zeroed where x is not positive.
+template <bool RELU>
+__global__ __launch_bounds__(256) void k_head_bwd16(const uint16_t *x, int ldx, const float *w, const float *dout,
+                                                    uint16_t *dx, float *dw, float *db, int64_t nvox) {
+    __shared__ float red[4][17];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    float wr[16], part[17];
+#pragma unroll
+    for (int c = 0; c < 16; ++c) wr[c] = w[c];
+#pragma unroll
+    for (int c = 0; c < 17; ++c) part[c] = 0.f;
+    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < nvox; v += (int64_t)gridDim.x * 256) {
+        const float g = dout[v];
+        part[16] += g;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint4 u = *reinterpret_cast<const uint4 *>(x + v * ldx + 8 * h);
+            float f[8], o[8];
+            bf8_to_f(u, f);
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                part[8 * h + k] += g * f[k];
+                o[k] = g * wr[8 * h + k];
+            }
+            uint4 r = f_to_bf8(o);
+            if (RELU) r = mask8(r, u);
+            *reinterpret_cast<uint4 *>(dx + v * 16 + 8 * h) = r;
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < 17; ++c) {
+        float s = part[c];
+        for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+        if (lane == 0) red[wave][c] = s;
+    }
+    __syncthreads();
+    if (threadIdx.x < 17) {
+        const int c = threadIdx.x;
+        atomicAdd(c < 16 ? &dw[c] : db, ((red[0][c] + red[1][c]) + red[2][c]) + red[3][c]);
+    }
 }
 
 __global__ __launch_bounds__(256) void k_mse(const float *pred, const float *target, const uint8_t *mask,
@@ -1087,6 +1220,27 @@ bool runs8(int c, int ld1, int off1, int ld2, int off2) { return ((c | ld1 | off
 
 }  // namespace
 
+static bool aligned16(const void *a, const void *b, const void *c) {
+    return ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b) | reinterpret_cast<uintptr_t>(c)) & 15) == 0;
+}
+
+template <bool RELU>
+static int head_bwd(const uint16_t *x, int32_t ldx, const float *w, const float *dout, uint16_t *dx, float *dw, float *db,
+                    int64_t nvox, int32_t c, void *stream) {
+    if (!x || !w || !dout || !dx || !dw || !db || nvox <= 0 || c <= 0 || c > kHeadMaxC || ldx < c) return -1;
+    (void)hipGetLastError();
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (c == 16 && ldx % 8 == 0 && aligned16(x, dx, nullptr)) {
+        const dim3 g((unsigned)std::min<int64_t>((nvox + 255) / 256, 512));
+        hipLaunchKernelGGL(k_head_bwd16<RELU>, g, dim3(256), 0, st, x, ldx, w, dout, dx, dw, db, nvox);
+        return status(hipGetLastError());
+    }
+    if (RELU) return -1;
+    const dim3 g((unsigned)std::min<int64_t>((nvox + 255) / 256, 1024));
+    hipLaunchKernelGGL(k_head_bwd, g, dim3(256), 0, st, x, ldx, w, dout, dx, dw, db, nvox, c);
+    return status(hipGetLastError());
+}
+
 extern "C" {
 
 int32_t unet_kpad(int32_t cin) { return kpad_of(cin); }
@@ -1125,9 +1279,11 @@ static int launch_conv(ConvArgs a, int64_t nx2, int64_t ny2, int64_t nz2, void *
         const dim3 g((unsigned)nxy, (unsigned)((nz + zr - 1) / zr), (unsigned)(tiles / nt)), blk(256);
         (void)hipGetLastError();
         if (a.hout)
-            hipLaunchKernelGGL(k_conv_zm<true>, g, blk, 0, static_cast<hipStream_t>(stream), a, (int)zr);
+            hipLaunchKernelGGL((k_conv_zm<true, false>), g, blk, 0, static_cast<hipStream_t>(stream), a, (int)zr);
+        else if (a.m)
+            hipLaunchKernelGGL((k_conv_zm<false, true>), g, blk, 0, static_cast<hipStream_t>(stream), a, (int)zr);
         else
-            hipLaunchKernelGGL(k_conv_zm<false>, g, blk, 0, static_cast<hipStream_t>(stream), a, (int)zr);
+            hipLaunchKernelGGL((k_conv_zm<false, false>), g, blk, 0, static_cast<hipStream_t>(stream), a, (int)zr);
         return status(hipGetLastError());
     }
     const bool large = nxy * ((nz + 3) / 4) * (tiles / nt) >= kZcLargeGrid;
@@ -1146,7 +1302,7 @@ int unet_conv3d_fwd(const uint16_t *x, int32_t ldx, int32_t offx, const uint16_t
                     int32_t ldy, int32_t offy, float *y32, int32_t nz, int32_t ny, int32_t nx, int32_t cin,
                     int32_t cout, int32_t relu, void *stream) {
     ConvArgs a{x, w, b, y, y32, ldx, offx, ldy, offy, nz, ny, nx, cin, cout, 0, relu, 0, 0, 0,
-               x, ldx, offx, cin, 0, 0, 0, nullptr, nullptr, nullptr, nullptr};
+               x, ldx, offx, cin, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0};
     return launch_conv(a, nx, ny, nz, stream);
 }
 
@@ -1156,7 +1312,7 @@ int unet_conv3d_fwd_head(const uint16_t *x, int32_t ldx, int32_t offx, const uin
     if (!hw || !hb || !out) return -1;
     // 16 -> 16 channels with ReLU, then the head; the BF16 outputs are not stored
     ConvArgs a{x, w, b, nullptr, nullptr, ldx, offx, 16, 0, nz, ny, nx, 16, 16, 0, 1, 0, 0, 0,
-               x, ldx, offx, 16, 0, 0, 0, hw, hb, base, out};
+               x, ldx, offx, 16, 0, 0, 0, hw, hb, base, out, nullptr, 0, 0};
     return launch_conv(a, nx, ny, nz, stream);
 }
 
@@ -1166,7 +1322,7 @@ int unet_conv3d_fwd_cat(const uint16_t *x, int32_t ldx, int32_t offx, int32_t ci
                         void *stream) {
     if (nz % 2 || ny % 2 || nx % 2) return -1;  // x2 holds the half-resolution grid
     ConvArgs a{x, w, b, y, y32, ldx, offx, ldy, offy, nz, ny, nx, cin, cout, 0, relu, 0, 0, 0,
-               x2, ldx2, offx2, cin1, 1, 0, 0, nullptr, nullptr, nullptr, nullptr};
+               x2, ldx2, offx2, cin1, 1, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0};
     if (cin1 >= cin) return -1;
     return launch_conv(a, nx / 2, ny / 2, nz / 2, stream);
 }
@@ -1255,11 +1411,7 @@ int unet_pool_fwd(const uint16_t *x, int32_t ldx, int32_t offx, uint16_t *y, int
 
 int unet_pool_bwd(const uint16_t *dy, int32_t ldy, int32_t offy, uint16_t *dx, int32_t ldx, int32_t offx, int32_t nz,
                   int32_t ny, int32_t nx, int32_t c, void *stream) {
-    if (!dy || !dx || (nz | ny | nx) & 1 || nz <= 0 || !ch_ok(ldx, offx, c) || !ch_ok(ldy, offy, c)) return -1;
-    (void)hipGetLastError();
-    hipLaunchKernelGGL(k_pool_bwd, grid1((int64_t)nz * ny * nx * c), dim3(256), 0, static_cast<hipStream_t>(stream),
-                       dy, ldy, offy, dx, ldx, offx, nz, ny, nx, c);
-    return status(hipGetLastError());
+    return unet::pool_bwd_relu(dy, ldy, offy, dx, ldx, offx, nullptr, 0, 0, nz, ny, nx, c, stream);
 }
 
 int unet_up_fwd(const uint16_t *x, int32_t ldx, int32_t offx, uint16_t *y, int32_t ldy, int32_t offy, int32_t nz,
@@ -1278,11 +1430,7 @@ int unet_up_fwd(const uint16_t *x, int32_t ldx, int32_t offx, uint16_t *y, int32
 
 int unet_up_bwd(const uint16_t *dy, int32_t ldy, int32_t offy, uint16_t *dx, int32_t ldx, int32_t offx, int32_t nz,
                 int32_t ny, int32_t nx, int32_t c, void *stream) {
-    if (!dy || !dx || (nz | ny | nx) & 1 || nz <= 0 || !ch_ok(ldx, offx, c) || !ch_ok(ldy, offy, c)) return -1;
-    (void)hipGetLastError();
-    hipLaunchKernelGGL(k_up_bwd, grid1((int64_t)nz * ny * nx / 8 * c), dim3(256), 0,
-                       static_cast<hipStream_t>(stream), dy, ldy, offy, dx, ldx, offx, nz, ny, nx, c);
-    return status(hipGetLastError());
+    return unet::up_bwd_relu(dy, ldy, offy, dx, ldx, offx, nullptr, 0, 0, nz, ny, nx, c, stream);
 }
 
 int unet_head_fwd(const uint16_t *x, int32_t ldx, const float *w, const float *b, const float *base, float *out,
@@ -1300,12 +1448,7 @@ int unet_head_fwd(const uint16_t *x, int32_t ldx, const float *w, const float *b
 
 int unet_head_bwd(const uint16_t *x, int32_t ldx, const float *w, const float *dout, uint16_t *dx, float *dw,
                   float *db, int64_t nvox, int32_t c, void *stream) {
-    if (!x || !w || !dout || !dx || !dw || !db || nvox <= 0 || c <= 0 || c > kHeadMaxC || ldx < c) return -1;
-    (void)hipGetLastError();
-    const dim3 g((unsigned)std::min<int64_t>((nvox + 255) / 256, 1024));
-    hipLaunchKernelGGL(k_head_bwd, g, dim3(256), 0, static_cast<hipStream_t>(stream), x, ldx, w, dout, dx, dw, db,
-                       nvox, c);
-    return status(hipGetLastError());
+    return head_bwd<false>(x, ldx, w, dout, dx, dw, db, nvox, c, stream);
 }
 
 int unet_mse(const float *pred, const float *target, const uint8_t *mask, const float *weight, float *dout,
@@ -1388,3 +1531,63 @@ int unet_mfma_selftest(const float *a, const float *b, float *d, void *stream) {
 }
 
 }  // extern "C"
+
+namespace unet {
+
+int conv3d_dgrad_relu(const uint16_t *dy, int ldy, int offy, const uint16_t *wt, uint16_t *dx, int ldx, int offx,
+                      const uint16_t *m, int ldm, int offm, int nz, int ny, int nx, int cout, int cin, void *stream) {
+    if (!m || ldm % 8 || offm % 8 || !ch_ok(ldm, offm, cin) || !aligned16(m, nullptr, nullptr)) return -1;
+    ConvArgs a{dy, wt, nullptr, dx, nullptr, ldy, offy, ldx, offx, nz, ny, nx, cout, cin, 0, 0, 0, 0, 0,
+               dy, ldy, offy, cout, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, m, ldm, offm};
+    return launch_conv(a, nx, ny, nz, stream);
+}
+
+int pool_bwd_relu(const uint16_t *dy, int ldy, int offy, uint16_t *dx, int ldx, int offx, const uint16_t *m, int ldm,
+                  int offm, int nz, int ny, int nx, int c, void *stream) {
+    if (!dy || !dx || (nz | ny | nx) & 1 || nz <= 0 || !ch_ok(ldx, offx, c) || !ch_ok(ldy, offy, c)) return -1;
+    (void)hipGetLastError();
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (runs8(c, ldx | ldm, offx | offm, ldy, offy) && aligned16(dy, dx, m) && (int64_t)nz * ny * nx * (c / 8) < ((int64_t)1 << 32)) {
+        hipLaunchKernelGGL(k_pool_bwd8, grid1((int64_t)nz * ny * nx * (c / 8)), dim3(256), 0, st, dy, ldy, offy, dx, ldx,
+                           offx, m, ldm, offm, (uint32_t)nz, (uint32_t)ny, (uint32_t)nx, (uint32_t)(c / 8));
+        return status(hipGetLastError());
+    }
+    if (m) return -1;
+    hipLaunchKernelGGL(k_pool_bwd, grid1((int64_t)nz * ny * nx * c), dim3(256), 0, st, dy, ldy, offy, dx, ldx, offx, nz,
+                       ny, nx, c);
+    return status(hipGetLastError());
+}
+
+int up_bwd_relu(const uint16_t *dy, int ldy, int offy, uint16_t *dx, int ldx, int offx, const uint16_t *m, int ldm,
+                int offm, int nz, int ny, int nx, int c, void *stream) {
+    if (!dy || !dx || (nz | ny | nx) & 1 || nz <= 0 || !ch_ok(ldx, offx, c) || !ch_ok(ldy, offy, c)) return -1;
+    (void)hipGetLastError();
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    if (runs8(c, ldx | ldm, offx | offm, ldy, offy) && aligned16(dy, dx, m) &&
+        (int64_t)nz * ny * nx / 8 * (c / 8) < ((int64_t)1 << 32)) {
+        hipLaunchKernelGGL(k_up_bwd8, grid1((int64_t)nz * ny * nx / 8 * (c / 8)), dim3(256), 0, st, dy, ldy, offy, dx, ldx,
+                           offx, m, ldm, offm, (uint32_t)nz, (uint32_t)ny, (uint32_t)nx, (uint32_t)(c / 8));
+        return status(hipGetLastError());
+    }
+    if (m) return -1;
+    hipLaunchKernelGGL(k_up_bwd, grid1((int64_t)nz * ny * nx / 8 * c), dim3(256), 0, st, dy, ldy, offy, dx, ldx, offx, nz,
+                       ny, nx, c);
+    return status(hipGetLastError());
+}
+
+int head_bwd_relu(const uint16_t *x, int ldx, const float *w, const float *dout, uint16_t *dx, float *dw, float *db,
+                  int64_t nvox, int c, void *stream) {
+    return head_bwd<true>(x, ldx, w, dout, dx, dw, db, nvox, c, stream);
+}
+
+int conv3d_wtrans_all(const uint16_t *w, uint16_t *wt, const TransTable &t, void *stream) {
+    if (!w || !wt || t.n <= 0 || t.n > kMaxTrans) return -1;
+    int64_t most = 0;
+    for (int l = 0; l < t.n; ++l) most = std::max<int64_t>(most, (int64_t)t.cin[l] * kpad_of(t.cout[l]));
+    (void)hipGetLastError();
+    hipLaunchKernelGGL(k_wtrans_all, dim3((unsigned)std::min<int64_t>((most + 255) / 256, 256), (unsigned)t.n), dim3(256), 0,
+                       static_cast<hipStream_t>(stream), w, wt, t);
+    return status(hipGetLastError());
+}
+
+}  // namespace unet

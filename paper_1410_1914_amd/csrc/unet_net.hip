@@ -17,6 +17,7 @@
 #include <new>
 
 #include "include/unet.h"
+#include "unet_kernels.h"
 
 namespace {
 
@@ -72,6 +73,8 @@ struct unet_net {
     int dims[4][3];
     int64_t vox[4];
     ParamLayout P;
+    unet::TransTable trans{};
+    int64_t wt_off[kLayers] = {};
     size_t off_p, off_pb, off_g, off_m, off_v, off_act[A_COUNT], off_out, off_gact[A_COUNT], off_gout, off_wt,
         off_loss, bytes;
     char *ws = nullptr;
@@ -116,10 +119,17 @@ struct unet_net {
         if (train) {
             for (int a = A_A1; a < A_COUNT; ++a) off_gact[a] = take(sizeof(uint16_t) * vox[kActLevel[a]] * kActCh[a]);
             off_gout = take(sizeof(float) * vox[0]);
+            // transposed weights of every layer with a backward data convolution (all but the first)
             int64_t wt = 0;
+            trans.n = 0;
             for (int l = 0; l < kLayers; ++l) {
-                const int64_t n = (int64_t)kSpec[l].cin * unet_kpad(kSpec[l].cout);
-                wt = n > wt ? n : wt;
+                if (l == E1A) continue;
+                const int k = trans.n++;
+                trans.cin[k] = kSpec[l].cin;
+                trans.cout[k] = kSpec[l].cout;
+                trans.w_off[k] = P.w[l];
+                trans.wt_off[k] = wt_off[l] = wt;
+                wt = align64(wt + (int64_t)kSpec[l].cin * unet_kpad(kSpec[l].cout));
             }
             off_wt = take(sizeof(uint16_t) * wt);
             off_loss = take(sizeof(float) * 64);
@@ -201,63 +211,61 @@ struct unet_net {
         return e;
     }
 
-    // Backward of one convolution: gy holds dL/dy (after the ReLU) and becomes
-    // dL/d(pre-activation); the weight and bias gradients accumulate into g();
-    // dL/dx is written into gx unless gx is null.
-    hipError_t conv_bwd(int l, const uint16_t *x, int ldx, int offx, const uint16_t *y, int ldy, int offy, uint16_t *gy,
-                        int ldg, int offg, uint16_t *gx, int ldgx, int offgx, int lev) {
+    // Backward of one convolution: gy holds dL/d(pre-activation); the weight and bias
+    // gradients accumulate into g(); dL/dx is written into gx unless gx is null, masked by
+    // the ReLU of the activation m it belongs to unless m is null.
+    hipError_t conv_bwd(int l, const uint16_t *x, int ldx, const uint16_t *gy, int ldg, uint16_t *gx, int ldgx,
+                        const uint16_t *m, int lev) {
         const int *d = dims[lev];
         const int cin = kSpec[l].cin, cout = kSpec[l].cout;
-        int s = unet_relu_bwd(y, ldy, offy, gy, ldg, offg, vox[lev], cout, st);
-        if (s == 0)
-            s = unet_conv3d_wgrad(x, ldx, offx, gy, ldg, offg, d[0], d[1], d[2], cin, cout, g() + P.w[l], g() + P.b[l],
-                                  st);
+        int s = unet_conv3d_wgrad(x, ldx, 0, gy, ldg, 0, d[0], d[1], d[2], cin, cout, g() + P.w[l], g() + P.b[l], st);
         if (s == 0 && gx) {
-            uint16_t *wt = at<uint16_t>(off_wt);
-            s = unet_conv3d_wtrans(pb() + P.w[l], wt, cin, cout, st);
-            if (s == 0)
-                s = unet_conv3d_fwd(gy, ldg, offg, wt, nullptr, gx, ldgx, offgx, nullptr, d[0], d[1], d[2], cout, cin, 0,
-                                    st);
+            const uint16_t *wt = at<uint16_t>(off_wt) + wt_off[l];
+            s = m ? unet::conv3d_dgrad_relu(gy, ldg, 0, wt, gx, ldgx, 0, m, ldgx, 0, d[0], d[1], d[2], cout, cin, st)
+                  : unet_conv3d_fwd(gy, ldg, 0, wt, nullptr, gx, ldgx, 0, nullptr, d[0], d[1], d[2], cout, cin, 0, st);
         }
         return to_hip(s);
     }
 
+    // Every gradient is written once with the ReLU mask of its activation already applied:
+    // by the convolution after it, by upsampling's adjoint (decoder outputs), or, for a skip
+    // tensor, by pooling's adjoint, which adds the encoder's part to the decoder's (the
+    // convolution over the concatenation writes all of its channels first).
     hipError_t backward(const uint16_t *feat, const float *dout) {
         hipError_t e = to_hip(unet_zero(g(), (int64_t)sizeof(float) * P.total, st));
         auto run = [&](hipError_t r) {
             if (e == hipSuccess) e = r;
         };
-        for (int a : {A_CAT1, A_CAT2, A_CAT3})
-            run(to_hip(unet_zero(gact(a), (int64_t)sizeof(uint16_t) * vox[kActLevel[a]] * kActCh[a], st)));
         const int *d0 = dims[0], *d1 = dims[1], *d2 = dims[2];
-        run(to_hip(unet_head_bwd(act(A_D1B), kC1, p() + P.w[kLayers], dout, gact(A_D1B), g() + P.w[kLayers],
-                                 g() + P.b[kLayers], vox[0], kC1, st)));
-        run(conv_bwd(D1B, act(A_D1A), kC1, 0, act(A_D1B), kC1, 0, gact(A_D1B), kC1, 0, gact(A_D1A), kC1, 0, 0));
-        run(conv_bwd(D1A, act(A_CAT1), kC1 + kC2, 0, act(A_D1A), kC1, 0, gact(A_D1A), kC1, 0, gact(A_CAT1), kC1 + kC2,
-                     0, 0));
-        run(to_hip(unet_up_bwd(gact(A_CAT1), kC1 + kC2, kC1, gact(A_D2B), kC2, 0, d0[0], d0[1], d0[2], kC2, st)));
-        run(conv_bwd(D2B, act(A_D2A), kC2, 0, act(A_D2B), kC2, 0, gact(A_D2B), kC2, 0, gact(A_D2A), kC2, 0, 1));
-        run(conv_bwd(D2A, act(A_CAT2), kC2 + kC3, 0, act(A_D2A), kC2, 0, gact(A_D2A), kC2, 0, gact(A_CAT2), kC2 + kC3,
-                     0, 1));
-        run(to_hip(unet_up_bwd(gact(A_CAT2), kC2 + kC3, kC2, gact(A_D3B), kC3, 0, d1[0], d1[1], d1[2], kC3, st)));
-        run(conv_bwd(D3B, act(A_D3A), kC3, 0, act(A_D3B), kC3, 0, gact(A_D3B), kC3, 0, gact(A_D3A), kC3, 0, 2));
-        run(conv_bwd(D3A, act(A_CAT3), kC3 + kC4, 0, act(A_D3A), kC3, 0, gact(A_D3A), kC3, 0, gact(A_CAT3), kC3 + kC4,
-                     0, 2));
-        run(to_hip(unet_up_bwd(gact(A_CAT3), kC3 + kC4, kC3, gact(A_B4B), kC4, 0, d2[0], d2[1], d2[2], kC4, st)));
-        run(conv_bwd(B4B, act(A_B4A), kC4, 0, act(A_B4B), kC4, 0, gact(A_B4B), kC4, 0, gact(A_B4A), kC4, 0, 3));
-        run(conv_bwd(B4A, act(A_P4), kC3, 0, act(A_B4A), kC4, 0, gact(A_B4A), kC4, 0, gact(A_P4), kC3, 0, 3));
-        run(to_hip(unet_pool_bwd(gact(A_P4), kC3, 0, gact(A_CAT3), kC3 + kC4, 0, d2[0], d2[1], d2[2], kC3, st)));
-        run(conv_bwd(E3B, act(A_A3), kC3, 0, act(A_CAT3), kC3 + kC4, 0, gact(A_CAT3), kC3 + kC4, 0, gact(A_A3), kC3, 0,
-                     2));
-        run(conv_bwd(E3A, act(A_P3), kC2, 0, act(A_A3), kC3, 0, gact(A_A3), kC3, 0, gact(A_P3), kC2, 0, 2));
-        run(to_hip(unet_pool_bwd(gact(A_P3), kC2, 0, gact(A_CAT2), kC2 + kC3, 0, d1[0], d1[1], d1[2], kC2, st)));
-        run(conv_bwd(E2B, act(A_A2), kC2, 0, act(A_CAT2), kC2 + kC3, 0, gact(A_CAT2), kC2 + kC3, 0, gact(A_A2), kC2, 0,
-                     1));
-        run(conv_bwd(E2A, act(A_P2), kC1, 0, act(A_A2), kC2, 0, gact(A_A2), kC2, 0, gact(A_P2), kC1, 0, 1));
-        run(to_hip(unet_pool_bwd(gact(A_P2), kC1, 0, gact(A_CAT1), kC1 + kC2, 0, d0[0], d0[1], d0[2], kC1, st)));
-        run(conv_bwd(E1B, act(A_A1), kC1, 0, act(A_CAT1), kC1 + kC2, 0, gact(A_CAT1), kC1 + kC2, 0, gact(A_A1), kC1, 0,
-                     0));
-        run(conv_bwd(E1A, feat, kIn, 0, act(A_A1), kC1, 0, gact(A_A1), kC1, 0, nullptr, 0, 0, 0));
+        run(to_hip(unet::conv3d_wtrans_all(pb(), at<uint16_t>(off_wt), trans, st)));
+        run(to_hip(unet::head_bwd_relu(act(A_D1B), kC1, p() + P.w[kLayers], dout, gact(A_D1B), g() + P.w[kLayers],
+                                       g() + P.b[kLayers], vox[0], kC1, st)));
+        run(conv_bwd(D1B, act(A_D1A), kC1, gact(A_D1B), kC1, gact(A_D1A), kC1, act(A_D1A), 0));
+        run(conv_bwd(D1A, act(A_CAT1), kC1 + kC2, gact(A_D1A), kC1, gact(A_CAT1), kC1 + kC2, nullptr, 0));
+        run(to_hip(unet::up_bwd_relu(gact(A_CAT1), kC1 + kC2, kC1, gact(A_D2B), kC2, 0, act(A_D2B), kC2, 0, d0[0], d0[1],
+                                     d0[2], kC2, st)));
+        run(conv_bwd(D2B, act(A_D2A), kC2, gact(A_D2B), kC2, gact(A_D2A), kC2, act(A_D2A), 1));
+        run(conv_bwd(D2A, act(A_CAT2), kC2 + kC3, gact(A_D2A), kC2, gact(A_CAT2), kC2 + kC3, nullptr, 1));
+        run(to_hip(unet::up_bwd_relu(gact(A_CAT2), kC2 + kC3, kC2, gact(A_D3B), kC3, 0, act(A_D3B), kC3, 0, d1[0], d1[1],
+                                     d1[2], kC3, st)));
+        run(conv_bwd(D3B, act(A_D3A), kC3, gact(A_D3B), kC3, gact(A_D3A), kC3, act(A_D3A), 2));
+        run(conv_bwd(D3A, act(A_CAT3), kC3 + kC4, gact(A_D3A), kC3, gact(A_CAT3), kC3 + kC4, nullptr, 2));
+        run(to_hip(unet::up_bwd_relu(gact(A_CAT3), kC3 + kC4, kC3, gact(A_B4B), kC4, 0, act(A_B4B), kC4, 0, d2[0], d2[1],
+                                     d2[2], kC4, st)));
+        run(conv_bwd(B4B, act(A_B4A), kC4, gact(A_B4B), kC4, gact(A_B4A), kC4, act(A_B4A), 3));
+        run(conv_bwd(B4A, act(A_P4), kC3, gact(A_B4A), kC4, gact(A_P4), kC3, nullptr, 3));
+        run(to_hip(unet::pool_bwd_relu(gact(A_P4), kC3, 0, gact(A_CAT3), kC3 + kC4, 0, act(A_CAT3), kC3 + kC4, 0, d2[0],
+                                       d2[1], d2[2], kC3, st)));
+        run(conv_bwd(E3B, act(A_A3), kC3, gact(A_CAT3), kC3 + kC4, gact(A_A3), kC3, act(A_A3), 2));
+        run(conv_bwd(E3A, act(A_P3), kC2, gact(A_A3), kC3, gact(A_P3), kC2, nullptr, 2));
+        run(to_hip(unet::pool_bwd_relu(gact(A_P3), kC2, 0, gact(A_CAT2), kC2 + kC3, 0, act(A_CAT2), kC2 + kC3, 0, d1[0],
+                                       d1[1], d1[2], kC2, st)));
+        run(conv_bwd(E2B, act(A_A2), kC2, gact(A_CAT2), kC2 + kC3, gact(A_A2), kC2, act(A_A2), 1));
+        run(conv_bwd(E2A, act(A_P2), kC1, gact(A_A2), kC2, gact(A_P2), kC1, nullptr, 1));
+        run(to_hip(unet::pool_bwd_relu(gact(A_P2), kC1, 0, gact(A_CAT1), kC1 + kC2, 0, act(A_CAT1), kC1 + kC2, 0, d0[0],
+                                       d0[1], d0[2], kC1, st)));
+        run(conv_bwd(E1B, act(A_A1), kC1, gact(A_CAT1), kC1 + kC2, gact(A_A1), kC1, act(A_A1), 0));
+        run(conv_bwd(E1A, feat, kIn, gact(A_A1), kC1, nullptr, 0, nullptr, 0));
         return e;
     }
 };
