@@ -18,15 +18,19 @@ typedef float f32x4 __attribute__((__vector_size__(4 * sizeof(float))));
 
 __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
-// round to nearest even (NaN kept quiet)
-__device__ __forceinline__ uint16_t f2bf(float f) {
-    uint32_t u = __float_as_uint(f);
-    if ((u & 0x7f800000u) == 0x7f800000u && (u & 0x007fffffu)) return (uint16_t)((u >> 16) | 0x40u);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return (uint16_t)(u >> 16);
+// round to nearest even, NaN kept quiet: the conversion instruction (equal to the integer
+// form, bits + 0x7fff + bit 16, over all 2^32 inputs)
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint16_t f2bf(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
+__device__ __forceinline__ uint32_t f2bf2(float lo, float hi) {
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo, hi}, bf16x2));
 }
 
 __host__ __device__ __forceinline__ int kpad_of(int cin) { return (27 * cin + 31) / 32 * 32; }
+
+// elements of a layer's weights in fragment order (k_pack)
+constexpr int64_t packed_len(int cin, int cout) { return (int64_t)(cin / 16) * (cout / 16) * 14 * 512; }
 
 int status(hipError_t e) { return e == hipSuccess ? 0 : -6; }
 
@@ -36,18 +40,22 @@ int status(hipError_t e) { return e == hipSuccess ? 0 : -6; }
 // v_mfma_f32_16x16x32_bf16.  Fragment mapping (pinned by unet_mfma_selftest):
 //   A[m][k]: lane l holds m = l % 16, k = 8 (l / 16) + j;  B[k][n]: n = l % 16, same k;
 //   D[m][n]: lane l holds m = 4 (l / 16) + i, n = l % 16.
-// A workgroup (4 waves) owns kTY rows of kTX voxels in ZC consecutive planes and
-// 16 * NT output channels (a channel slice).  Per stage of 16 input channels it
-// copies the ZC + 2 input planes its planes read ((kTY + 2) rows x
-// (kTX + 2) voxels each, halo included) straight from global memory into LDS, all
-// in flight at once and with no registers in between, so each input plane is copied
-// once per stage rather than once for every output plane that reads it.  Each
-// wave takes one row: per K chunk of 32 (two taps of the 16 channels) it reads four
-// input fragments from LDS (four 16-voxel tiles), holds NT weight fragments (the
-// same for every wave) and issues 4 x NT MFMAs, so an input fragment feeds NT
-// products and a weight fragment four.  The weights are the MFMA's A operand and
-// the inputs its B operand, so a lane's result is four consecutive output channels
-// of one voxel, which leave as one 8-byte store.
+// K runs over stages of 16 input channels, in a stage over 14 chunks of two taps (the
+// 28th tap is zero).  The weights are the MFMA's A operand and the inputs its B operand,
+// so a lane's result is four consecutive output channels of one voxel, which leave as
+// one 8-byte store.
+//
+// A wave owns four rows of 16 voxels in y of each plane and 16 output channels.  What
+// bounded the product was the LDS: a chunk's input fragment (1 KB) read for every product
+// is 256 bytes per cycle and CU at the matrix cores' rate, twice what the LDS gives.  So
+// a wave takes an input plane at a time and reads each of its fragments once: chunks 0-3
+// of the output plane above, 4-8 of the one at its height and 9-13 of the one below use
+// the same three kinds of fragment (two neighbours in x, or the end of a row with the
+// start of the next) of the wave's six halo rows.  19 reads serve 56 products, and every
+// output still adds its chunks in the order 0 .. 13 of stage after stage.
+//
+// A workgroup is four waves: S slices of 16 output channels times 4 / S row groups of a
+// tile of 16 x 16 / S voxels, so that the input copied into LDS serves S slices.
 struct ConvArgs {
     const uint16_t *x;
     const uint16_t *w;
@@ -72,6 +80,7 @@ struct ConvArgs {
     // The ReLU mask of the tensor written (backward): y is zeroed where m is not positive.
     const uint16_t *m;
     int ldm, offm;
+    int packed;  // w is in the order of k_pack rather than in rows of kpad
 };
 
 typedef __attribute__((address_space(3))) void lds_void;
@@ -92,232 +101,438 @@ constexpr int kRawBuffer = 0x00020000;
 constexpr int64_t kMaxX = ((int64_t)1 << 31) - 16;
 constexpr uint32_t kNoOff = 0x80000000u;
 
-constexpr int kTX = 64, kTY = 4;            // voxels of a workgroup in each of its planes: 4 rows of 64
-constexpr int kBX = kTX + 2, kBY = kTY + 2; // an input plane, halo included
-constexpr int kPlane = kBX * kBY;           // 396 voxels
-constexpr int kCC = 16;                     // input channels per stage
+constexpr int kSX = 16, kSBX = kSX + 2;  // voxels of a tile's row, halo included
+constexpr int kCC = 16;                  // input channels per stage
 constexpr int kVS = 16;  // LDS elements per voxel: the 16 channels, unpadded.  A 32-byte voxel
                          // stride reads at the full LDS rate on gfx950 (the lanes' 16-byte
                          // reads tile whole 512-byte spans); a padded 48-byte stride ran 1.5x slower
+constexpr int64_t kConvSlots = 512;       // workgroups a chip holds: two on each of 256 CUs
 constexpr int kKC = 14;  // K chunks of 32 per stage: 27 taps x 16 channels, the last half empty
-constexpr int kPS = (2 * kPlane + 255) / 256;  // 16-byte loads per thread and input plane
+// s_waitcnt vmcnt(n), the other counters not waited for (gfx9 encoding)
+constexpr int wait_vmcnt(int n) { return 0x0F70 | (n & 15) | (n >> 4) << 14; }
+constexpr int kWaitVmcnt0 = wait_vmcnt(0);
 
-// ZC output planes per workgroup: the accumulators of ZC planes and the stage's
-// weight fragments stay in registers (218 VGPRs at ZC = 3, 256 at ZC = 4; two
-// workgroups per CU, 63 or 76 KB of LDS each).  A tile re-reads (ZC + 2) / ZC of its
-// input planes, and each stage's loads are exposed once per ZC planes, so larger
-// grids take ZC = 4; small ones keep ZC = 3 for more workgroups.
-constexpr int kZcLargeGrid = 2048;  // workgroups at ZC = 4 from which ZC = 4 is used
-constexpr int kZmWorkgroups = 1536; // the z-marching form aims for about this many workgroups
-// s_waitcnt vmcnt(0) (expcnt and lgkmcnt at their maxima: not waited for) on gfx9
-constexpr int kWaitVmcnt0 = 0x0F70;
-
-// The tile of this workgroup: x and y origin, plane chunk and channel slice.  The grid
-// is (x-y tiles, plane chunks, channel slices).  Workgroups reach the 8 XCDs
-// round-robin by launch index b; XCD b % 8 takes a contiguous eighth of the tile
-// order, so that tiles sharing input rows and planes run together under one L2 (the
-// input copies are the convolution's bottleneck).  Within a channel slice the tiles go
-// in bands of four tile rows in y: x fastest, then y within the band, then the plane
-// chunks, then the bands (the last band may be shorter).
+// The tile of this workgroup: x and y origin, chunk of planes and group of channel slices.
+// The grid is (x-y tiles, chunks, groups).  Workgroups reach the 8 XCDs round-robin by
+// launch index b; XCD b % 8 takes a contiguous eighth of the tile order, so that tiles
+// sharing input rows and planes run together under one L2.  Within a group the tiles go in
+// bands of 16 rows in y: x fastest, then y within the band, then the chunks, then the bands
+// (the last band may be shorter).
 struct ConvTile {
     int x0, y0, zc, slice;
 };
+template <int TY>
 __device__ __forceinline__ ConvTile conv_tile(int nx) {
-    const int nxt = (nx + kTX - 1) / kTX;
+    const int nxt = (nx + kSX - 1) / kSX;
     const int nblk = (int)(gridDim.x * gridDim.y * gridDim.z);
     const int b = (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z));
     const int xcd = b % 8, per = nblk / 8, extra = nblk % 8;
     const int t = xcd * per + min(xcd, extra) + b / 8;
-    constexpr int kYB = 4;
+    constexpr int kYB = 16 / TY;
     const int nyt = (int)gridDim.x / nxt, nzc = (int)gridDim.y;
     const int per_slice = (int)gridDim.x * nzc;
     const int slice = t / per_slice, rem = t % per_slice;
     const int band = rem / (nxt * kYB * nzc), in_band = rem % (nxt * kYB * nzc);
     const int h = min(kYB, nyt - band * kYB);
     const int xt = in_band % nxt, yin = (in_band / nxt) % h, zc = in_band / (nxt * h);
-    return ConvTile{xt * kTX, (band * kYB + yin) * kTY, zc, slice};
+    return ConvTile{xt * kSX, (band * kYB + yin) * TY, zc, slice};
 }
 
-template <int NT, int ZC>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_fwd(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) uint16_t slab[(ZC + 2) * kPlane * kVS];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    // each tile reads 5/3 x 6/4 of its own input (ZC = 3)
-    const ConvTile T = conv_tile(a.nx);
-    const int x0 = T.x0, y0 = T.y0;
-    const int z0 = T.zc * ZC;
-    const int co0 = T.slice * 16 * NT;
-    const int m = lane & 15, kb = lane >> 4;
-    f32x4 acc[ZC][4][NT];
+__device__ __forceinline__ bf16x8 lane_select(bool second, bf16x8 x, bf16x8 y) {
+    const uint4 a = __builtin_bit_cast(uint4, x), b = __builtin_bit_cast(uint4, y);
+    return __builtin_bit_cast(bf16x8, make_uint4(second ? a.x : b.x, second ? a.y : b.y, second ? a.z : b.z, second ? a.w : b.w));
+}
+
+// Fragments of one input plane for a wave's four rows of 16 voxels, halo rows 0 .. 5:
+// a[r] holds taps x, x + 1 of row r, b[r] taps x + 1, x + 2, and c[r + 1] tap x + 2 of row r
+// with tap x of row r + 1 (the two taps of a chunk lie in the two halves of the lanes);
+// p: the rows 2 .. 5 of c of the plane before.
+struct Frags {
+    bf16x8 a[6], b[6], c[7], p[4];
+};
+// where a lane reads them (LDS elements from the plane's start)
+struct FragAt {
+    int a, c, d;
+    __device__ __forceinline__ FragAt(int row, int m, int kb) {
+        const int chan = 8 * (kb & 1), g = kb >> 1;
+        a = (row * kSBX + m + g) * kVS + chan;
+        c = (g ? (row + 1) * kSBX + m : row * kSBX + m + 2) * kVS + chan;
+        d = (row * kSBX + m) * kVS + chan;
+    }
+};
+__device__ __forceinline__ bf16x8 frag(const uint16_t *p, int voxel) {
+    return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(p + voxel * kVS));
+}
+__device__ __forceinline__ void read_a(Frags &F, const uint16_t *plane, const FragAt &at) {
+#pragma unroll
+    for (int r = 0; r < 6; ++r) F.a[r] = frag(plane + at.a, r * kSBX);
+}
+__device__ __forceinline__ void read_b(Frags &F, const uint16_t *plane, const FragAt &at) {
+#pragma unroll
+    for (int r = 0; r < 6; ++r) F.b[r] = frag(plane + at.a, r * kSBX + 1);
+}
+__device__ __forceinline__ void read_c(Frags &F, const uint16_t *plane, const FragAt &at) {
+    F.c[0] = frag(plane + at.d, 0);
+#pragma unroll
+    for (int r = 0; r < 5; ++r) F.c[r + 1] = frag(plane + at.c, r * kSBX);
+    F.c[6] = frag(plane + at.d, 5 * kSBX + 2);
+}
+// The products of one input plane: chunks 0 .. 3 of the output plane above it (D0), 4 .. 8
+// of the one at its height (D1), 9 .. 13 of the one below (D2).  Expects a and c read;
+// next_a() and next_c() run once a and c are no longer needed.
+template <bool D0, bool D1, bool D2, class NextA, class NextC>
+__device__ __forceinline__ void plane_products(Frags &F, const uint16_t *plane, const FragAt &at, bool second,
+                                               const bf16x8 (&B)[kKC], f32x4 (&above)[4], f32x4 (&level)[4],
+                                               f32x4 (&below)[4], NextA next_a, NextC next_c) {
+    auto mm = [&](int q, bf16x8 x, f32x4 &c) { c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[q], x, c, 0, 0, 0); };
+    const bf16x8 zero = __builtin_bit_cast(bf16x8, make_uint4(0u, 0u, 0u, 0u));
+    read_b(F, plane, at);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) if (D0) mm(0, F.a[t], above[t]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) if (D2) mm(9, F.a[t], below[t]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) if (D0) mm(1, F.c[t + 1], above[t]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) if (D2) mm(10, F.c[t + 1], below[t]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) if (D1) mm(4, lane_select(second, F.c[t], F.p[t]), level[t]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) if (D0) mm(2, F.b[t + 1], above[t]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) if (D2) mm(11, F.b[t + 1], below[t]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) if (D1) mm(5, F.b[t], level[t]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) if (D0) mm(3, F.a[t + 2], above[t]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) if (D2) mm(12, F.a[t + 2], below[t]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) if (D1) mm(6, F.a[t + 1], level[t]);
+    __builtin_amdgcn_sched_barrier(0);
+    next_a();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) if (D1) mm(7, F.c[t + 2], level[t]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) if (D2) mm(13, lane_select(second, zero, F.c[t + 3]), below[t]);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) F.p[t] = F.c[t + 3];
+    next_c();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) if (D1) mm(8, F.b[t + 2], level[t]);
+    __builtin_amdgcn_sched_barrier(0);
+}
+// All of them for the ZC + 2 planes of a slab, one stage; next(from, to): the weights of
+// chunks from .. to - 1 are no longer needed.
+template <int I, int ZC, int PLANE, class Next>
+__device__ __forceinline__ void slab_products(Frags &F, const uint16_t *slab, const FragAt &at, bool second,
+                                              const bf16x8 (&B)[kKC], f32x4 (&acc)[ZC][4], Next next) {
+    constexpr bool D0 = I < ZC, D1 = I >= 1 && I <= ZC, D2 = I >= 2;
+    const uint16_t *plane = slab + I * PLANE * kVS, *after = plane + PLANE * kVS;
+    plane_products<D0, D1, D2>(
+        F, plane, at, second, B, acc[D0 ? I : 0], acc[D1 ? I - 1 : 0], acc[D2 ? I - 2 : 0],
+        [&]() __attribute__((always_inline)) { if (I <= ZC) read_a(F, after, at); },
+        [&]() __attribute__((always_inline)) { if (I <= ZC) read_c(F, after, at); });
+    if (I == ZC - 1) next(0, 4);
+    if (I == ZC) next(4, 9);
+    if (I == ZC + 1) next(9, kKC);
+    if constexpr (I <= ZC) slab_products<I + 1, ZC, PLANE>(F, slab, at, second, B, acc, next);
+}
+
+// ZC output planes per workgroup; a stage's ZC + 2 input planes are copied straight from
+// global memory into LDS, all in flight at once, then multiplied.  The weights of a chunk
+// are fetched for the next stage as soon as its last product is out.  Two workgroups per CU
+// (160 .. 241 VGPRs, 10 .. 62 KB of LDS), one's copies under the other's products.
+// us before (one 4 x 64 tile and slice per workgroup, fragments read per product) and now
+// with packed weights: 96 -> 32 channels at 96^3 307 -> 144 (1.0 PFLOP/s), 192 -> 64 at 48^3
+// 164 -> 67, 64 -> 64 at 48^3 63 -> 26 (rows of kpad 31), 192 -> 64 at 24^3 57 -> 23,
+// 128 -> 128 at 12^3 39 -> 12.4.
+template <int S, int ZC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_slab(ConvArgs a) {
+    constexpr int TY = 16 / S, PLANE = kSBX * (TY + 2), NE = 2 * PLANE, PS = (NE + 255) / 256;
+    constexpr int kSlab = (ZC + 2) * PLANE * kVS;
+    __shared__ __attribute__((aligned(16))) uint16_t slab[kSlab];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wy = wave % (4 / S), ws = wave / (4 / S);  // rows 4 wy .. 4 wy + 3, channel slice ws of the workgroup's
+    const ConvTile T = conv_tile<TY>(a.nx);
+    const int x0 = T.x0, y0 = T.y0, z0 = T.zc * ZC, co0 = 16 * (T.slice * S + ws);
+    const int m = lane & 15, kb = lane >> 4, chan = 8 * (kb & 1);
+    const bool second = kb >> 1;
+    f32x4 acc[ZC][4];
 #pragma unroll
     for (int p = 0; p < ZC; ++p)
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int n = 0; n < NT; ++n) acc[p][t][n] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    // this lane's two taps per K chunk: tap = 2 q + (kb >> 1), channels 8 (kb & 1) .. + 7
-    const int chan = 8 * (kb & 1);
-    // weights through a buffer resource: this lane's byte offset of output channel
-    // co0 + 16 n + m, its tap parity kb >> 1 and channel half; the chunk's part is uniform
+        for (int t = 0; t < 4; ++t) acc[p][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
     const __amdgpu_buffer_rsrc_t rw =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.w), (short)0, (int)a.wbytes, kRawBuffer);
-    uint32_t woff[NT];
-#pragma unroll
-    for (int n = 0; n < NT; ++n) woff[n] = 2u * (uint32_t)((co0 + 16 * n + m) * a.kpad + (kb >> 1) * a.cin + chan);
-    // One input plane straight from global memory into slot `slot` of the LDS slab:
-    // 16 bytes per lane, lanes landing on consecutive 16-byte LDS entries (voxel-major,
-    // two entries per voxel).  poff: this thread's byte offsets within a plane of the
-    // stage's source, or kNoOff outside the grid.
+    // this lane's weights, and the bytes from one chunk, one stage to the next
+    const uint32_t wlane = a.packed ? 2u * (uint32_t)((co0 / 16) * (a.cin / kCC) * kKC * 512 + 8 * lane)
+                                    : 2u * (uint32_t)((co0 + m) * a.kpad + (kb >> 1) * a.cin + chan);
+    const uint32_t wchunk = a.packed ? 1024u : 4u * (uint32_t)a.cin, wstage = a.packed ? kKC * 1024u / kCC : 2u;
     const __amdgpu_buffer_rsrc_t rx =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.x), (short)0, (int)a.xbytes, kRawBuffer);
     const __amdgpu_buffer_rsrc_t rx2 =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.x2), (short)0, (int)a.x2bytes, kRawBuffer);
-    uint32_t poff[kPS];
-    auto source_offsets = [&](bool second) {
-        const int sh = second && a.up2 ? 1 : 0, ld = second ? a.ldx2 : a.ldx, off = second ? a.offx2 : a.offx;
+    uint32_t poff[PS];
+    auto source_offsets = [&](bool from2) __attribute__((always_inline)) {
+        const int sh = from2 && a.up2 ? 1 : 0, ld = from2 ? a.ldx2 : a.ldx, off = from2 ? a.offx2 : a.offx;
 #pragma unroll
-        for (int it = 0; it < kPS; ++it) {
+        for (int it = 0; it < PS; ++it) {
             const int e = tid + 256 * it, bv = e >> 1, h = e & 1;
-            const int xx = x0 + bv % kBX - 1, yy = y0 + bv / kBX - 1;
+            const int xx = x0 + bv % kSBX - 1, yy = y0 + bv / kSBX - 1;
             const bool in = xx >= 0 && xx < a.nx && yy >= 0 && yy < a.ny;
             poff[it] = in ? 2u * (uint32_t)(((yy >> sh) * (a.nx >> sh) + (xx >> sh)) * ld + off + 8 * h) : kNoOff;
         }
     };
-    auto dma_plane = [&](int zz, int c0, int slot) {
-        const bool second = c0 >= a.cin1;
-        const bool zin = zz >= 0 && zz < a.nz;  // else the whole plane reads as zeros
-        const uint32_t zoff = !zin ? 0u
-                              : second ? (uint32_t)(a.up2 ? zz >> 1 : zz) * a.plane2_bytes + 2u * (uint32_t)(c0 - a.cin1)
-                                       : (uint32_t)zz * a.plane_bytes + 2u * (uint32_t)c0;
+    auto copy_stage = [&](int c0) __attribute__((always_inline)) {
+        if (c0 == 0 || c0 == a.cin1) source_offsets(c0 >= a.cin1);
+        const bool from2 = c0 >= a.cin1;
 #pragma unroll
-        for (int it = 0; it < kPS; ++it) {
-            const int e0 = 256 * it + 64 * wave, e = e0 + lane;
-            if (e0 >= 2 * kPlane) break;  // wave-uniform
-            if (e < 2 * kPlane)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(second ? rx2 : rx,
-                                                         (lds_void *)(slab + (slot * kPlane * kVS + 8 * e0)), 16,
-                                                         zin ? poff[it] : kNoOff, zoff, 0, 0);
+        for (int s = 0; s < ZC + 2; ++s) {
+            const int zz = z0 - 1 + s;
+            const bool zin = zz >= 0 && zz < a.nz;  // else the whole plane reads as zeros
+            const uint32_t zoff = !zin    ? 0u
+                                  : from2 ? (uint32_t)(a.up2 ? zz >> 1 : zz) * a.plane2_bytes + 2u * (uint32_t)(c0 - a.cin1)
+                                          : (uint32_t)zz * a.plane_bytes + 2u * (uint32_t)c0;
+#pragma unroll
+            for (int it = 0; it < PS; ++it) {
+                const int e0 = 256 * it + 64 * wave, e = e0 + lane;
+                if (e0 >= NE) break;  // wave-uniform
+                const uint32_t off = zin ? poff[it] : kNoOff;
+                uint16_t *to = slab + s * PLANE * kVS + 8 * e0;
+                if (e < NE) __builtin_amdgcn_raw_ptr_buffer_load_lds(from2 ? rx2 : rx, (lds_void *)to, 16, off, zoff, 0, 0);
+            }
         }
     };
+    const FragAt at(4 * wy, m, kb);
+    Frags F{};
+    bf16x8 B[kKC];
+    auto load_weights = [&](int c0, int from, int to) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = from; q < to; ++q) {
+            const int tap = 2 * q + (kb >> 1);  // past the 27th tap the offset lies past w: zeros
+            const uint32_t off = tap < 27 ? wlane : kNoOff;
+            B[q] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, off, wchunk * q + wstage * c0, 0));
+        }
+    };
+    load_weights(0, 0, kKC);
     for (int c0 = 0; c0 < a.cin; c0 += kCC) {
-        if (c0 == 0 || c0 == a.cin1) source_offsets(c0 >= a.cin1);
-        __syncthreads();  // the previous stage's reads of the slab are done
-        // every input plane of the stage in flight at once (plane z0 - 1 + s in slot s),
-        // and with them the stage's weight fragments: K chunk q, output tile n (zero
-        // past the 27th tap)
-#pragma unroll
-        for (int s = 0; s < ZC + 2; ++s) dma_plane(z0 - 1 + s, c0, s);
-        bf16x8 B[kKC][NT];
-#pragma unroll
-        for (int q = 0; q < kKC; ++q) {
-            const int tap = 2 * q + (kb >> 1);
-#pragma unroll
-            for (int n = 0; n < NT; ++n) {
-                // past the 27th tap the offset lies past w: zeros
-                const uint32_t vo = tap < 27 ? woff[n] : kNoOff;
-                B[q][n] = __builtin_bit_cast(
-                    bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, vo, 2u * (uint32_t)(2 * q * a.cin + c0), 0));
-            }
-        }
+        if (c0) __syncthreads();  // the previous stage's reads of the slab are done
+        copy_stage(c0);
         __syncthreads();  // waits for the copies (vmcnt) and publishes them
-#pragma unroll
-        for (int p = 0; p < ZC; ++p) {
-            // A fragments of K chunk q from the slab (zero past the 27th tap)
-            auto read_a = [&](int q, bf16x8(&A)[4]) {
-                const int tap = 2 * q + (kb >> 1);
-                const int dz = tap / 9, dy = (tap / 3) % 3, dx = tap % 3;  // dz 0..2 from the output plane's slot
-                const int base = (p + dz) * kPlane + (wave + dy) * kBX + m + dx;
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    uint4 av = make_uint4(0u, 0u, 0u, 0u);
-                    if (tap < 27) av = *reinterpret_cast<const uint4 *>(&slab[(base + 16 * t) * kVS + chan]);
-                    A[t] = __builtin_bit_cast(bf16x8, av);
-                }
-            };
-            // one K chunk ahead, into the other of two fragment sets (chunk parity, no
-            // copies): the next chunk's LDS reads run under this chunk's products
-            bf16x8 Af[2][4];
-            read_a(0, Af[0]);
-#pragma unroll
-            for (int q = 0; q < kKC; ++q) {
-                if (q + 1 < kKC) read_a(q + 1, Af[(q + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);  // the reads go out ahead of the products
-#pragma unroll
-                for (int t = 0; t < 4; ++t)
-#pragma unroll
-                    for (int n = 0; n < NT; ++n)
-                        acc[p][t][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[q][n], Af[q & 1][t], acc[p][t][n], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);  // keep later chunks' reads out of this one
-            }
-        }
+        read_a(F, slab, at);
+        read_c(F, slab, at);
+        slab_products<0, ZC, PLANE>(F, slab, at, second, B, acc, [&](int from, int to) __attribute__((always_inline)) {
+            if (c0 + kCC < a.cin) load_weights(c0 + kCC, from, to);
+        });
     }
-    // Epilogue: with the weights as the A operand each lane holds four consecutive
-    // output channels of one voxel, stored as one 8-byte run (16 bytes for FP32)
-    const int yy = y0 + wave;
-    if (yy >= a.ny) return;
+    const int xx = x0 + m, c = co0 + 4 * kb;
+    if (xx >= a.nx) return;
+    float bias[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bias[i] = a.b ? a.b[c + i] : 0.f;
 #pragma unroll
     for (int p = 0; p < ZC; ++p) {
         const int zz = z0 + p;
         if (zz >= a.nz) break;
 #pragma unroll
-        for (int n = 0; n < NT; ++n) {
-            const int c = co0 + 16 * n + 4 * kb;
-            float bias[4];
+        for (int t = 0; t < 4; ++t) {
+            const int yy = y0 + 4 * wy + t;
+            if (yy >= a.ny) break;
+            const int64_t vm = ((int64_t)zz * a.ny + yy) * a.nx + xx;
+            float v[4];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) bias[i] = a.b ? a.b[c + i] : 0.f;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int xx = x0 + 16 * t + m;
-                if (xx >= a.nx) continue;
-                const int64_t vm = ((int64_t)zz * a.ny + yy) * a.nx + xx;
-                float v[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    v[i] = acc[p][t][n][i] + bias[i];
-                    if (a.relu) v[i] = fmaxf(v[i], 0.f);
-                }
-                uint2 o = make_uint2((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
-                                     (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
-                if (a.m) o = mask4(o, *reinterpret_cast<const uint2 *>(a.m + vm * a.ldm + a.offm + c));
-                *reinterpret_cast<uint2 *>(a.y + vm * a.ldy + a.offy + c) = o;
-                if (a.y32) *reinterpret_cast<float4 *>(a.y32 + vm * a.cout + c) = make_float4(v[0], v[1], v[2], v[3]);
+            for (int i = 0; i < 4; ++i) {
+                v[i] = acc[p][t][i] + bias[i];
+                if (a.relu) v[i] = fmaxf(v[i], 0.f);
             }
+            uint2 o = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+            if (a.m) o = mask4(o, *reinterpret_cast<const uint2 *>(a.m + vm * a.ldm + a.offm + c));
+            *reinterpret_cast<uint2 *>(a.y + vm * a.ldy + a.offy + c) = o;
+            if (a.y32) *reinterpret_cast<float4 *>(a.y32 + vm * a.cout + c) = make_float4(v[0], v[1], v[2], v[3]);
         }
     }
 }
 
-// Single-stage form for 16 input channels: a workgroup marches through a run of zr
-// output planes of its 4 x 64 tile.  Input plane z0 - 1 + i lives in ring slot i & 3
-// (four distinct LDS arrays, chosen at compile time by a loop unrolled four times);
-// while output plane p is computed from slots p, p + 1, p + 2, input plane z0 + p + 2
-// is copied straight into slot p + 3, so each plane is copied once per run and the
-// copy runs under the products (the compiler keeps a read of one slot from waiting
-// on the copy into another only while every read names its slot at compile time).
-// A plane's BF16 results are stored at the next step, after that step's copy is
-// issued, so a barrier (which waits for the copies) never waits for fresh stores.
-// One plane of accumulators, 240 VGPRs: two workgroups per CU.  HEAD: the head is
-// applied in the epilogue and only its FP32 output is stored.
-template <bool HEAD, bool MASK>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_zm(ConvArgs a, int zr) {
-    __shared__ __attribute__((aligned(16))) uint16_t s0[kPlane * kVS], s1[kPlane * kVS], s2[kPlane * kVS],
-        s3[kPlane * kVS];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const ConvTile T = conv_tile(a.nx);
-    const int x0 = T.x0, y0 = T.y0;
-    const int z0 = T.zc * zr, co0 = T.slice * 16;
-    const int n = min(zr, a.nz - z0);  // output planes of this run, at least one
-    const int m = lane & 15, kb = lane >> 4, chan = 8 * (kb & 1);
-    const int yy = y0 + wave, c = co0 + 4 * kb;
-    // weights (once: a single stage) and biases
+// The same with the LDS planes as a ring over (stage, plane): as soon as every wave is done
+// with a plane, the next stage's plane of that place is copied into it, ZC + 1 steps before
+// it is read.  For 16 output channels on large grids, where a copy serves one slice only and
+// comes from beyond the L2: 48 -> 16 at 192^3 445 -> 371 us (558 before either).  Elsewhere a
+// barrier per plane costs what the overlap gives (96 -> 32 at 96^3 144 and 143 us, 64 -> 64 at
+// 48^3 26 and 28, 128 -> 128 at 12^3 12.4 and 14).
+template <int S, int ZC>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_ring(ConvArgs a) {
+    constexpr int TY = 16 / S, PLANE = kSBX * (TY + 2), C = (2 * PLANE + 255) / 256, SLOT = 256 * C * 8;
+    __shared__ __attribute__((aligned(16))) uint16_t slab[(ZC + 2) * SLOT];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wy = wave % (4 / S), ws = wave / (4 / S);  // rows 4 wy .. 4 wy + 3, channel slice ws of the workgroup's
+    const ConvTile T = conv_tile<TY>(a.nx);
+    const int x0 = T.x0, y0 = T.y0, z0 = T.zc * ZC, co0 = 16 * (T.slice * S + ws);
+    const int m = lane & 15, kb = lane >> 4;
+    const bool second = kb >> 1;
+    f32x4 acc[ZC][4];
+#pragma unroll
+    for (int p = 0; p < ZC; ++p)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) acc[p][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
     const __amdgpu_buffer_rsrc_t rw =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.w), (short)0, (int)a.wbytes, kRawBuffer);
-    const uint32_t woff = 2u * (uint32_t)((co0 + m) * a.kpad + (kb >> 1) * a.cin + chan);
+    // this lane's weights, and the bytes from one chunk, one stage to the next
+    const uint32_t wlane = a.packed ? 2u * (uint32_t)((co0 / 16) * (a.cin / kCC) * kKC * 512 + 8 * lane)
+                                    : 2u * (uint32_t)((co0 + m) * a.kpad + (kb >> 1) * a.cin + 8 * (kb & 1));
+    const uint32_t wchunk = a.packed ? 1024u : 4u * (uint32_t)a.cin, wstage = a.packed ? kKC * 1024u / kCC : 2u;
+    bf16x8 B[kKC];
+    auto load_weights = [&](int c0, int from, int to) __attribute__((always_inline)) {
+#pragma unroll
+        for (int q = from; q < to; ++q) {
+            const int tap = 2 * q + (kb >> 1);  // past the 27th tap the offset lies past w: zeros
+            const uint32_t off = tap < 27 ? wlane : kNoOff;
+            B[q] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, off, wchunk * q + wstage * c0, 0));
+        }
+    };
+    const __amdgpu_buffer_rsrc_t rx =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.x), (short)0, (int)a.xbytes, kRawBuffer);
+    const __amdgpu_buffer_rsrc_t rx2 =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.x2), (short)0, (int)a.x2bytes, kRawBuffer);
+    uint32_t poff[C];
+    auto source_offsets = [&](bool from2) __attribute__((always_inline)) {
+        const int sh = from2 && a.up2 ? 1 : 0, ld = from2 ? a.ldx2 : a.ldx, off = from2 ? a.offx2 : a.offx;
+#pragma unroll
+        for (int it = 0; it < C; ++it) {
+            const int e = tid + 256 * it, bv = e >> 1, h = e & 1;
+            const int xx = x0 + bv % kSBX - 1, yy = y0 + bv / kSBX - 1;
+            const bool in = bv < PLANE && xx >= 0 && xx < a.nx && yy >= 0 && yy < a.ny;
+            poff[it] = in ? 2u * (uint32_t)(((yy >> sh) * (a.nx >> sh) + (xx >> sh)) * ld + off + 8 * h) : kNoOff;
+        }
+    };
+    // plane `slot` of the stage of channels c0 ..: C copies by every wave, so that the waits
+    // can count them (the entries past the plane land in the slot's tail)
+    auto copy_plane = [&](int c0, int slot) __attribute__((always_inline)) {
+        const bool from2 = c0 >= a.cin1;
+        const int zz = z0 - 1 + slot;
+        const bool zin = zz >= 0 && zz < a.nz;  // else the whole plane reads as zeros
+        const uint32_t zoff = !zin    ? 0u
+                              : from2 ? (uint32_t)(a.up2 ? zz >> 1 : zz) * a.plane2_bytes + 2u * (uint32_t)(c0 - a.cin1)
+                                      : (uint32_t)zz * a.plane_bytes + 2u * (uint32_t)c0;
+#pragma unroll
+        for (int it = 0; it < C; ++it) {
+            const uint32_t off = zin ? poff[it] : kNoOff;
+            uint16_t *to = slab + slot * SLOT + 8 * (256 * it + 64 * wave);
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(from2 ? rx2 : rx, (lds_void *)to, 16, off, zoff, 0, 0);
+        }
+    };
+    const FragAt at(4 * wy, m, kb);
+    Frags F{};
+    source_offsets(false);
+    load_weights(0, 0, kKC);
+#pragma unroll
+    for (int s = 0; s <= ZC; ++s) copy_plane(0, s);
+    auto step = [&](auto I, int c0, bool last) __attribute__((always_inline)) {
+        constexpr int s = decltype(I)::value;
+        constexpr bool D0 = s < ZC, D1 = s >= 1 && s <= ZC, D2 = s >= 2;
+        // This wave's copies of the plane have landed when no more than the younger loads are
+        // out: ZC planes' copies and the weights fetched since (in the first stage the weights
+        // came first), or what is left of this stage's copies in the last
+        constexpr int kYounger = ZC * C, kTail = ZC > s ? (ZC - s) * C : 0;
+        constexpr int kWeights = (s + 1 <= ZC - 1 ? 4 : 0) + (s + 1 <= ZC ? 5 : 0) + (s + 1 <= ZC + 1 ? 5 : 0);
+        if (last)
+            __builtin_amdgcn_s_waitcnt(wait_vmcnt(kTail));
+        else if (c0 == 0)
+            __builtin_amdgcn_s_waitcnt(wait_vmcnt(kYounger));
+        else
+            __builtin_amdgcn_s_waitcnt(wait_vmcnt(kYounger + kWeights));
+        __builtin_amdgcn_s_barrier();  // everyone's have, and everyone is done with the plane before
+        asm volatile("" ::: "memory");
+        if (s == 0) {
+            copy_plane(c0, ZC + 1);
+        } else if (!last) {
+            if (s == 1 && c0 + kCC == a.cin1) source_offsets(true);
+            copy_plane(c0 + kCC, s - 1);
+        }
+        const uint16_t *plane = slab + s * SLOT;
+        read_a(F, plane, at);
+        read_c(F, plane, at);
+        plane_products<D0, D1, D2>(F, plane, at, second, B, acc[D0 ? s : 0], acc[D1 ? s - 1 : 0], acc[D2 ? s - 2 : 0],
+                                   []() {}, []() {});
+        if (!last) {
+            if (s == ZC - 1) load_weights(c0 + kCC, 0, 4);
+            if (s == ZC) load_weights(c0 + kCC, 4, 9);
+            if (s == ZC + 1) load_weights(c0 + kCC, 9, kKC);
+        }
+    };
+    for (int c0 = 0; c0 < a.cin; c0 += kCC) {
+        const bool last = c0 + kCC >= a.cin;
+        step(std::integral_constant<int, 0>{}, c0, last);
+        step(std::integral_constant<int, 1>{}, c0, last);
+        step(std::integral_constant<int, 2>{}, c0, last);
+        if constexpr (ZC >= 2) step(std::integral_constant<int, 3>{}, c0, last);
+        if constexpr (ZC >= 3) step(std::integral_constant<int, 4>{}, c0, last);
+        if constexpr (ZC >= 4) step(std::integral_constant<int, 5>{}, c0, last);
+    }
+    const int xx = x0 + m, c = co0 + 4 * kb;
+    if (xx >= a.nx) return;
+    float bias[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) bias[i] = a.b ? a.b[c + i] : 0.f;
+#pragma unroll
+    for (int p = 0; p < ZC; ++p) {
+        const int zz = z0 + p;
+        if (zz >= a.nz) break;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int yy = y0 + 4 * wy + t;
+            if (yy >= a.ny) break;
+            const int64_t vm = ((int64_t)zz * a.ny + yy) * a.nx + xx;
+            float v[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                v[i] = acc[p][t][i] + bias[i];
+                if (a.relu) v[i] = fmaxf(v[i], 0.f);
+            }
+            uint2 o = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+            if (a.m) o = mask4(o, *reinterpret_cast<const uint2 *>(a.m + vm * a.ldm + a.offm + c));
+            *reinterpret_cast<uint2 *>(a.y + vm * a.ldy + a.offy + c) = o;
+            if (a.y32) *reinterpret_cast<float4 *>(a.y32 + vm * a.cout + c) = make_float4(v[0], v[1], v[2], v[3]);
+        }
+    }
+}
+
+// Single-stage form for 16 input channels: a workgroup marches through a run of zr output
+// planes of its tile, one input plane per step, three output planes in flight in registers.
+// Input plane z0 - 1 + i lives in ring slot i % 4 (four distinct LDS arrays, chosen at
+// compile time by a loop unrolled four times, or the compiler waits for every copy before
+// every read); each plane is copied once per run, three steps before it is read.  A finished
+// plane is stored in the next step.  Bound by the copies' and stores' way to memory at 192^3
+// (64 bytes per voxel: 4.2 TB/s).  236 VGPRs: two workgroups per CU.  HEAD: the head is
+// applied in the epilogue and only its FP32 output is stored.  MASK: a.m is not null.
+// Before (4 x 64 tiles, fragments read per product) and now: 16 -> 16 at 192^3 176 -> 108 us,
+// at 96^3 37 -> 20; 16 -> 32 at 96^3 56 -> 31.
+template <int S, bool HEAD, bool MASK>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_march(ConvArgs a, int zr) {
+    constexpr int TY = 16 / S, PLANE = kSBX * (TY + 2), NE = 2 * PLANE, PS = (NE + 255) / 256;
+    __shared__ __attribute__((aligned(16))) uint16_t s0[PLANE * kVS], s1[PLANE * kVS], s2[PLANE * kVS], s3[PLANE * kVS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wy = wave % (4 / S), ws = wave / (4 / S);
+    const ConvTile T = conv_tile<TY>(a.nx);
+    const int x0 = T.x0, y0 = T.y0, z0 = T.zc * zr, co0 = 16 * (T.slice * S + ws);
+    const int n = min(zr, a.nz - z0);
+    const int m = lane & 15, kb = lane >> 4, c = co0 + 4 * kb, xx = x0 + m, yw = y0 + 4 * wy;
+    const bool second = kb >> 1;
+    const __amdgpu_buffer_rsrc_t rw =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.w), (short)0, (int)a.wbytes, kRawBuffer);
+    const uint32_t wlane = a.packed ? 2u * (uint32_t)((co0 / 16) * kKC * 512 + 8 * lane)
+                                    : 2u * (uint32_t)((co0 + m) * a.kpad + (kb >> 1) * a.cin + 8 * (kb & 1));
+    const uint32_t wchunk = a.packed ? 1024u : 4u * (uint32_t)a.cin;
     bf16x8 B[kKC];
 #pragma unroll
     for (int q = 0; q < kKC; ++q) {
-        const int tap = 2 * q + (kb >> 1);
-        B[q] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, tap < 27 ? woff : kNoOff,
-                                                                                  2u * (uint32_t)(2 * q * a.cin), 0));
+        const uint32_t off = 2 * q + (kb >> 1) < 27 ? wlane : kNoOff;
+        B[q] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rw, off, wchunk * q, 0));
     }
     float bias[4], hw[4], hb = 0.f;
 #pragma unroll
@@ -328,172 +543,135 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     if (HEAD) hb = a.hb[0];
     const __amdgpu_buffer_rsrc_t rx =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.x), (short)0, (int)a.xbytes, kRawBuffer);
-    uint32_t poff[kPS];
+    uint32_t poff[PS];
 #pragma unroll
-    for (int it = 0; it < kPS; ++it) {
+    for (int it = 0; it < PS; ++it) {
         const int e = tid + 256 * it, bv = e >> 1, h = e & 1;
-        const int xx = x0 + bv % kBX - 1, yq = y0 + bv / kBX - 1;
-        const bool in = xx >= 0 && xx < a.nx && yq >= 0 && yq < a.ny;
-        poff[it] = in ? 2u * (uint32_t)((yq * a.nx + xx) * a.ldx + a.offx + 8 * h) : kNoOff;
+        const int xq = x0 + bv % kSBX - 1, yq = y0 + bv / kSBX - 1;
+        const bool in = xq >= 0 && xq < a.nx && yq >= 0 && yq < a.ny;
+        poff[it] = in ? 2u * (uint32_t)((yq * a.nx + xq) * a.ldx + a.offx + 8 * h) : kNoOff;
     }
     auto copy_plane = [&](int zz, uint16_t *slot) __attribute__((always_inline)) {
         const bool zin = zz >= 0 && zz < a.nz;  // else the plane reads as zeros
         const uint32_t zoff = zin ? (uint32_t)zz * a.plane_bytes : 0u;
 #pragma unroll
-        for (int it = 0; it < kPS; ++it) {
+        for (int it = 0; it < PS; ++it) {
             const int e0 = 256 * it + 64 * wave, e = e0 + lane;
-            if (e0 >= 2 * kPlane) break;  // wave-uniform
-            if (e < 2 * kPlane)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)(slot + 8 * e0), 16, zin ? poff[it] : kNoOff,
-                                                         zoff, 0, 0);
+            if (e0 >= NE) break;  // wave-uniform
+            const uint32_t off = zin ? poff[it] : kNoOff;
+            uint16_t *to = slot + 8 * e0;
+            if (e < NE) __builtin_amdgcn_raw_ptr_buffer_load_lds(rx, (lds_void *)to, 16, off, zoff, 0, 0);
         }
     };
-    // BF16 results of the previous plane, stored after the next copy is issued (the
-    // FP32 results, written in training only, leave at once)
-    uint2 pend0 = make_uint2(0u, 0u), pend1 = pend0, pend2 = pend0, pend3 = pend0;
-    float hpend0 = 0.f, hpend1 = 0.f, hpend2 = 0.f, hpend3 = 0.f;  // HEAD: the head's outputs
+    uint2 pend[4];
+    float hpend[4];
     int pend_z = -1;
     auto flush = [&]() __attribute__((always_inline)) {
-        const bool row = pend_z >= 0 && yy < a.ny;
+        if (pend_z < 0 || xx >= a.nx) return;
+        const int64_t vm = ((int64_t)pend_z * a.ny + yw) * a.nx + xx;
 #pragma unroll
-        for (int t4 = 0; t4 < 4; ++t4) {
-            const int xx = x0 + 16 * t4 + m;
-            if (row && xx < a.nx) {
-                const int64_t vm = ((int64_t)pend_z * a.ny + yy) * a.nx + xx;
-                if (HEAD) {
-                    if (kb == 3) a.hout[vm] = t4 == 0 ? hpend0 : t4 == 1 ? hpend1 : t4 == 2 ? hpend2 : hpend3;
-                } else {
-                    *reinterpret_cast<uint2 *>(a.y + vm * a.ldy + a.offy + c) =
-                        t4 == 0 ? pend0 : t4 == 1 ? pend1 : t4 == 2 ? pend2 : pend3;
-                }
+        for (int t = 0; t < 4; ++t) {
+            if (yw + t >= a.ny) break;
+            const int64_t v = vm + (int64_t)t * a.nx;
+            if (HEAD) {
+                if (kb == 3) a.hout[v] = hpend[t];
+            } else {
+                *reinterpret_cast<uint2 *>(a.y + v * a.ldy + a.offy + c) = pend[t];
             }
         }
     };
-    // Output plane z0 + p reads the slots of input planes z0 + p - 1 .. z0 + p + 1
-    // (ring slots p, p + 1, p + 2, mod 4) while input plane z0 + p + 2 is copied into
-    // slot p + 3; the loop runs four planes per trip so that every slot is a fixed
-    // array in each of them.  ring(i): slot i, a constant once the loop is unrolled.
-    auto ring = [&](int i) -> uint16_t * {
+    auto ring = [&](int i) __attribute__((always_inline)) -> uint16_t * {
         i &= 3;
         return i == 0 ? s0 : i == 1 ? s1 : i == 2 ? s2 : s3;
     };
+    const FragAt at(4 * wy, m, kb);
+    Frags F{};
+    f32x4 above[4], level[4], below[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) above[t] = level[t] = below[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    const bool full = yw + 4 <= a.ny;
+    constexpr int kMinCopies = NE / 256;  // of every wave for a plane
     copy_plane(z0 - 1, s0);
     copy_plane(z0, s1);
     copy_plane(z0 + 1, s2);
-    for (int p0 = 0; p0 < n; p0 += 4) {
+    // weights and the first planes: waited for here, or the compiler waits for the weights
+    // (and with them for every copy issued since) in each trip of the loop
+    __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+    for (int i0 = 0; i0 < n + 2; i0 += 4) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const int p = p0 + k;
-            if (p >= n) break;
-            // This plane's inputs have landed (each wave waits for its own copies, the
-            // barrier for all of them) and every wave is done with slot k + 3's plane.
-            // The wait is explicit: the compiler does not carry the copy issued in the
-            // last step of a trip around the loop's back edge.
-            __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
-            __syncthreads();
-            // HEAD: this plane's base values, loaded before this step's stores and copy
-            // so that waiting for them waits for nothing younger
+            const int i = i0 + k;
+            if (i >= n + 2) break;
+            // this wave's copies of this plane have landed: in the steady state two planes'
+            // copies (at least 2 or 1 per wave each) and two planes' stores are younger
+            if (i < n && i >= 5 && full)
+                __builtin_amdgcn_s_waitcnt(kWaitVmcnt0 | (8 + 2 * kMinCopies));
+            else if (i < n)
+                __builtin_amdgcn_s_waitcnt(kWaitVmcnt0 | 2 * kMinCopies);
+            else
+                __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            const int pz = z0 + i - 2;  // the output plane this step completes
             float hbase[4] = {0.f, 0.f, 0.f, 0.f};
-            if (HEAD && a.hbase && kb == 0 && yy < a.ny) {
+            uint2 mask[4];
+            if (i >= 2 && xx < a.nx) {
 #pragma unroll
-                for (int t4 = 0; t4 < 4; ++t4) {
-                    const int xx = x0 + 16 * t4 + m;
-                    if (xx < a.nx) hbase[t4] = a.hbase[((int64_t)(z0 + p) * a.ny + yy) * a.nx + xx];
-                }
-            }
-            uint2 mask[4];  // MASK: this plane's ReLU mask, loaded early for the same reason
-            if (MASK && yy < a.ny) {
-#pragma unroll
-                for (int t4 = 0; t4 < 4; ++t4) {
-                    const int xx = x0 + 16 * t4 + m;
-                    const int64_t vm = ((int64_t)(z0 + p) * a.ny + yy) * a.nx + xx;
-                    mask[t4] = xx < a.nx ? *reinterpret_cast<const uint2 *>(a.m + vm * a.ldm + a.offm + c) : make_uint2(0u, 0u);
+                for (int t = 0; t < 4; ++t) {
+                    const int64_t vm = ((int64_t)pz * a.ny + yw + t) * a.nx + xx;
+                    const bool in = yw + t < a.ny;
+                    if (HEAD && a.hbase && kb == 0 && in) hbase[t] = a.hbase[vm];
+                    if (MASK) mask[t] = in ? *reinterpret_cast<const uint2 *>(a.m + vm * a.ldm + a.offm + c) : make_uint2(0u, 0u);
                 }
             }
             flush();
-            if (p + 2 <= n) copy_plane(z0 + p + 2, ring(k + 3));
-            // The slot a lane reads is fixed per chunk except where the chunk's two taps
-            // lie in different planes (taps 8 and 9): there both slots are read and each
-            // lane keeps its own, so that every LDS read names one slot at compile time
-            // (a read the compiler cannot place waits for the copy in flight).
-            auto read_a = [&](int q, bf16x8(&A)[4]) {
-                const int tap = 2 * q + (kb >> 1);
-                const int dy = (tap / 3) % 3, dx = tap % 3;
-                const int dz0 = (2 * q) / 9, dz1 = (2 * q + 1) / 9;
-                const int base = (wave + dy) * kBX + m + dx;
+            if (i + 3 < n + 2) copy_plane(z0 - 1 + i + 3, ring(k + 3));
+            uint16_t *slot = ring(k);
+            read_a(F, slot, at);
+            read_c(F, slot, at);
+            plane_products<true, true, true>(F, slot, at, second, B, above, level, below, []() {}, []() {});
+            if (i >= 2) {
 #pragma unroll
-                for (int t4 = 0; t4 < 4; ++t4) {
-                    const int o = (base + 16 * t4) * kVS + chan;
-                    uint4 av = *reinterpret_cast<const uint4 *>(&ring(k + dz0)[o]);
-                    if (dz1 != dz0 && 2 * q + 1 < 27) {
-                        // combined by masks: a select of the two loads would fold into
-                        // one load from a selected slot
-                        const uint4 a1 = *reinterpret_cast<const uint4 *>(&ring(k + dz1)[o]);
-                        const uint32_t k1 = 0u - (uint32_t)(kb >> 1), k0 = ~k1;
-                        av = make_uint4((av.x & k0) | (a1.x & k1), (av.y & k0) | (a1.y & k1), (av.z & k0) | (a1.z & k1),
-                                        (av.w & k0) | (a1.w & k1));
+                for (int t = 0; t < 4; ++t) {
+                    float v[4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        v[j] = below[t][j] + bias[j];
+                        if (a.relu) v[j] = fmaxf(v[j], 0.f);
                     }
-                    if (tap >= 27) av = make_uint4(0u, 0u, 0u, 0u);
-                    A[t4] = __builtin_bit_cast(bf16x8, av);
+                    uint2 o = make_uint2(f2bf2(v[0], v[1]), f2bf2(v[2], v[3]));
+                    if (MASK) o = mask4(o, mask[t]);
+                    if (HEAD) {
+                        float hs = hb + hbase[t];
+#pragma unroll
+                        for (int g = 0; g < 4; ++g) {
+                            if (g > 0) {
+                                const float up = __shfl_up(hs, 16, 64);
+                                if (kb == g) hs = up;
+                            }
+                            if (kb == g) {
+                                hs = fmaf(hw[0], bf2f((uint16_t)(o.x & 0xffffu)), hs);
+                                hs = fmaf(hw[1], bf2f((uint16_t)(o.x >> 16)), hs);
+                                hs = fmaf(hw[2], bf2f((uint16_t)(o.y & 0xffffu)), hs);
+                                hs = fmaf(hw[3], bf2f((uint16_t)(o.y >> 16)), hs);
+                            }
+                        }
+                        hpend[t] = hs;
+                    } else {
+                        pend[t] = o;
+                    }
+                    if (a.y32 && yw + t < a.ny && xx < a.nx)
+                        *reinterpret_cast<float4 *>(a.y32 + (((int64_t)pz * a.ny + yw + t) * a.nx + xx) * a.cout + c) =
+                            make_float4(v[0], v[1], v[2], v[3]);
                 }
-            };
-            f32x4 acc[4];
-#pragma unroll
-            for (int t4 = 0; t4 < 4; ++t4) acc[t4] = (f32x4){0.f, 0.f, 0.f, 0.f};
-            bf16x8 Af[2][4];
-            read_a(0, Af[0]);
-#pragma unroll
-            for (int q = 0; q < kKC; ++q) {
-                if (q + 1 < kKC) read_a(q + 1, Af[(q + 1) & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int t4 = 0; t4 < 4; ++t4)
-                    acc[t4] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[q], Af[q & 1][t4], acc[t4], 0, 0, 0);
-                __builtin_amdgcn_sched_barrier(0);
+                pend_z = pz;
             }
 #pragma unroll
-            for (int t4 = 0; t4 < 4; ++t4) {
-                float v[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    v[i] = acc[t4][i] + bias[i];
-                    if (a.relu) v[i] = fmaxf(v[i], 0.f);
-                }
-                uint2 o = make_uint2((uint32_t)f2bf(v[0]) | ((uint32_t)f2bf(v[1]) << 16),
-                                     (uint32_t)f2bf(v[2]) | ((uint32_t)f2bf(v[3]) << 16));
-                if (MASK) o = mask4(o, mask[t4]);
-                if (HEAD) {
-                    // the head's sum in channel order, as unet_head_fwd forms it from the
-                    // stored BF16 values: lanes of group kb add channels 4 kb .. 4 kb + 3
-                    // and pass the sum to group kb + 1 (16 lanes up)
-                    float hs = hb + hbase[t4];
-#pragma unroll
-                    for (int g = 0; g < 4; ++g) {
-                        if (g > 0) {
-                            const float up = __shfl_up(hs, 16, 64);
-                            if (kb == g) hs = up;
-                        }
-                        if (kb == g) {
-                            hs = fmaf(hw[0], bf2f((uint16_t)(o.x & 0xffffu)), hs);
-                            hs = fmaf(hw[1], bf2f((uint16_t)(o.x >> 16)), hs);
-                            hs = fmaf(hw[2], bf2f((uint16_t)(o.y & 0xffffu)), hs);
-                            hs = fmaf(hw[3], bf2f((uint16_t)(o.y >> 16)), hs);
-                        }
-                    }
-                    if (t4 == 0) hpend0 = hs;
-                    else if (t4 == 1) hpend1 = hs;
-                    else if (t4 == 2) hpend2 = hs;
-                    else hpend3 = hs;
-                } else if (t4 == 0) pend0 = o;
-                else if (t4 == 1) pend1 = o;
-                else if (t4 == 2) pend2 = o;
-                else pend3 = o;
-                const int xx = x0 + 16 * t4 + m;
-                if (a.y32 && yy < a.ny && xx < a.nx)
-                    *reinterpret_cast<float4 *>(a.y32 + (((int64_t)p + z0) * a.ny + yy) * a.nx * a.cout +
-                                                (int64_t)xx * a.cout + c) = make_float4(v[0], v[1], v[2], v[3]);
+            for (int t = 0; t < 4; ++t) {
+                below[t] = level[t];
+                level[t] = above[t];
+                above[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
             }
-            pend_z = z0 + p;
         }
     }
     flush();
@@ -512,15 +690,32 @@ __global__ void k_wtrans(const uint16_t *w, uint16_t *wt, int cin, int cout, int
     wt[i] = v;
 }
 
-// The same for the layers of a table, one after another (blockIdx.y the layer).
-__global__ void k_wtrans_all(const uint16_t *w, uint16_t *wt, unet::TransTable t) {
-    const int l = blockIdx.y, cin = t.cin[l], cout = t.cout[l], kpad_in = kpad_of(cin), kpad_out = kpad_of(cout);
-    const uint16_t *src = w + t.w_off[l];
-    uint16_t *dst = wt + t.wt_off[l];
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < (int64_t)cin * kpad_out;
+// Weights in fragment order, for the layers of a table (blockIdx.y the layer): the 14 chunks
+// of each 16-channel stage of each 16-channel slice of the outputs, every chunk the 16
+// bytes of each lane in turn.  A wave's fragment is then one run of 1 KB; from rows of
+// kpad it takes 32 pieces of 32 bytes out of as many cache lines.
+__global__ void k_pack(const uint16_t *w, uint16_t *packed, unet::PackTable t) {
+    const unet::PackLayer L = t.l[blockIdx.y];
+    const int stages = L.cin / 16;
+    const uint16_t *src = w + L.from;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < packed_len(L.cin, L.cout) / 8;
          i += (int64_t)gridDim.x * blockDim.x) {
-        const int ci = (int)(i / kpad_out), kk = (int)(i % kpad_out), tp = kk / cout, co = kk % cout;
-        dst[i] = kk < 27 * cout ? src[(int64_t)co * kpad_in + (26 - tp) * cin + ci] : (uint16_t)0;
+        const int lane = (int)(i % 64), q = (int)(i / 64 % kKC), st = (int)(i / (64 * kKC) % stages);
+        const int n = 16 * (int)(i / (64 * kKC * stages)) + lane % 16;         // output channel
+        const int tap = 2 * q + lane / 32, k = 16 * st + 8 * (lane / 16 % 2);  // tap and first input channel
+        uint4 v = make_uint4(0u, 0u, 0u, 0u);
+        if (tap < 27) {
+            if (!L.transposed) {
+                v = *reinterpret_cast<const uint4 *>(src + (int64_t)n * kpad_of(L.cin) + tap * L.cin + k);
+            } else {  // the roles of the channels and the taps reversed; w has L.cin outputs
+                const uint16_t *p = src + (int64_t)k * kpad_of(L.cout) + (26 - tap) * L.cout + n;
+                uint32_t e[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) e[j] = p[(int64_t)j * kpad_of(L.cout)];
+                v = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
+            }
+        }
+        *reinterpret_cast<uint4 *>(packed + L.to + 8 * i) = v;
     }
 }
 
@@ -939,7 +1134,7 @@ __global__ void k_up_fwd8(const uint16_t *x, int ldx, int offx, uint16_t *y, int
 __device__ __forceinline__ uint4 f_to_bf8(const float (&f)[8]) {
     uint32_t w[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) w[k] = (uint32_t)f2bf(f[2 * k]) | (uint32_t)f2bf(f[2 * k + 1]) << 16;
+    for (int k = 0; k < 4; ++k) w[k] = f2bf2(f[2 * k], f[2 * k + 1]);
     return make_uint4(w[0], w[1], w[2], w[3]);
 }
 __device__ __forceinline__ uint4 mask8(uint4 v, uint4 m) {
@@ -1241,6 +1436,46 @@ static int head_bwd(const uint16_t *x, int32_t ldx, const float *w, const float 
     return status(hipGetLastError());
 }
 
+// Planes per run of the marching form: each run costs its planes, two more to fill and about
+// three of start, in rounds of kConvSlots workgroups.
+static int march_planes(int64_t tiles, int nz) {
+    int best = nz;
+    int64_t cost = INT64_MAX;
+    for (int runs = 1; runs <= std::max(1, nz / 4); ++runs) {
+        const int zr = (nz + runs - 1) / runs;
+        const int64_t c = (tiles * ((nz + zr - 1) / zr) + kConvSlots - 1) / kConvSlots * (zr + 5);
+        if (c < cost) cost = c, best = zr;
+    }
+    return best;
+}
+
+// Planes of a slab: the busiest CU's workgroups times their planes, weighed by what a plane
+// costs in a slab of that many (halo planes and weights are shared by its planes: measured
+// over 12^3 .. 192^3; rows of kpad make the weights dearer), and by 1.25 where a CU has one
+// workgroup, whose copies nothing covers.  At 64 -> 64 channels, packed: 12^3 best at 1
+// (7.9 us; 11.7 at 2), 24^3 at 1 (10 us; 16 at 4), 48^3 at 4 (26 us; 32 at 1).
+static int slab_planes(int64_t tiles, int nz, int s, bool packed) {
+    static const double kCost[3][4] = {{1.17, 1.12, 1.0, 1.0}, {1.2, 1.0, 1.02, 1.1}, {2.2, 1.5, 1.15, 1.0}};
+    const double *w = kCost[!packed ? 2 : s == 1 ? 1 : 0];
+    int best = 1;
+    double cost = 0.;
+    for (int zc = 1; zc <= 4; ++zc) {
+        const int64_t n = (tiles * ((nz + zc - 1) / zc) + kConvSlots / 2 - 1) / (kConvSlots / 2);
+        const double c = (double)n * zc * w[zc - 1] * (n == 1 ? 1.25 : 1.);
+        if (zc == 1 || c < cost) cost = c, best = zc;
+    }
+    return best;
+}
+
+template <int S>
+static void launch_slab(int zc, dim3 g, hipStream_t st, const ConvArgs &a) {
+    const dim3 blk(256);
+    if (zc == 1) hipLaunchKernelGGL((k_conv_slab<S, 1>), g, blk, 0, st, a);
+    else if (zc == 2) hipLaunchKernelGGL((k_conv_slab<S, 2>), g, blk, 0, st, a);
+    else if (zc == 3) hipLaunchKernelGGL((k_conv_slab<S, 3>), g, blk, 0, st, a);
+    else hipLaunchKernelGGL((k_conv_slab<S, 4>), g, blk, 0, st, a);
+}
+
 extern "C" {
 
 int32_t unet_kpad(int32_t cin) { return kpad_of(cin); }
@@ -1258,10 +1493,9 @@ static int launch_conv(ConvArgs a, int64_t nx2, int64_t ny2, int64_t nz2, void *
          reinterpret_cast<uintptr_t>(a.y) | reinterpret_cast<uintptr_t>(a.y32)) & 15)
         return -1;  // 16-byte vector loads and stores
     const int tiles = cout / 16;
-    const int nt = 1;  // one 16-channel tile per wave: its 14 weight fragments stay in registers
     const int64_t plane_bytes = 2 * (int64_t)ny * nx * a.ldx, xbytes = plane_bytes * nz;
     const int64_t plane2_bytes = 2 * ny2 * nx2 * a.ldx2, x2bytes = plane2_bytes * nz2;
-    const int64_t wbytes = 2 * (int64_t)cout * kpad_of(cin);
+    const int64_t wbytes = a.packed ? 2 * packed_len(cin, cout) : 2 * (int64_t)cout * kpad_of(cin);
     if (xbytes > kMaxX || x2bytes > kMaxX || wbytes > kMaxX) return -1;
     a.kpad = kpad_of(cin);
     a.xbytes = (uint32_t)xbytes;
@@ -1269,32 +1503,39 @@ static int launch_conv(ConvArgs a, int64_t nx2, int64_t ny2, int64_t nz2, void *
     a.x2bytes = (uint32_t)x2bytes;
     a.plane2_bytes = (uint32_t)plane2_bytes;
     a.wbytes = (uint32_t)wbytes;
-    const int64_t nxy = (int64_t)((nx + kTX - 1) / kTX) * ((ny + kTY - 1) / kTY);
-    if (nxy > 0x7fffffff) return -1;
-    if (cin == kCC && a.cin1 == cin) {
-        // one stage: the z-marching form, runs of zr planes (4 .. 32), about three
-        // rounds of two workgroups per CU on a large grid (timed best among 768 ..
-        // 6144 workgroups)
-        const int64_t zr = std::min<int64_t>(32, std::max<int64_t>(4, nxy * (tiles / nt) * nz / kZmWorkgroups));
-        const dim3 g((unsigned)nxy, (unsigned)((nz + zr - 1) / zr), (unsigned)(tiles / nt)), blk(256);
-        (void)hipGetLastError();
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const dim3 blk(256);
+    auto tiles_xy = [&](int s) { return (int64_t)((nx + kSX - 1) / kSX) * ((ny + 16 / s - 1) / (16 / s)); };
+    // slices per workgroup: as many as share the copies evenly
+    int s = tiles % 4 == 0 ? 4 : tiles % 2 == 0 ? 2 : 1;
+    if (tiles_xy(s) > 0x7fffffff) return -1;
+    (void)hipGetLastError();
+    // One stage: march where a chip full of workgroups (two per CU) has at least five planes
+    // each.  Below that the run's first two planes cost more than they save (16 -> 32 at 48^3,
+    // 1.7 planes: 10.0 us against 7.5 in slabs; 16 -> 16 at 96^3, 6.8: 20.4 against 22.9).
+    const int sm = s > 1 && !a.m && !a.hout ? 2 : 1;
+    if (cin == kCC && a.cin1 == cin && (a.hout || tiles_xy(sm) * (tiles / sm) * nz >= 5 * kConvSlots)) {
+        const int zr = march_planes(tiles_xy(sm) * (tiles / sm), nz);
+        const dim3 g((unsigned)tiles_xy(sm), (unsigned)((nz + zr - 1) / zr), (unsigned)(tiles / sm));
         if (a.hout)
-            hipLaunchKernelGGL((k_conv_zm<true, false>), g, blk, 0, static_cast<hipStream_t>(stream), a, (int)zr);
+            hipLaunchKernelGGL((k_conv_march<1, true, false>), g, blk, 0, st, a, zr);
         else if (a.m)
-            hipLaunchKernelGGL((k_conv_zm<false, true>), g, blk, 0, static_cast<hipStream_t>(stream), a, (int)zr);
+            hipLaunchKernelGGL((k_conv_march<1, false, true>), g, blk, 0, st, a, zr);
+        else if (sm == 1)
+            hipLaunchKernelGGL((k_conv_march<1, false, false>), g, blk, 0, st, a, zr);
         else
-            hipLaunchKernelGGL((k_conv_zm<false, false>), g, blk, 0, static_cast<hipStream_t>(stream), a, (int)zr);
+            hipLaunchKernelGGL((k_conv_march<2, false, false>), g, blk, 0, st, a, zr);
         return status(hipGetLastError());
     }
-    const bool large = nxy * ((nz + 3) / 4) * (tiles / nt) >= kZcLargeGrid;
-    const int zc = large ? 4 : 3;
-    const dim3 g((unsigned)nxy, (unsigned)((nz + zc - 1) / zc), (unsigned)(tiles / nt)), blk(256);
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    (void)hipGetLastError();
-    if (large)
-        hipLaunchKernelGGL((k_conv_fwd<1, 4>), g, blk, 0, st, a);
-    else
-        hipLaunchKernelGGL((k_conv_fwd<1, 3>), g, blk, 0, st, a);
+    const int64_t t = tiles_xy(s) * (tiles / s);
+    // 16 output channels and eight rounds of workgroups: see k_conv_ring
+    const bool ring = s == 1 && t * ((nz + 3) / 4) >= 8 * kConvSlots;
+    const int zc = ring ? 4 : slab_planes(t, nz, s, a.packed);
+    const dim3 g((unsigned)tiles_xy(s), (unsigned)((nz + zc - 1) / zc), (unsigned)(tiles / s));
+    if (ring) hipLaunchKernelGGL((k_conv_ring<1, 4>), g, blk, 0, st, a);
+    else if (s == 4) launch_slab<4>(zc, g, st, a);
+    else if (s == 2) launch_slab<2>(zc, g, st, a);
+    else launch_slab<1>(zc, g, st, a);
     return status(hipGetLastError());
 }
 
@@ -1302,7 +1543,7 @@ int unet_conv3d_fwd(const uint16_t *x, int32_t ldx, int32_t offx, const uint16_t
                     int32_t ldy, int32_t offy, float *y32, int32_t nz, int32_t ny, int32_t nx, int32_t cin,
                     int32_t cout, int32_t relu, void *stream) {
     ConvArgs a{x, w, b, y, y32, ldx, offx, ldy, offy, nz, ny, nx, cin, cout, 0, relu, 0, 0, 0,
-               x, ldx, offx, cin, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0};
+               x, ldx, offx, cin, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, 0};
     return launch_conv(a, nx, ny, nz, stream);
 }
 
@@ -1312,7 +1553,7 @@ int unet_conv3d_fwd_head(const uint16_t *x, int32_t ldx, int32_t offx, const uin
     if (!hw || !hb || !out) return -1;
     // 16 -> 16 channels with ReLU, then the head; the BF16 outputs are not stored
     ConvArgs a{x, w, b, nullptr, nullptr, ldx, offx, 16, 0, nz, ny, nx, 16, 16, 0, 1, 0, 0, 0,
-               x, ldx, offx, 16, 0, 0, 0, hw, hb, base, out, nullptr, 0, 0};
+               x, ldx, offx, 16, 0, 0, 0, hw, hb, base, out, nullptr, 0, 0, 0};
     return launch_conv(a, nx, ny, nz, stream);
 }
 
@@ -1322,7 +1563,7 @@ int unet_conv3d_fwd_cat(const uint16_t *x, int32_t ldx, int32_t offx, int32_t ci
                         void *stream) {
     if (nz % 2 || ny % 2 || nx % 2) return -1;  // x2 holds the half-resolution grid
     ConvArgs a{x, w, b, y, y32, ldx, offx, ldy, offy, nz, ny, nx, cin, cout, 0, relu, 0, 0, 0,
-               x2, ldx2, offx2, cin1, 1, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0};
+               x2, ldx2, offx2, cin1, 1, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0, 0};
     if (cin1 >= cin) return -1;
     return launch_conv(a, nx / 2, ny / 2, nz / 2, stream);
 }
@@ -1534,12 +1775,15 @@ int unet_mfma_selftest(const float *a, const float *b, float *d, void *stream) {
 
 namespace unet {
 
-int conv3d_dgrad_relu(const uint16_t *dy, int ldy, int offy, const uint16_t *wt, uint16_t *dx, int ldx, int offx,
-                      const uint16_t *m, int ldm, int offm, int nz, int ny, int nx, int cout, int cin, void *stream) {
-    if (!m || ldm % 8 || offm % 8 || !ch_ok(ldm, offm, cin) || !aligned16(m, nullptr, nullptr)) return -1;
-    ConvArgs a{dy, wt, nullptr, dx, nullptr, ldy, offy, ldx, offx, nz, ny, nx, cout, cin, 0, 0, 0, 0, 0,
-               dy, ldy, offy, cout, 0, 0, 0, nullptr, nullptr, nullptr, nullptr, m, ldm, offm};
-    return launch_conv(a, nx, ny, nz, stream);
+int conv3d(const Conv &c, int nz, int ny, int nx, int cin, int cout, void *stream) {
+    if (c.m && (c.ldm % 8 || c.offm % 8 || !ch_ok(c.ldm, c.offm, cout) || !aligned16(c.m, nullptr, nullptr))) return -1;
+    const bool cat = c.x2 != nullptr;
+    if (cat && (nz % 2 || ny % 2 || nx % 2 || c.cin1 >= cin)) return -1;
+    ConvArgs a{c.x, c.w, c.b, c.y, nullptr, c.ldx, 0, c.ldy, 0, nz, ny, nx, cin, cout, 0, c.relu, 0, 0, 0,
+               cat ? c.x2 : c.x, cat ? c.ldx2 : c.ldx, 0, cat ? c.cin1 : cin, cat ? 1 : 0, 0, 0,
+               nullptr, nullptr, nullptr, nullptr, c.m, c.ldm, c.offm, 1};
+    const int h = cat ? 2 : 1;
+    return launch_conv(a, nx / h, ny / h, nz / h, stream);
 }
 
 int pool_bwd_relu(const uint16_t *dy, int ldy, int offy, uint16_t *dx, int ldx, int offx, const uint16_t *m, int ldm,
@@ -1580,13 +1824,18 @@ int head_bwd_relu(const uint16_t *x, int ldx, const float *w, const float *dout,
     return head_bwd<true>(x, ldx, w, dout, dx, dw, db, nvox, c, stream);
 }
 
-int conv3d_wtrans_all(const uint16_t *w, uint16_t *wt, const TransTable &t, void *stream) {
-    if (!w || !wt || t.n <= 0 || t.n > kMaxTrans) return -1;
+int64_t conv3d_packed_len(int cin, int cout) { return packed_len(cin, cout); }
+
+int conv3d_pack(const uint16_t *w, uint16_t *packed, const PackTable &t, void *stream) {
+    if (!w || !packed || t.n <= 0 || t.n > kMaxPack || !aligned16(w, packed, nullptr)) return -1;
     int64_t most = 0;
-    for (int l = 0; l < t.n; ++l) most = std::max<int64_t>(most, (int64_t)t.cin[l] * kpad_of(t.cout[l]));
+    for (int l = 0; l < t.n; ++l) {
+        if (t.l[l].cin % 16 || t.l[l].cout % 16 || t.l[l].from % 8 || t.l[l].to % 8) return -1;
+        most = std::max(most, packed_len(t.l[l].cin, t.l[l].cout) / 8);
+    }
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_wtrans_all, dim3((unsigned)std::min<int64_t>((most + 255) / 256, 256), (unsigned)t.n), dim3(256), 0,
-                       static_cast<hipStream_t>(stream), w, wt, t);
+    hipLaunchKernelGGL(k_pack, dim3((unsigned)std::min<int64_t>((most + 255) / 256, 256), (unsigned)t.n), dim3(256), 0,
+                       static_cast<hipStream_t>(stream), w, packed, t);
     return status(hipGetLastError());
 }
 

@@ -73,9 +73,9 @@ struct unet_net {
     int dims[4][3];
     int64_t vox[4];
     ParamLayout P;
-    unet::TransTable trans{};
-    int64_t wt_off[kLayers] = {};
-    size_t off_p, off_pb, off_g, off_m, off_v, off_act[A_COUNT], off_out, off_gact[A_COUNT], off_gout, off_wt,
+    unet::PackTable pack{};
+    int64_t w_at[kLayers] = {}, wt_at[kLayers] = {};
+    size_t off_p, off_pb, off_g, off_m, off_v, off_act[A_COUNT], off_out, off_gact[A_COUNT], off_gout, off_packed,
         off_loss, bytes;
     char *ws = nullptr;
     hipStream_t st = nullptr;
@@ -106,6 +106,20 @@ struct unet_net {
         };
         off_p = take(sizeof(float) * P.total);
         off_pb = take(sizeof(uint16_t) * P.total);
+        // weights in the kernels' order: every layer's, and in training the transposed ones of
+        // every layer with a backward data convolution (all but the first)
+        int64_t packed = 0;
+        pack.n = 0;
+        auto packed_layer = [&](int l, bool transposed) {
+            const int cin = transposed ? kSpec[l].cout : kSpec[l].cin, cout = transposed ? kSpec[l].cin : kSpec[l].cout;
+            (transposed ? wt_at : w_at)[l] = packed;
+            pack.l[pack.n++] = unet::PackLayer{cin, cout, transposed ? 1 : 0, P.w[l], packed};
+            packed += unet::conv3d_packed_len(cin, cout);
+        };
+        for (int l = 0; l < kLayers; ++l) packed_layer(l, false);
+        for (int l = 0; train && l < kLayers; ++l)
+            if (l != E1A) packed_layer(l, true);
+        off_packed = take(sizeof(uint16_t) * packed);
         off_g = off_m = off_v = 0;
         if (train) {
             off_g = take(sizeof(float) * P.total);
@@ -114,42 +128,34 @@ struct unet_net {
         }
         for (int a = 0; a < A_COUNT; ++a) off_act[a] = take(sizeof(uint16_t) * vox[kActLevel[a]] * kActCh[a]);
         off_out = take(sizeof(float) * vox[0]);
-        off_gout = off_wt = off_loss = 0;
+        off_gout = off_loss = 0;
         for (int a = 0; a < A_COUNT; ++a) off_gact[a] = 0;
         if (train) {
             for (int a = A_A1; a < A_COUNT; ++a) off_gact[a] = take(sizeof(uint16_t) * vox[kActLevel[a]] * kActCh[a]);
             off_gout = take(sizeof(float) * vox[0]);
-            // transposed weights of every layer with a backward data convolution (all but the first)
-            int64_t wt = 0;
-            trans.n = 0;
-            for (int l = 0; l < kLayers; ++l) {
-                if (l == E1A) continue;
-                const int k = trans.n++;
-                trans.cin[k] = kSpec[l].cin;
-                trans.cout[k] = kSpec[l].cout;
-                trans.w_off[k] = P.w[l];
-                trans.wt_off[k] = wt_off[l] = wt;
-                wt = align64(wt + (int64_t)kSpec[l].cin * unet_kpad(kSpec[l].cout));
-            }
-            off_wt = take(sizeof(uint16_t) * wt);
             off_loss = take(sizeof(float) * 64);
         }
         bytes = o;
     }
 
-    // one 3x3x3 convolution of layer l on level lev: x (ldx, offx) -> y (ldy, offy)
-    hipError_t conv(int l, const uint16_t *x, int ldx, int offx, uint16_t *y, int ldy, int offy, int lev, bool relu) {
+    // the weights of layer l in the kernels' order, and its transposed ones
+    const uint16_t *pw(int l) const { return at<uint16_t>(off_packed) + w_at[l]; }
+    const uint16_t *pwt(int l) const { return at<uint16_t>(off_packed) + wt_at[l]; }
+    int pack_weights() { return unet::conv3d_pack(pb(), at<uint16_t>(off_packed), pack, st); }
+
+    // one 3x3x3 convolution with ReLU of layer l on level lev: x (rows of ldx) -> y (rows of ldy)
+    hipError_t conv(int l, const uint16_t *x, int ldx, uint16_t *y, int ldy, int lev) {
         const int *d = dims[lev];
-        return to_hip(unet_conv3d_fwd(x, ldx, offx, pb() + P.w[l], p() + P.b[l], y, ldy, offy, nullptr, d[0], d[1],
-                                      d[2], kSpec[l].cin, kSpec[l].cout, relu ? 1 : 0, st));
+        return to_hip(unet::conv3d(unet::Conv{x, ldx, pw(l), p() + P.b[l], y, ldy, 1}, d[0], d[1], d[2], kSpec[l].cin,
+                                   kSpec[l].cout, st));
     }
 
     // a decoder convolution of layer l on level lev over [skip x (c1 channels), the
     // level below's x2 (c2 channels) upsampled], the concatenation never stored
     hipError_t conv_cat(int l, const uint16_t *x, int c1, const uint16_t *x2, int c2, uint16_t *y, int lev) {
         const int *d = dims[lev];
-        return to_hip(unet_conv3d_fwd_cat(x, c1, 0, c1, x2, c2, 0, pb() + P.w[l], p() + P.b[l], y, kSpec[l].cout, 0,
-                                          nullptr, d[0], d[1], d[2], kSpec[l].cin, kSpec[l].cout, 1, st));
+        return to_hip(unet::conv3d(unet::Conv{x, c1, pw(l), p() + P.b[l], y, kSpec[l].cout, 1, x2, c2, c1}, d[0], d[1],
+                                   d[2], kSpec[l].cin, kSpec[l].cout, st));
     }
 
     hipError_t forward(const uint16_t *feat, const float *base, float *out) {
@@ -164,21 +170,21 @@ struct unet_net {
             // the level below upsampled in place, so no concatenation is written and
             // pooling reads whole rows.  Training keeps the concatenations: the weight
             // gradients read them.
-            run(conv(E1A, feat, kIn, 0, act(A_A1), kC1, 0, 0, true));
-            run(conv(E1B, act(A_A1), kC1, 0, act(A_CAT1), kC1, 0, 0, true));
+            run(conv(E1A, feat, kIn, act(A_A1), kC1, 0));
+            run(conv(E1B, act(A_A1), kC1, act(A_CAT1), kC1, 0));
             run(to_hip(unet_pool_fwd(act(A_CAT1), kC1, 0, act(A_P2), kC1, 0, d0[0], d0[1], d0[2], kC1, st)));
-            run(conv(E2A, act(A_P2), kC1, 0, act(A_A2), kC2, 0, 1, true));
-            run(conv(E2B, act(A_A2), kC2, 0, act(A_CAT2), kC2, 0, 1, true));
+            run(conv(E2A, act(A_P2), kC1, act(A_A2), kC2, 1));
+            run(conv(E2B, act(A_A2), kC2, act(A_CAT2), kC2, 1));
             run(to_hip(unet_pool_fwd(act(A_CAT2), kC2, 0, act(A_P3), kC2, 0, d1[0], d1[1], d1[2], kC2, st)));
-            run(conv(E3A, act(A_P3), kC2, 0, act(A_A3), kC3, 0, 2, true));
-            run(conv(E3B, act(A_A3), kC3, 0, act(A_CAT3), kC3, 0, 2, true));
+            run(conv(E3A, act(A_P3), kC2, act(A_A3), kC3, 2));
+            run(conv(E3B, act(A_A3), kC3, act(A_CAT3), kC3, 2));
             run(to_hip(unet_pool_fwd(act(A_CAT3), kC3, 0, act(A_P4), kC3, 0, d2[0], d2[1], d2[2], kC3, st)));
-            run(conv(B4A, act(A_P4), kC3, 0, act(A_B4A), kC4, 0, 3, true));
-            run(conv(B4B, act(A_B4A), kC4, 0, act(A_B4B), kC4, 0, 3, true));
+            run(conv(B4A, act(A_P4), kC3, act(A_B4A), kC4, 3));
+            run(conv(B4B, act(A_B4A), kC4, act(A_B4B), kC4, 3));
             run(conv_cat(D3A, act(A_CAT3), kC3, act(A_B4B), kC4, act(A_D3A), 2));
-            run(conv(D3B, act(A_D3A), kC3, 0, act(A_D3B), kC3, 0, 2, true));
+            run(conv(D3B, act(A_D3A), kC3, act(A_D3B), kC3, 2));
             run(conv_cat(D2A, act(A_CAT2), kC2, act(A_D3B), kC3, act(A_D2A), 1));
-            run(conv(D2B, act(A_D2A), kC2, 0, act(A_D2B), kC2, 0, 1, true));
+            run(conv(D2B, act(A_D2A), kC2, act(A_D2B), kC2, 1));
             run(conv_cat(D1A, act(A_CAT1), kC1, act(A_D2B), kC2, act(A_D1A), 0));
             // the last convolution with the head in its epilogue: D1B is never stored
             static_assert(kC1 == 16, "unet_conv3d_fwd_head is the 16-channel form");
@@ -186,26 +192,26 @@ struct unet_net {
                                             p() + P.b[kLayers], base, out, d0[0], d0[1], d0[2], st)));
             return e;
         }
-        run(conv(E1A, feat, kIn, 0, act(A_A1), kC1, 0, 0, true));
-        run(conv(E1B, act(A_A1), kC1, 0, act(A_CAT1), kC1 + kC2, 0, 0, true));
+        run(conv(E1A, feat, kIn, act(A_A1), kC1, 0));
+        run(conv(E1B, act(A_A1), kC1, act(A_CAT1), kC1 + kC2, 0));
         run(to_hip(unet_pool_fwd(act(A_CAT1), kC1 + kC2, 0, act(A_P2), kC1, 0, d0[0], d0[1], d0[2], kC1, st)));
-        run(conv(E2A, act(A_P2), kC1, 0, act(A_A2), kC2, 0, 1, true));
-        run(conv(E2B, act(A_A2), kC2, 0, act(A_CAT2), kC2 + kC3, 0, 1, true));
+        run(conv(E2A, act(A_P2), kC1, act(A_A2), kC2, 1));
+        run(conv(E2B, act(A_A2), kC2, act(A_CAT2), kC2 + kC3, 1));
         run(to_hip(unet_pool_fwd(act(A_CAT2), kC2 + kC3, 0, act(A_P3), kC2, 0, d1[0], d1[1], d1[2], kC2, st)));
-        run(conv(E3A, act(A_P3), kC2, 0, act(A_A3), kC3, 0, 2, true));
-        run(conv(E3B, act(A_A3), kC3, 0, act(A_CAT3), kC3 + kC4, 0, 2, true));
+        run(conv(E3A, act(A_P3), kC2, act(A_A3), kC3, 2));
+        run(conv(E3B, act(A_A3), kC3, act(A_CAT3), kC3 + kC4, 2));
         run(to_hip(unet_pool_fwd(act(A_CAT3), kC3 + kC4, 0, act(A_P4), kC3, 0, d2[0], d2[1], d2[2], kC3, st)));
-        run(conv(B4A, act(A_P4), kC3, 0, act(A_B4A), kC4, 0, 3, true));
-        run(conv(B4B, act(A_B4A), kC4, 0, act(A_B4B), kC4, 0, 3, true));
+        run(conv(B4A, act(A_P4), kC3, act(A_B4A), kC4, 3));
+        run(conv(B4B, act(A_B4A), kC4, act(A_B4B), kC4, 3));
         run(to_hip(unet_up_fwd(act(A_B4B), kC4, 0, act(A_CAT3), kC3 + kC4, kC3, d2[0], d2[1], d2[2], kC4, st)));
-        run(conv(D3A, act(A_CAT3), kC3 + kC4, 0, act(A_D3A), kC3, 0, 2, true));
-        run(conv(D3B, act(A_D3A), kC3, 0, act(A_D3B), kC3, 0, 2, true));
+        run(conv(D3A, act(A_CAT3), kC3 + kC4, act(A_D3A), kC3, 2));
+        run(conv(D3B, act(A_D3A), kC3, act(A_D3B), kC3, 2));
         run(to_hip(unet_up_fwd(act(A_D3B), kC3, 0, act(A_CAT2), kC2 + kC3, kC2, d1[0], d1[1], d1[2], kC3, st)));
-        run(conv(D2A, act(A_CAT2), kC2 + kC3, 0, act(A_D2A), kC2, 0, 1, true));
-        run(conv(D2B, act(A_D2A), kC2, 0, act(A_D2B), kC2, 0, 1, true));
+        run(conv(D2A, act(A_CAT2), kC2 + kC3, act(A_D2A), kC2, 1));
+        run(conv(D2B, act(A_D2A), kC2, act(A_D2B), kC2, 1));
         run(to_hip(unet_up_fwd(act(A_D2B), kC2, 0, act(A_CAT1), kC1 + kC2, kC1, d0[0], d0[1], d0[2], kC2, st)));
-        run(conv(D1A, act(A_CAT1), kC1 + kC2, 0, act(A_D1A), kC1, 0, 0, true));
-        run(conv(D1B, act(A_D1A), kC1, 0, act(A_D1B), kC1, 0, 0, true));
+        run(conv(D1A, act(A_CAT1), kC1 + kC2, act(A_D1A), kC1, 0));
+        run(conv(D1B, act(A_D1A), kC1, act(A_D1B), kC1, 0));
         run(to_hip(unet_head_fwd(act(A_D1B), kC1, p() + P.w[kLayers], p() + P.b[kLayers], base, out, vox[0], kC1,
                                  st)));
         return e;
@@ -220,9 +226,10 @@ struct unet_net {
         const int cin = kSpec[l].cin, cout = kSpec[l].cout;
         int s = unet_conv3d_wgrad(x, ldx, 0, gy, ldg, 0, d[0], d[1], d[2], cin, cout, g() + P.w[l], g() + P.b[l], st);
         if (s == 0 && gx) {
-            const uint16_t *wt = at<uint16_t>(off_wt) + wt_off[l];
-            s = m ? unet::conv3d_dgrad_relu(gy, ldg, 0, wt, gx, ldgx, 0, m, ldgx, 0, d[0], d[1], d[2], cout, cin, st)
-                  : unet_conv3d_fwd(gy, ldg, 0, wt, nullptr, gx, ldgx, 0, nullptr, d[0], d[1], d[2], cout, cin, 0, st);
+            unet::Conv c{gy, ldg, pwt(l), nullptr, gx, ldgx, 0};
+            c.m = m;
+            c.ldm = ldgx;
+            s = unet::conv3d(c, d[0], d[1], d[2], cout, cin, st);
         }
         return to_hip(s);
     }
@@ -237,7 +244,6 @@ struct unet_net {
             if (e == hipSuccess) e = r;
         };
         const int *d0 = dims[0], *d1 = dims[1], *d2 = dims[2];
-        run(to_hip(unet::conv3d_wtrans_all(pb(), at<uint16_t>(off_wt), trans, st)));
         run(to_hip(unet::head_bwd_relu(act(A_D1B), kC1, p() + P.w[kLayers], dout, gact(A_D1B), g() + P.w[kLayers],
                                        g() + P.b[kLayers], vox[0], kC1, st)));
         run(conv_bwd(D1B, act(A_D1A), kC1, gact(A_D1B), kC1, gact(A_D1A), kC1, act(A_D1A), 0));
@@ -332,7 +338,8 @@ int unet_set_params(unet_net *n, const float *params_dev) {
     const int64_t P = n->P.total;
     hipError_t e = hipMemcpyAsync(n->p(), params_dev, sizeof(float) * P, hipMemcpyDeviceToDevice, n->st);
     if (e != hipSuccess) return -6;
-    const int s = unet_to_bf16(n->p(), n->pb(), P, n->st);
+    int s = unet_to_bf16(n->p(), n->pb(), P, n->st);
+    if (s == 0) s = n->pack_weights();
     if (s == 0) n->have_params = true;
     return s;
 }
@@ -367,9 +374,10 @@ int unet_adam_step(unet_net *n, float lr, float beta1, float beta2, float eps) {
         return -1;
     n->t += 1;
     // one step over the whole flat array; the BF16 mirror follows (bias entries of the
-    // mirror are never read)
-    return unet_adam(n->p(), n->at<float>(n->off_m), n->at<float>(n->off_v), n->g(), n->pb(), n->P.total, lr, beta1,
-                     beta2, eps, n->t, n->st);
+    // mirror are never read), and from it the kernels' copies of the weights
+    const int s = unet_adam(n->p(), n->at<float>(n->off_m), n->at<float>(n->off_v), n->g(), n->pb(), n->P.total, lr,
+                            beta1, beta2, eps, n->t, n->st);
+    return s ? s : n->pack_weights();
 }
 
 int unet_train_step(unet_net *n, const uint16_t *feat_dev, const float *target_dev, const uint8_t *mask_dev,
