@@ -25,7 +25,7 @@ namespace cl {
 namespace {
 
 constexpr size_t kAlign = 256;
-constexpr int kMeasMaxBlocks = 512;
+constexpr int kMeasMaxBlocks = 2048;
 constexpr int kMeasWaves = 4;
 constexpr int64_t kMaxWindow = int64_t(1) << 22;  // longest check window (steps)
 
@@ -226,8 +226,17 @@ struct Engine {
         // measure table and per-instance partial ranges
         std::vector<int4> mb;
         std::vector<int2> rg(ninst, make_int2(0, 0));
+        // Segments per wave: two, a wave's serial chain, while the chip has room (32^3 20 ->
+        // 6.6 us, 64^3 21 -> 8.6 against sixteen); up to 1024 workgroups, whose partials are
+        // cheap to add (128^3 29 -> 21 us; 2048 the same, and 5 us more to add them); then up
+        // to 2048, where a wave has 16 or more (256^3 263 -> 102; 156 with 1024).
+        int64_t segs = 0;
+        for (int i : live) segs += P[i].nseg;
+        int64_t per = std::max<int64_t>(2, (segs + 1024 * kMeasWaves - 1) / (1024 * kMeasWaves));
+        if (per > 16) per = std::max<int64_t>(16, (per + 1) / 2);
+        per *= kMeasWaves;
         for (int i : live) {
-            int64_t nb = (P[i].nseg + kMeasWaves * 16 - 1) / (kMeasWaves * 16);
+            int64_t nb = (P[i].nseg + per - 1) / per;
             nb = std::max<int64_t>(1, std::min<int64_t>(nb, kMeasMaxBlocks));
             rg[i] = make_int2((int)mb.size(), (int)nb);
             for (int64_t b = 0; b < nb; ++b) mb.push_back(make_int4(i, (int)b, (int)nb, (int)mb.size()));

@@ -517,24 +517,25 @@ __global__ __launch_bounds__(kMeasWaves * 64) void k_measure(Lattice L, MeasureL
     }
 }
 
-// Per-instance totals of the reduction partials: 64 threads stride over the
-// instance's partial slots, then a fixed-order wave reduction (deterministic).
-__global__ __launch_bounds__(64) void k_finish(const double *__restrict__ partial, const int2 *__restrict__ ranges,
-                                               double *results) {
+// Per-instance totals of the reduction partials: one wave per quantity strides over the
+// instance's partial slots, then a fixed-order wave reduction (deterministic).  Bound by
+// the latency of a few dependent loads (one wave for all quantities: 11.4 us at 128^3).
+__global__ __launch_bounds__(64 * NQ) void k_finish(const double *__restrict__ partial, const int2 *__restrict__ ranges,
+                                                    double *results) {
     const int inst = blockIdx.x;
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63, i = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int2 r = ranges[inst];
+    const bool mx = (i == Q_DCMAX || i == Q_CMAX);
+    double v = 0.0;
+    for (int b = lane; b < r.y; b += 64 * 8) {
+        double p[8];  // loaded together: past the end 0, which changes neither sum nor maximum
 #pragma unroll
-    for (int i = 0; i < NQ; ++i) {
-        const bool mx = (i == Q_DCMAX || i == Q_CMAX);
-        double v = 0.0;
-        for (int b = lane; b < r.y; b += 64) {
-            const double p = partial[(int64_t)(r.x + b) * NQ + i];
-            v = mx ? fmax(v, p) : v + p;
-        }
-        v = mx ? wave_max(v) : wave_sum(v);
-        if (lane == 0) results[(int64_t)inst * NQ + i] = v;
+        for (int k = 0; k < 8; ++k) p[k] = b + 64 * k < r.y ? partial[(int64_t)(r.x + b + 64 * k) * NQ + i] : 0.0;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) v = mx ? fmax(v, p[k]) : v + p[k];
     }
+    v = mx ? wave_max(v) : wave_sum(v);
+    if (lane == 0) results[(int64_t)inst * NQ + i] = v;
 }
 
 // ------------------------------------------------------------------ conversions
@@ -709,7 +710,7 @@ hipError_t launch_measure(const Lattice &L, const MeasureLaunch &M, bool react, 
 hipError_t launch_finish(const double *partial, const int2 *ranges, int32_t ninst, double *results, hipStream_t st) {
     if (ninst <= 0) return hipSuccess;
     (void)hipGetLastError();
-    hipLaunchKernelGGL(k_finish, dim3(ninst), dim3(64), 0, st, partial, ranges, results);
+    hipLaunchKernelGGL(k_finish, dim3(ninst), dim3(64 * NQ), 0, st, partial, ranges, results);
     return hipGetLastError();
 }
 
