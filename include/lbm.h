@@ -351,9 +351,10 @@ int lbm_reach_device(const uint8_t *pass_dev, int32_t nx, int32_t ny, int32_t nz
  * change flag lives in a fixed 256-byte device array of this library (one copy per
  * device, held until the process ends) instead of freshly allocated pinned host
  * memory; it does not grow with the grid, so every grid lbm_reach_device accepts
- * is accepted.  The flag is cleared by a kernel at the start of every sweep cycle
- * and read back with a copy into host memory followed by a synchronisation of
- * stream, once per cycle.  Calls that overlap on one device (other host threads,
+ * is accepted.  The array holds one flag for each of the sweep cycles issued between
+ * two waits (up to two); a kernel clears each flag at the start of its cycle, and
+ * all are read back with a copy into host memory followed by a synchronisation of
+ * stream.  Calls that overlap on one device (other host threads,
  * other streams) share that flag and race: serialise them. */
 int lbm_reach_device_static(const uint8_t *pass_dev, int32_t nx, int32_t ny, int32_t nz, int32_t faces,
                             uint8_t *hit_dev, int32_t *cycles, void *stream);
