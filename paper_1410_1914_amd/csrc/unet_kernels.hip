@@ -505,7 +505,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // The head on a wave's four rows of results (o[r]: row r, this lane's four channels): the
 // 16-lane groups' quarters and the rows change places, so that each lane has all 16 channels
 // of its voxel in row lane / 16 and adds them in channel order, as unet_head_fwd does.  (The
-// sum handed from group to group row by row took 150 us of a 192^3 pass against 121 us.)
+// sum handed from group to group, row by row, took the last convolution at 192^3 154 us; now
+// it takes 119.)
 __device__ __forceinline__ float head_of_rows(const uint2 (&o)[4], const float (&hw)[16], float sum) {
     uint32_t q[4][2];
 #pragma unroll
