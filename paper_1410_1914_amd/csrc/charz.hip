@@ -622,6 +622,9 @@ hipError_t reach_scratch(int32_t **out) {
 constexpr int kReachAhead = 2;  // cycles enqueued before their flags are read
 
 size_t reach_lds(int64_t nx, int64_t rows) { return 24 * (size_t)((nx + 63) / 64 * rows); }
+// What a sheet may take: k_reach_sheet's block-wide ORs have LDS of their own (256 bytes as
+// compiled), which the launch adds to the sheet's.
+constexpr size_t kMaxReachLds = kMaxLds - 1024;
 
 template <bool FIRST, bool WIDE>
 hipError_t launch_reach_t(const ReachArgs &a, int sheets, hipStream_t st) {
@@ -650,7 +653,7 @@ hipError_t reach_cycles(const uint8_t *pass_dev, int32_t nx, int32_t ny, int32_t
                         hipStream_t st, int32_t *flag_dev, Flag &&flag, int32_t *n_cycles) {
     const int64_t N = (int64_t)nx * ny * nz;
     (void)hipGetLastError();
-    if (reach_lds(nx, std::max(ny, nz)) <= kMaxLds) {
+    if (reach_lds(nx, std::max(ny, nz)) <= kMaxReachLds) {
         const bool wide = nx % 8 == 0 && ((reinterpret_cast<uintptr_t>(pass_dev) | reinterpret_cast<uintptr_t>(hit_dev)) & 7) == 0;
         ReachArgs z{pass_dev, hit_dev, nx, (int64_t)ny * nx, nx, ny, faces, flag_dev};  // the rows of a z plane
         ReachArgs y{pass_dev, hit_dev, (int64_t)ny * nx, nx, nx, nz, faces, flag_dev};  // the rows of a y plane

@@ -1,0 +1,20 @@
+"""Structure characterisation at the limits of what a workgroup's LDS holds: the reach's
+largest sheets, the first ones past them (line sweeps) and the sizes between, where a sheet
+alone would still fit 160 KB but not together with the kernel's own LDS."""
+import numpy as np
+import pytest
+
+from oracle import lbm as O
+
+pytestmark = pytest.mark.gpu
+
+
+# nx / 64 rounded up times the rows of a sheet: 6784, 6785, 6816, 6820, 6826, 6827; 6822, 6824
+@pytest.mark.parametrize("shape", [(1, 6784, 64), (1, 6785, 64), (1, 6816, 64), (1, 6820, 60), (1, 6826, 64),
+                                   (1, 6827, 64), (2, 1137, 384), (1706, 2, 256)])
+def test_reach_of_the_largest_sheets(hip, shape):
+    m = np.random.default_rng(sum(shape)).random(shape) >= 0.3
+    seed = np.zeros(shape, bool)
+    seed[:, :, 0] = seed[:, :, -1] = True
+    got, _ = hip.reach_device(m, 3)
+    assert np.array_equal(got.cpu().numpy(), O.flood(m, seed & m).astype(np.uint8))
