@@ -299,13 +299,19 @@ size_t sheet_lds(int64_t nx, int64_t rows) {
 }
 constexpr size_t kMaxLds = 160 << 10;
 
+// Lets a kernel's launches ask for up to `bytes` of dynamic LDS.  The limit belongs to the
+// process: every call sets the one value that all sizes share, so that calls of other host
+// threads never find it lowered between here and their launch.
+hipError_t allow_lds(const void *kernel, size_t bytes) {
+    return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+}
+
 template <int KIND>
 hipError_t launch_pore_sheet(const uint8_t *pore, int nx, int ny, int nz, const Dir13 &D, double *dp, hipStream_t st) {
     const int gcd = std::gcd(ny, nz);
     const SheetGeom g{nx, ny, nz, KIND == 0 ? ny : KIND == 1 ? nz : ny / gcd * nz};
     const size_t lds = sheet_lds(nx, g.rows);
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_pore_sheet<KIND>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    const hipError_t e = allow_lds(reinterpret_cast<const void *>(k_pore_sheet<KIND>), kMaxLds);
     if (e != hipSuccess) return e;
     // Few sheets leave CUs idle: two or three workgroups then share one, each laying out all
     // of its lines (25 us of a kind's 85-140 us at 256^3).  128^3: 158 us with one, 124 with
@@ -629,9 +635,6 @@ constexpr size_t kMaxReachLds = kMaxLds - 1024;
 template <bool FIRST, bool WIDE>
 hipError_t launch_reach_t(const ReachArgs &a, int sheets, hipStream_t st) {
     const size_t lds = reach_lds(a.nx, a.rows);
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(k_reach_sheet<FIRST, WIDE>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
     // few words: a wave to each 64 rows is enough
     const int threads = (a.nx + 63) / 64 * a.rows >= 512 ? kReachThreads : 256;
     hipLaunchKernelGGL((k_reach_sheet<FIRST, WIDE>), dim3(sheets), dim3(threads), lds, st, a);
@@ -641,6 +644,15 @@ hipError_t launch_reach_t(const ReachArgs &a, int sheets, hipStream_t st) {
 hipError_t launch_reach(const ReachArgs &a, bool first, bool wide, int sheets, hipStream_t st) {
     if (first) return wide ? launch_reach_t<true, true>(a, sheets, st) : launch_reach_t<true, false>(a, sheets, st);
     return wide ? launch_reach_t<false, true>(a, sheets, st) : launch_reach_t<false, false>(a, sheets, st);
+}
+
+hipError_t allow_reach(bool wide) {
+    const void *first = wide ? reinterpret_cast<const void *>(k_reach_sheet<true, true>)
+                             : reinterpret_cast<const void *>(k_reach_sheet<true, false>);
+    const void *next = wide ? reinterpret_cast<const void *>(k_reach_sheet<false, true>)
+                            : reinterpret_cast<const void *>(k_reach_sheet<false, false>);
+    const hipError_t e = allow_lds(first, kMaxReachLds);
+    return e == hipSuccess ? allow_lds(next, kMaxReachLds) : e;
 }
 
 // Cycles until one turns nothing on: the loop both reach entry points share.  `flag_dev`
@@ -657,7 +669,7 @@ hipError_t reach_cycles(const uint8_t *pass_dev, int32_t nx, int32_t ny, int32_t
         const bool wide = nx % 8 == 0 && ((reinterpret_cast<uintptr_t>(pass_dev) | reinterpret_cast<uintptr_t>(hit_dev)) & 7) == 0;
         ReachArgs z{pass_dev, hit_dev, nx, (int64_t)ny * nx, nx, ny, faces, flag_dev};  // the rows of a z plane
         ReachArgs y{pass_dev, hit_dev, (int64_t)ny * nx, nx, nx, nz, faces, flag_dev};  // the rows of a y plane
-        hipError_t e = hipSuccess;
+        hipError_t e = allow_reach(wide);
         *n_cycles = 0;
         // two cycles to a wait: waiting costs about as much as a cycle of a small grid, and a
         // cycle after the last one changes nothing

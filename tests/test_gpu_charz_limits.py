@@ -18,3 +18,31 @@ def test_reach_of_the_largest_sheets(hip, shape):
     seed[:, :, 0] = seed[:, :, -1] = True
     got, _ = hip.reach_device(m, 3)
     assert np.array_equal(got.cpu().numpy(), O.flood(m, seed & m).astype(np.uint8))
+
+
+def test_threads_with_different_sizes(hip):
+    """Calls of two host threads, one with small and one with large sheets, on streams of
+    their own: none is refused and each gives what it gives alone."""
+    import threading
+
+    import torch
+
+    maps = [np.random.default_rng(n).random((n, n, 60)) >= 0.4 for n in (8, 140)]
+    want = [(hip.pore_size_device(m).cpu(), hip.reach_device(m, 1)[0].cpu()) for m in maps]
+    errors = []
+
+    def work(k):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                for _ in range(150 if k == 0 else 40):
+                    assert torch.equal(hip.pore_size_device(maps[k]).cpu(), want[k][0])
+                    assert torch.equal(hip.reach_device(maps[k], 1)[0].cpu(), want[k][1])
+        except Exception as e:  # handed to the test's own thread
+            errors.append((k, e))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in (0, 1)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not errors, errors
