@@ -229,13 +229,17 @@ struct Engine {
         // Segments per wave: two, a wave's serial chain, while the chip has room (32^3 20 ->
         // 6.6 us, 64^3 21 -> 8.6 against sixteen); up to 1024 workgroups, whose partials are
         // cheap to add (128^3 29 -> 21 us; 2048 the same, and 5 us more to add them); then up
-        // to 2048, where a wave has 16 or more (256^3 263 -> 102; 156 with 1024).
-        int64_t segs = 0;
-        for (int i : live) segs += P[i].nseg;
-        int64_t per = std::max<int64_t>(2, (segs + 1024 * kMeasWaves - 1) / (1024 * kMeasWaves));
-        if (per > 16) per = std::max<int64_t>(16, (per + 1) / 2);
-        per *= kMeasWaves;
+        // to 2048, where a wave has 16 or more (256^3 263 -> 102; 156 with 1024).  From the
+        // instance's own segments alone: its totals are added in the same order by itself,
+        // in any batch and after others of the batch have finished, and the stop rule
+        // compares them between windows.
+        auto share = [](int64_t nseg) {
+            int64_t per = std::max<int64_t>(2, (nseg + 1024 * kMeasWaves - 1) / (1024 * kMeasWaves));
+            if (per > 16) per = std::max<int64_t>(16, (per + 1) / 2);
+            return per * kMeasWaves;
+        };
         for (int i : live) {
+            const int64_t per = share(P[i].nseg);
             int64_t nb = (P[i].nseg + per - 1) / per;
             nb = std::max<int64_t>(1, std::min<int64_t>(nb, kMeasMaxBlocks));
             rg[i] = make_int2((int)mb.size(), (int)nb);
