@@ -64,7 +64,7 @@ struct Engine {
     size_t off_zbase = 0;  // per-instance zeros: dense output on one instance's own grid
     std::vector<int> cb_start, cb_count;  // conversion blocks of each instance
     size_t off_f0 = 0, off_f1 = 0, off_om = 0, off_snap = 0, off_rec = 0, off_srec = 0, off_inst = 0, off_dbase = 0, off_sblk = 0,
-           off_sinst = 0,
+           off_sinst = 0, off_ranges = 0,
            off_cblk = 0, off_mblk = 0, off_rng = 0, off_part = 0, off_res = 0;
     int64_t cap_sblk = 0, cap_cblk = 0, cap_mblk = 0;
 
@@ -87,6 +87,7 @@ struct Engine {
     // Blocks of planes stepped several times in a row (plan_blocks): their number (1:
     // whole steps) and the steps a block takes before the next one's turn.
     int nblocks = 1, block_steps = 1;
+    std::vector<int> block_most;  // largest XCD's entries of every block's steps
     // Two steps per launch (one instance only): rows per tile (0 = off), planes per chunk.
     int t2_by = 0, t2_zc = 32;
     // Batches run as consecutive groups of instances whose combined working set
@@ -154,6 +155,7 @@ struct Engine {
         off_dbase = take(sizeof(int64_t) * ninst);
         off_zbase = take(sizeof(int64_t) * ninst);
         off_sblk = take(sizeof(uint32_t) * cap_sblk);
+        off_ranges = take(nblocks > 1 ? sizeof(StepRange) * kXcds * nblocks * block_steps : 0);
         off_sinst = take(sizeof(uint32_t) * (ninst > 1 ? cap_sblk : 1));
         off_cblk = take(sizeof(int2) * cap_cblk);
         off_mblk = take(sizeof(int4) * cap_mblk);
@@ -255,6 +257,10 @@ struct Engine {
         if (e == hipSuccess && !mb.empty())
             e = hipMemcpyAsync(at<int4>(off_mblk), mb.data(), sizeof(int4) * mb.size(), hipMemcpyHostToDevice, st);
         if (e == hipSuccess) e = hipMemcpyAsync(at<int2>(off_rng), rg.data(), sizeof(int2) * ninst, hipMemcpyHostToDevice, st);
+        std::vector<StepRange> br;
+        if (nblocks > 1 && !zstart.empty()) br = block_ranges();
+        if (e == hipSuccess && !br.empty())
+            e = hipMemcpyAsync(at<StepRange>(off_ranges), br.data(), sizeof(StepRange) * br.size(), hipMemcpyHostToDevice, st);
         if (e == hipSuccess) e = launch_order(L, at<uint32_t>(off_sblk), step_nent, at<SegRec>(off_srec), st);
         if (e == hipSuccess) e = hipStreamSynchronize(st);  // host vectors go out of scope
         g_valid = false;
@@ -425,37 +431,40 @@ struct Engine {
         s.nent = step_nent;
         s.list_inst = at<uint32_t>(off_sinst);
         s.single = ninst == 1 ? 1 : 0;
-        int most = step_nent;
-        if (xcd) {  // contiguous eighths of the list
-            most = 0;
-            for (int x = 0; x < kXcds; ++x) {
-                const int a = (int)((int64_t)step_nent * x / kXcds), b = (int)((int64_t)step_nent * (x + 1) / kXcds);
-                s.rng[x] = {a, b - a, 0, 0};
-                most = std::max(most, b - a);
-            }
-        }
-        set_grid(s, most);
+        set_grid(s, xcd ? (step_nent + kXcds - 1) / kXcds : step_nent);
         return s;
     }
+    // workgroups for at most `most` entries of an XCD (of the list, without the XCD-aware order)
     void set_grid(StepLaunch &s, int most) const {
         const int per = waves * spw;
         s.nblk = (xcd ? kXcds : 1) * ((most + per - 1) / per);
     }
 
-    // Planes za <= z < zb only (zb beyond nz: the rest from plane 0 on); each XCD its slab.
-    void set_planes(StepLaunch &s, int za, int zb) const {
+    // Planes za <= z < zb of the step list (zb beyond nz: the rest from plane 0 on); each XCD
+    // its slab.  Returns the entries of the largest.
+    int plane_ranges(int za, int zb, StepRange *r) const {
         const int nz = P[0].nz;
         int most = 0;
         for (int x = 0; x < kXcds; ++x) {
             const int *zs = zstart.data() + (int64_t)x * nz;
-            StepLaunch::Range &r = s.rng[x];
-            r.s0 = zs[za];
-            r.n0 = zs[std::min(zb, nz)] - zs[za];
-            r.s1 = zs[0];
-            r.n1 = zb > nz ? zs[zb - nz] - zs[0] : 0;
-            most = std::max(most, r.n0 + r.n1);
+            r[x] = {zs[za], zs[std::min(zb, nz)] - zs[za], zs[0], zb > nz ? zs[zb - nz] - zs[0] : 0};
+            most = std::max(most, r[x].n0 + r[x].n1);
         }
-        set_grid(s, most);
+        return most;
+    }
+    // The ranges of step t of block c (see plan_blocks), for every c and t.
+    std::vector<StepRange> block_ranges() {
+        std::vector<StepRange> r((size_t)nblocks * block_steps * kXcds);
+        block_most.resize((size_t)nblocks * block_steps);
+        const int nz = P[0].nz;
+        for (int c = 0; c < nblocks; ++c)
+            for (int t = 0; t < block_steps; ++t) {
+                const size_t k = (size_t)c * block_steps + t;
+                const int za = c == 0 ? t : nz * c / nblocks - t;
+                const int zb = c == nblocks - 1 ? nz + t : nz * (c + 1) / nblocks - t;
+                block_most[k] = plane_ranges(za, zb, r.data() + k * kXcds);
+            }
+        return r;
     }
 
     // Where both lattices are larger than the last-level cache (256 MB), a step streams
@@ -523,9 +532,9 @@ struct Engine {
                 const int T = (int)((n - k + r - 1) / r);
                 for (int c = 0; c < nblocks; ++c)
                     for (int t = 0; t < T; ++t) {
-                        const int za = c == 0 ? t : nz * c / nblocks - t;
-                        const int zb = c == nblocks - 1 ? nz + t : nz * (c + 1) / nblocks - t;
-                        set_planes(s, za, zb);
+                        const size_t b = (size_t)c * block_steps + t;
+                        s.ranges = at<StepRange>(off_ranges) + b * kXcds;
+                        set_grid(s, block_most[b]);
                         s.reverse = t & 1;
                         const int from = cur ^ (t & 1);
                         hipError_t e = launch_step(L, s, knudsen, react, f[from], f[from ^ 1], st);
@@ -908,8 +917,8 @@ int make_engine(int n, const lbm_grid *grids, const uint8_t *const *phases, cons
     E->check_every = params[0].check_every;
     // one y slab of the step list per XCD, when the slabs are at least two rows
     E->slabs = n == 1 && E->P[0].ny >= 2 * Engine::kXcds;
-    E->layout();
     E->plan_blocks();
+    E->layout();
     // segment indices are 32-bit; population byte offsets are 32-bit (buffer resources)
     if (E->nseg_total > (int64_t)INT32_MAX || 28 * E->stride >= ((int64_t)1 << 32) - 64) return LBM_ERR_INVALID_ARG;
     E->rs.assign(n, RunState{});

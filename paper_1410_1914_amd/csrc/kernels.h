@@ -57,17 +57,20 @@ struct Lattice {
                               // 7 x 64 (one block per 64 compact voxels), 7 * stride * 4 < 2^32
 };
 
+// What one XCD walks of the step list: n0 entries from s0 and then n1 from s1 (the planes
+// past the periodic end of a range of planes).
+struct StepRange {
+    int32_t s0, n0, s1, n1;
+};
+
 struct StepLaunch {
     int32_t waves;            // waves per workgroup: 1, 2, 4, 8
     int32_t spw;              // segments per wave: 1, 2, 4
     int32_t xcd;              // XCD-aware block order
     int32_t nblk;             // workgroups
     int32_t nent;             // entries of the list
-    // XCD-aware order: XCD x walks rng[x], n0 entries from s0 and then n1 from s1 (the
-    // planes past the periodic end of a range of planes).
-    struct Range {
-        int32_t s0, n0, s1, n1;
-    } rng[8];
+    const StepRange *ranges;  // one instance: what each XCD walks (8 of them, in device memory), or null:
+                              // an eighth of the list each
     const uint32_t *list_inst;// instance of each list entry (several instances), so a wave can load
                               // its instance constants in parallel with its segment record
     int32_t single;           // 1: one instance (its constants load without waiting for the record)

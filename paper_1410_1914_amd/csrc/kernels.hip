@@ -190,21 +190,42 @@ __device__ __forceinline__ void collide_store(const SegRec &R, const InstDev &I,
 // Fused pull stream + collide.  Each wave takes SPW consecutive list entries (row
 // segments holding fluid) and issues all their loads before any arithmetic, so a
 // wave keeps SPW x 8 loads in flight.  Workgroups reach the 8 XCDs round robin; with
-// the XCD-aware order XCD x walks its own part of the list (rng[x]), so neighbour rows
+// the XCD-aware order XCD x walks its own part of the list, so neighbour rows
 // share its L2.  The records lie in list order: one scalar load less in front of the
 // gather than through a list of segment numbers (105.2 -> 103.0 us per step at 256^3).
+//
+// The arguments fill one 64-byte line: a step of a small grid is bound by latencies, and every
+// line of arguments that is not fetched with the first is one more of them, longest where the
+// argument memory lies far from the GPU (in most processes).  lbm_step at 32^3, us per step in
+// near and far processes: 2.81 and 3.8 with 224 bytes (the ranges of the XCDs among them),
+// 2.74 and 3.07 with 96, 2.67 and 3.0 with these 64.
+struct StepArgs {
+    const SegRec *srec;
+    const float *omega;
+    const InstDev *inst;
+    const void *of;  // one instance: StepLaunch::ranges; several: list_inst
+    uint32_t stride;
+    int32_t nent;
+    uint32_t flags;  // kStepXcd, kStepReverse
+};
+static_assert(sizeof(StepArgs) + 2 * sizeof(float *) == 64, "one line");
+enum : uint32_t { kStepXcd = 1u, kStepReverse = 2u };
+
 template <int WAVES, int SPW, bool KNUDSEN, bool REACT, bool SINGLE>
-__global__ __launch_bounds__(WAVES * 64) void k_step(Lattice L, StepLaunch S, const float *__restrict__ fin,
+__global__ __launch_bounds__(WAVES * 64) void k_step(StepArgs a, const float *__restrict__ fin,
                                                     float *__restrict__ fout) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const StepLaunch::Range rng = S.rng[blockIdx.x & 7];
-    const int nent = S.xcd ? rng.n0 + rng.n1 : S.nent;
-    const int base = ((int)(S.xcd ? blockIdx.x >> 3 : blockIdx.x) * WAVES + wave) * SPW;
+    const int sh = a.flags & kStepXcd ? 3 : 0, x = (int)blockIdx.x & ((1 << sh) - 1);
+    const int q = a.nent >> sh, more = a.nent - (q << sh);  // an eighth, or an entry more in the first ones
+    StepRange rng{q * x + min(x, more), q + (x < more ? 1 : 0), 0, 0};
+    if (SINGLE && a.of) rng = static_cast<const StepRange *>(a.of)[x];
+    const int nent = rng.n0 + rng.n1;
+    const int base = ((int)(blockIdx.x >> sh) * WAVES + wave) * SPW;
     if (base >= nent) return;
-    const uint32_t S4 = 4u * L.stride;
+    const uint32_t S4 = 4u * a.stride;
     const __amdgpu_buffer_rsrc_t rin = rsrc(fin, 7u * S4), rout = rsrc(fout, 7u * S4);
-    const __amdgpu_buffer_rsrc_t rom = rsrc(L.omega, KNUDSEN ? S4 : 0u);
+    const __amdgpu_buffer_rsrc_t rom = rsrc(a.omega, KNUDSEN ? S4 : 0u);
     const SegRec *R[SPW];
     const InstDev *Ip[SPW];
     bool act[SPW];
@@ -214,10 +235,10 @@ __global__ __launch_bounds__(WAVES * 64) void k_step(Lattice L, StepLaunch S, co
     for (int k = 0; k < SPW; ++k) {
         const bool valid = base + k < nent;  // wave-uniform
         int idx = valid ? base + k : 0;
-        if (S.reverse) idx = nent - 1 - idx;
-        if (S.xcd) idx = idx < rng.n0 ? rng.s0 + idx : rng.s1 + (idx - rng.n0);
-        R[k] = &L.srec[idx];
-        Ip[k] = &L.inst[SINGLE ? 0 : S.list_inst[idx]];  // independent of the record
+        if (a.flags & kStepReverse) idx = nent - 1 - idx;
+        idx = idx < rng.n0 ? rng.s0 + idx : rng.s1 + (idx - rng.n0);
+        R[k] = &a.srec[idx];
+        Ip[k] = &a.inst[SINGLE ? 0 : static_cast<const uint32_t *>(a.of)[idx]];  // independent of the record
         act[k] = valid && bit(R[k]->m, lane);
         gather<KNUDSEN>(*R[k], rin, rom, act[k], r[k], j4[k]);
     }
@@ -620,15 +641,18 @@ template <int W, int SPW, bool SINGLE>
 hipError_t launch_step_t(const Lattice &L, const StepLaunch &S, bool kn, bool re, const float *fin, float *fout,
                          hipStream_t st) {
     const dim3 grid(S.nblk), block(W * 64);
+    const StepArgs a{L.srec, L.omega, L.inst,
+                     SINGLE ? (S.xcd ? (const void *)S.ranges : nullptr) : (const void *)S.list_inst, L.stride, S.nent,
+                     (S.xcd ? (uint32_t)kStepXcd : 0u) | (S.reverse ? (uint32_t)kStepReverse : 0u)};
     (void)hipGetLastError();  // drop a stale error (e.g. hipErrorNotReady from an event query)
     if (kn && re) {
-        hipLaunchKernelGGL((k_step<W, SPW, true, true, SINGLE>), grid, block, 0, st, L, S, fin, fout);
+        hipLaunchKernelGGL((k_step<W, SPW, true, true, SINGLE>), grid, block, 0, st, a, fin, fout);
     } else if (kn) {
-        hipLaunchKernelGGL((k_step<W, SPW, true, false, SINGLE>), grid, block, 0, st, L, S, fin, fout);
+        hipLaunchKernelGGL((k_step<W, SPW, true, false, SINGLE>), grid, block, 0, st, a, fin, fout);
     } else if (re) {
-        hipLaunchKernelGGL((k_step<W, SPW, false, true, SINGLE>), grid, block, 0, st, L, S, fin, fout);
+        hipLaunchKernelGGL((k_step<W, SPW, false, true, SINGLE>), grid, block, 0, st, a, fin, fout);
     } else {
-        hipLaunchKernelGGL((k_step<W, SPW, false, false, SINGLE>), grid, block, 0, st, L, S, fin, fout);
+        hipLaunchKernelGGL((k_step<W, SPW, false, false, SINGLE>), grid, block, 0, st, a, fin, fout);
     }
     return hipGetLastError();
 }
