@@ -241,6 +241,12 @@ int lbm_autotune(lbm_solver *s, int32_t steps_per_trial, double *ms_best);
 int lbm_set_temporal(lbm_solver *s, int32_t rows_per_tile, int32_t planes_per_chunk);
 int lbm_get_temporal(const lbm_solver *s, int32_t *rows_per_tile, int32_t *planes_per_chunk);
 
+/* How lbm_step(s, steps) walks the grid: in `blocks` blocks of planes of which each
+ * takes steps_per_round steps before the next one's turn (grids whose two lattices are
+ * larger than the last-level cache), or whole (1 and 1).  The populations are the same
+ * either way.  Pointers may be NULL; LBM_ERR_UNBOUND before lbm_bind. */
+int lbm_get_blocks(const lbm_solver *s, int64_t steps, int32_t *blocks, int32_t *steps_per_round);
+
 /* The loop of lbm_run_to_steady with a budget: at most max_new_steps further
  * steps (whole windows of K steps; fewer than K steps of budget does nothing).
  * Returns LBM_OK once converged, LBM_NOT_CONVERGED while the budget ran out

@@ -481,7 +481,16 @@ struct Engine {
     // (289 MB) 54.0, 47.3 / 50.3 in 2 / 3; 176^3 (222 MB, nearly cached) 34.9 whole,
     // 37.4 in 2.  Rounds of a quarter of a block's planes: 8, 16, 24, 32 steps took 97.9,
     // 92.7, 92.3, 93.0 us at 256^3 in 3 blocks of 85 planes.
+    // Rounds of fewer than five steps cost more launches of part of the chip's work than they
+    // save: whole over cut at 2, 3, 4, 5, 6 steps 0.88, 0.93, 0.98, 1.01, 1.02 at 256^3
+    // reactive in 4 blocks, 0.95, 1.02, 1.13, 1.09, 1.05 at 64 x 400^2 in 3, 0.86, 0.92, 0.97,
+    // 1.01, 1.02 at 96 x 420 x 400 D_eff in 4.  So a call of fewer steps, and one that would
+    // be split into shorter rounds, walks the whole grid, as does a grid with fewer than 20
+    // planes to a block (64 x 512^2 in 4 blocks of 16, any number of steps: 0.90 to 0.97;
+    // 40 x 500 x 400 in 2 of 20: 1.03; 48 x 420^2 in 2 of 24: 1.17).  Slabs of very uneven size
+    // (18 rows in 8 of them) cost nothing: 1.15 at 1500 x 18 x 500.
     static constexpr int64_t kWholeBytes = int64_t(240) << 20, kBlockBytes = int64_t(167) << 20;
+    static constexpr int kMinRound = 5, kMinPlanes = 4 * kMinRound;
     void plan_blocks() {
         nblocks = block_steps = 1;
         if (!slabs || ninst != 1) return;
@@ -489,11 +498,19 @@ struct Engine {
         const int nz = P[0].nz;
         if (bytes <= kWholeBytes) return;
         const int64_t n = (bytes + kBlockBytes - 1) / kBlockBytes;
-        if (nz / n < 8) return;  // too few planes in a block to move through
+        if (nz / n < kMinPlanes) return;
         nblocks = (int)n;
         block_steps = std::min<int>(32, (int)(nz / n / 4));
     }
-    bool blocked() const { return nblocks > 1 && xcd && !zstart.empty(); }
+    // the first round's steps of the n left, in rounds as even as can be
+    int round_steps(int64_t n) const {
+        const int64_t rounds = (n + block_steps - 1) / block_steps;
+        return (int)((n + rounds - 1) / rounds);
+    }
+    // whether n steps are taken in blocks of planes
+    bool blocked(int64_t n) const {
+        return nblocks > 1 && xcd && n / ((n + block_steps - 1) / block_steps) >= kMinRound;
+    }
 
     bool two_step() const { return t2_by > 0 && ninst == 1; }
     // the two-step kernel tiles rows of segments: the row layout only (Prepared)
@@ -525,11 +542,9 @@ struct Engine {
             }
         }
         StepLaunch s = step_launch();
-        if (blocked() && n - k > 1) {
-            const int nz = P[0].nz;
-            const int64_t rounds = (n - k + block_steps - 1) / block_steps;
-            for (int64_t r = rounds; r > 0; --r) {
-                const int T = (int)((n - k + r - 1) / r);
+        if (blocked(n - k)) {
+            while (k < n) {
+                const int T = round_steps(n - k);
                 for (int c = 0; c < nblocks; ++c)
                     for (int t = 0; t < T; ++t) {
                         const size_t b = (size_t)c * block_steps + t;
@@ -1387,6 +1402,15 @@ int lbm_get_temporal(const lbm_solver *s, int32_t *rows_per_tile, int32_t *plane
     if (!s) return LBM_ERR_INVALID_ARG;
     if (rows_per_tile) *rows_per_tile = s->E->t2_by;
     if (planes_per_chunk) *planes_per_chunk = s->E->t2_zc;
+    return LBM_OK;
+}
+
+int lbm_get_blocks(const lbm_solver *s, int64_t steps, int32_t *blocks, int32_t *steps_per_round) {
+    if (!s || steps < 1) return LBM_ERR_INVALID_ARG;
+    if (!s->E->bound) return LBM_ERR_UNBOUND;
+    const bool cut = !s->E->two_step() && s->E->blocked(steps);
+    if (blocks) *blocks = cut ? s->E->nblocks : 1;
+    if (steps_per_round) *steps_per_round = cut ? s->E->round_steps(steps) : 1;
     return LBM_OK;
 }
 

@@ -117,6 +117,7 @@ SIGNATURES = {
     "lbm_autotune": ([_P, c_int32, ctypes.POINTER(c_double)], c_int32),
     "lbm_set_temporal": ([_P, c_int32, c_int32], c_int32),
     "lbm_get_temporal": ([_P, ctypes.POINTER(c_int32), ctypes.POINTER(c_int32)], c_int32),
+    "lbm_get_blocks": ([_P, c_int64, ctypes.POINTER(c_int32), ctypes.POINTER(c_int32)], c_int32),
     "lbm_deff": ([_P, ctypes.POINTER(c_double)], c_int32),
     "lbm_reaction_rate": ([_P, ctypes.POINTER(c_double), ctypes.POINTER(c_double)], c_int32),
     "lbm_concentration": ([_P, _P], c_int32),
@@ -400,6 +401,12 @@ def lbm_get_temporal(h):
     return a.value, b.value
 
 
+def lbm_get_blocks(h, steps: int):
+    a, b = c_int32(), c_int32()
+    _check("lbm_get_blocks", load().lbm_get_blocks(h, steps, ctypes.byref(a), ctypes.byref(b)))
+    return a.value, b.value
+
+
 def lbm_deff(h):
     v = c_double()
     st = load().lbm_deff(h, ctypes.byref(v))
@@ -642,6 +649,10 @@ class Solver:
 
     def temporal(self):
         return lbm_get_temporal(self.h)
+
+    def blocks(self, steps):
+        """(blocks of planes, steps per round) of ``step(steps)``; (1, 1): the whole grid."""
+        return lbm_get_blocks(self.h, steps)
 
     def autotune(self, steps_per_trial=20):
         return lbm_autotune(self.h, steps_per_trial)
