@@ -399,6 +399,7 @@ int lbm_reach_device_static(const uint8_t *pass_dev, int32_t nx, int32_t ny, int
  * lbm19_set_initial_concentration: stored state f_i = a_i C0 with C0 a device
  *   FP32 array of N values (NULL: C0 = 0); resets the step count.
  * lbm19_step: nsteps steps of Eq. (21).
+ * lbm19_get_blocks: how lbm19_step(s, steps) walks the grid, as lbm_get_blocks.
  * lbm19_measure: one step that also measures; *info (may be NULL) receives the
  *   fluxes of the links crossed during that step (j_in, j_out, j_vol per unit
  *   area), rate and mass of the new state; LBM_ERR_DIVERGED on NaN.
@@ -424,6 +425,7 @@ int lbm19_workspace_bytes(const lbm19_solver *s, size_t *bytes);
 int lbm19_bind(lbm19_solver *s, void *workspace_dev, size_t bytes, void *hip_stream);
 int lbm19_set_initial_concentration(lbm19_solver *s, const float *c_dev);
 int lbm19_step(lbm19_solver *s, int64_t nsteps);
+int lbm19_get_blocks(const lbm19_solver *s, int64_t steps, int32_t *blocks, int32_t *steps_per_round);
 int lbm19_measure(lbm19_solver *s, lbm_run_info *info);
 int lbm19_run_to_steady(lbm19_solver *s, lbm_run_info *info);
 int lbm19_deff(const lbm19_solver *s, double *deff_over_d0);

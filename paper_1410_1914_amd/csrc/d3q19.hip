@@ -83,11 +83,10 @@ struct D19Args {
     int react_outlet;                   // 1: zero-gradient outlet (no open links at x = nx - 1)
     int open_inlet;                     // 1: open links at x = 0 (0 for the potential problem)
     int reverse;                        // 1: each XCD walks its part of the records backwards
-    // A step without measurement: XCD x walks n0 records from s0, then n1 from s1 (the
-    // planes past the periodic end of a range of planes).
-    struct Range {
-        int s0, n0, s1, n1;
-    } rng[8];
+    // A step without measurement: XCD x walks ranges[x] (in device memory: arguments of
+    // several lines make the steps of small grids longer) or, where null, an eighth of the
+    // records.
+    const cl::StepRange *__restrict__ ranges;
 };
 
 // Blocks are dealt round-robin to the 8 XCDs; give XCD k the k-th contiguous
@@ -160,7 +159,9 @@ __global__ __launch_bounds__(kBlock) void k_d3q19(D19Args a) {
         e = lb * (kBlock / 64) + wave;
         some = e < a.nent;
     } else {
-        const D19Args::Range r = a.rng[blockIdx.x & 7];
+        const int x = (int)blockIdx.x & 7, q = (int)a.nent >> 3, more = (int)a.nent & 7;
+        cl::StepRange r{q * x + min(x, more), q + (x < more ? 1 : 0), 0, 0};
+        if (a.ranges) r = a.ranges[x];
         const int n = r.n0 + r.n1;
         int k = (int)(blockIdx.x >> 3) * (kBlock / 64) + wave;
         some = k < n;
@@ -355,10 +356,12 @@ struct lbm19_solver {
     std::vector<D19Rec> rec;       // segments holding simulated voxels, in walking order
     std::vector<int> zstart;       // first record of every slab's planes (empty: no slabs)
     int nblocks = 1, block_steps = 1;  // blocks of planes, and the steps each takes in a row (plan_blocks)
+    std::vector<cl::StepRange> block_ranges;  // what the XCDs walk in every block's steps
+    std::vector<int> block_grid;              // and the workgroups of each
     std::vector<float> om_c, kn_c; // compact 1/tau and k n
     // workspace carve-up
     size_t off_f[2] = {0, 0}, off_mask = 0, off_cidx = 0, off_rec = 0, off_om = 0, off_kn = 0,
-           off_cs = 0, off_part = 0, off_red = 0, need = 0;
+           off_cs = 0, off_part = 0, off_red = 0, off_ranges = 0, need = 0;
     char *ws = nullptr;
     hipStream_t st = nullptr;
     int device = 0;
@@ -398,26 +401,21 @@ struct lbm19_solver {
         return a;
     }
 
+    static int grid_of(int most) { return 8 * ((most + kBlock / 64 - 1) / (kBlock / 64)); }
+
     // The records of planes za <= z < zb (zb beyond nz: the rest from plane 0 on), two
-    // XCDs to a slab; without slabs every record, an eighth to each XCD.  Returns the
-    // step's workgroups.
-    int set_planes(D19Args &a, int za, int zb) const {
+    // XCDs to a slab.  Returns the step's workgroups.
+    int plane_ranges(int za, int zb, cl::StepRange *r) const {
         int most = 0;
         for (int x = 0; x < 8; ++x) {
-            D19Args::Range &r = a.rng[x];
-            if (zstart.empty()) {
-                const int lo = (int)(nent * x / 8), hi = (int)(nent * (x + 1) / 8);
-                r = {lo, hi - lo, 0, 0};
-            } else {
-                const int *zs = zstart.data() + (int64_t)(x / 2) * P.nz;
-                const int n0 = zs[std::min(zb, P.nz)] - zs[za], n1 = zb > P.nz ? zs[zb - P.nz] - zs[0] : 0;
-                const int lo = x & 1 ? (n0 + n1) / 2 : 0, hi = x & 1 ? n0 + n1 : (n0 + n1) / 2;
-                r = {zs[za] + std::min(lo, n0), std::min(hi, n0) - std::min(lo, n0),
-                     zs[0] + std::max(lo - n0, 0), std::max(hi - n0, 0) - std::max(lo - n0, 0)};
-            }
-            most = std::max(most, r.n0 + r.n1);
+            const int *zs = zstart.data() + (int64_t)(x / 2) * P.nz;
+            const int n0 = zs[std::min(zb, P.nz)] - zs[za], n1 = zb > P.nz ? zs[zb - P.nz] - zs[0] : 0;
+            const int lo = x & 1 ? (n0 + n1) / 2 : 0, hi = x & 1 ? n0 + n1 : (n0 + n1) / 2;
+            r[x] = {zs[za] + std::min(lo, n0), std::min(hi, n0) - std::min(lo, n0),
+                    zs[0] + std::max(lo - n0, 0), std::max(hi - n0, 0) - std::max(lo - n0, 0)};
+            most = std::max(most, r[x].n0 + r[x].n1);
         }
-        return 8 * ((most + kBlock / 64 - 1) / (kBlock / 64));
+        return grid_of(most);
     }
 
     // Blocks of planes that take several steps while they are in the last-level cache
@@ -427,19 +425,49 @@ struct lbm19_solver {
     // reactive (1.24 GB) 292.8, 292.2 / 273.0 / 273.8 in 5 / 6 / 7; 160^3 Pt D_eff
     // (433 MB) 96.0, 81.3 / 87.0 in 2 / 3; 144^3 (310 MB) 73.1, 64.1 in 2; 128^3 (217 MB,
     // cached) 38.2, 41.1 in 2.  Rounds of 8 to 16 steps differ by 1-2%, of 20 by up to 5%.
+    // Rounds of fewer than five steps cost more launches of part of the chip's work than they
+    // save (whole over cut at 2, 3, 4, 5, 6, 8 steps 0.88, 0.96, 1.02, 1.06, 1.08, 1.12 at
+    // 192^3 in 4 blocks, 0.89, 0.98, 1.02, 1.05, 0.98, 1.02 at 64 x 400 x 256 in 3 with 6 and
+    // 8 in two rounds): shorter calls and rounds walk the whole grid, as do grids of fewer
+    // than 20 planes to a block (24 x 400 x 300 in 2: 0.87), grids that nearly fit the cache
+    // and would take rounds of fewer than eight (40 x 300 x 256, 273 MiB: 0.98), and slabs of
+    // uneven size (500 x 9 x 700: 0.94 to 0.99).
+    static constexpr int kMinRound = 5;
+    static constexpr double kMaxUneven = 1.2;
     void plan_blocks() {
         nblocks = block_steps = 1;
         if (zstart.empty()) return;
         const int64_t bytes = nf * (2 * 4 * kQ + 8) + nent * (int64_t)sizeof(D19Rec);
-        const int64_t whole = int64_t(240) << 20, block = int64_t(210) << 20;
-        const int64_t n = (bytes + block - 1) / block;
-        if (bytes <= whole || P.nz / n < 8) return;  // cached, or too few planes to move through
+        const int64_t block = int64_t(210) << 20, n = (bytes + block - 1) / block;
+        const int round = std::min<int>(12, (int)(P.nz / n / 4));
+        const int64_t whole = int64_t(round < 8 ? 320 : 240) << 20;
+        if (bytes <= whole || round < kMinRound) return;
         nblocks = (int)n;
-        block_steps = std::min<int>(12, (int)(P.nz / n / 4));
+        block_steps = round;
+        tabulate_blocks();
     }
 
-    hipError_t launch_planes(D19Args &a, int za, int zb) {
-        const int grid = set_planes(a, za, zb);
+    // The ranges of step t of block c, for every c and t, and their workgroups; no blocks
+    // where the XCDs' slabs are uneven.
+    void tabulate_blocks() {
+        block_ranges.assign((size_t)nblocks * block_steps * 8, cl::StepRange{});
+        block_grid.assign((size_t)nblocks * block_steps, 0);
+        const int nz = P.nz;
+        int64_t slots = 0;
+        for (int c = 0; c < nblocks; ++c)
+            for (int t = 0; t < block_steps; ++t) {
+                const size_t k = (size_t)c * block_steps + t;
+                block_grid[k] = plane_ranges(c == 0 ? t : nz * c / nblocks - t,
+                                             c == nblocks - 1 ? nz + t : nz * (c + 1) / nblocks - t,
+                                             block_ranges.data() + 8 * k);
+                slots += (int64_t)block_grid[k] * (kBlock / 64);
+            }
+        if ((double)slots <= kMaxUneven * (double)nent * block_steps) return;
+        nblocks = block_steps = 1;
+        block_ranges.clear();
+    }
+
+    hipError_t launch_step(const D19Args &a, int grid) {
         if (grid <= 0) return hipSuccess;
         if (react)
             k_d3q19<true, false><<<grid, kBlock, 0, st>>>(a);
@@ -448,30 +476,39 @@ struct lbm19_solver {
         return hipGetLastError();
     }
 
+    // whether n steps are taken in blocks of planes, and the first round's steps
+    bool blocked(int64_t n) const {
+        return nblocks > 1 && n / ((n + block_steps - 1) / block_steps) >= kMinRound;
+    }
+    int round_steps(int64_t n) const {
+        const int64_t rounds = (n + block_steps - 1) / block_steps;
+        return (int)((n + rounds - 1) / rounds);
+    }
+
     // n steps without measurement
     hipError_t run_steps(int64_t n) {
         hipError_t e = hipSuccess;
-        while (n > 0 && e == hipSuccess) {
-            if (nblocks == 1 || n == 1) {
-                D19Args a = args(false);
-                e = launch_planes(a, 0, P.nz);
+        if (!blocked(n)) {
+            for (; n > 0 && e == hipSuccess; --n) {
+                e = launch_step(args(false), grid_of((int)((nent + 7) / 8)));
                 cur ^= 1;
                 ++steps;
-                --n;
-                continue;
             }
-            const int64_t rounds = (n + block_steps - 1) / block_steps;
-            const int T = (int)((n + rounds - 1) / rounds), nz = P.nz;
+            return e;
+        }
+        while (n > 0 && e == hipSuccess) {
+            const int T = round_steps(n);
             for (int c = 0; c < nblocks && e == hipSuccess; ++c)
                 for (int t = 0; t < T && e == hipSuccess; ++t) {
+                    const size_t k = (size_t)c * block_steps + t;
                     D19Args a = args(false);
+                    a.ranges = at<cl::StepRange>(off_ranges) + 8 * k;
                     a.reverse = t & 1;
                     if (t & 1) {
                         a.fin = at<float>(off_f[cur ^ 1]);
                         a.fout = at<float>(off_f[cur]);
                     }
-                    e = launch_planes(a, c == 0 ? t : nz * c / nblocks - t,
-                                      c == nblocks - 1 ? nz + t : nz * (c + 1) / nblocks - t);
+                    e = launch_step(a, block_grid[k]);
                 }
             cur ^= T & 1;
             steps += T;
@@ -705,6 +742,7 @@ static int create19(const lbm_grid *g, const uint8_t *phase, const lbm_params *p
         s->off_cs = take(4 * (size_t)std::max<int64_t>(nf, 1));
         s->off_part = take(sizeof(double) * kRed * (size_t)std::max(s->nblk, 1));
         s->off_red = take(sizeof(double) * kRed);
+        s->off_ranges = take(sizeof(cl::StepRange) * s->block_ranges.size());
         s->need = o;
         *out = s.release();
         return LBM_OK;
@@ -1053,6 +1091,7 @@ int lbm19_bind(lbm19_solver *s, void *ws, size_t bytes, void *stream) {
     up(s->off_mask, s->mask.data(), 4 * s->mask.size());
     up(s->off_cidx, s->cidx.data(), 4 * s->cidx.size());
     up(s->off_rec, s->rec.data(), sizeof(D19Rec) * s->rec.size());
+    up(s->off_ranges, s->block_ranges.data(), sizeof(cl::StepRange) * s->block_ranges.size());
     up(s->off_om, s->om_c.data(), 4 * s->om_c.size());
     if (s->react) up(s->off_kn, s->kn_c.data(), 4 * s->kn_c.size());
     if (e == hipSuccess) e = hipStreamSynchronize(s->st);
@@ -1081,6 +1120,14 @@ int lbm19_step(lbm19_solver *s, int64_t nsteps) {
     if (!s || nsteps < 0) return LBM_ERR_INVALID_ARG;
     if (!s->ws) return LBM_ERR_UNBOUND;
     return cl::record_error(s->run_steps(nsteps), "lbm19_step");
+}
+
+int lbm19_get_blocks(const lbm19_solver *s, int64_t steps, int32_t *blocks, int32_t *steps_per_round) {
+    if (!s || steps < 1) return LBM_ERR_INVALID_ARG;
+    const bool cut = s->blocked(steps);
+    if (blocks) *blocks = cut ? s->nblocks : 1;
+    if (steps_per_round) *steps_per_round = cut ? s->round_steps(steps) : 1;
+    return LBM_OK;
 }
 
 int lbm19_measure(lbm19_solver *s, lbm_run_info *info) {

@@ -148,6 +148,7 @@ SIGNATURES = {
     "lbm19_bind": ([_P, _P, ctypes.c_size_t, _P], c_int32),
     "lbm19_set_initial_concentration": ([_P, _P], c_int32),
     "lbm19_step": ([_P, c_int64], c_int32),
+    "lbm19_get_blocks": ([_P, c_int64, ctypes.POINTER(c_int32), ctypes.POINTER(c_int32)], c_int32),
     "lbm19_measure": ([_P, ctypes.POINTER(lbm_run_info)], c_int32),
     "lbm19_run_to_steady": ([_P, ctypes.POINTER(lbm_run_info)], c_int32),
     "lbm19_deff": ([_P, ctypes.POINTER(c_double)], c_int32),
@@ -738,6 +739,12 @@ class Solver19:
 
     def step(self, n=1):
         return _check("lbm19_step", load().lbm19_step(self.h, n))
+
+    def blocks(self, steps):
+        """(blocks of planes, steps per round) of ``step(steps)``; (1, 1): the whole grid."""
+        a, b = c_int32(), c_int32()
+        _check("lbm19_get_blocks", load().lbm19_get_blocks(self.h, steps, ctypes.byref(a), ctypes.byref(b)))
+        return a.value, b.value
 
     def measure(self) -> lbm_run_info:
         r = lbm_run_info()

@@ -61,3 +61,39 @@ def test_every_tiling_on_a_cut_grid(hip, shape, mode, knudsen):
             assert torch.equal(a.populations(), want7), (spw, waves)
             a.step(33)
             assert torch.equal(a.populations(), want40), (spw, waves)
+
+
+def test_d3q19_short_calls_thin_blocks_and_uneven_slabs_walk_the_whole_grid(hip):
+    s = hip.Solver19(_map((90, 210, 220), 1), _params(hip, "deff", 1))
+    n, _ = s.blocks(200)
+    assert n >= 3
+    most = min(12, 90 // n // 4)
+    for k in range(1, 3 * most):
+        rounds = -(-k // most)
+        assert s.blocks(k) == ((n, -(-k // rounds)) if k // rounds >= 5 else (1, 1))
+    s.close()
+    for shape in ((16, 350, 400), (300, 9, 800), (50, 50, 50)):
+        s = hip.Solver19(_map(shape, 2), _params(hip, "deff", 1))
+        assert s.blocks(200) == (1, 1)
+        s.close()
+
+
+@pytest.mark.parametrize("shape,mode,steps", [((121, 170, 160), "react", 29), ((90, 210, 220), "deff", 41)])
+def test_d3q19_middle_blocks_and_empty_planes(hip, shape, mode, steps):
+    import torch
+
+    ph = _map(shape, 4)
+    ph[:, shape[1] // 3:shape[1] // 3 + 10] = 1
+    ph[40:48] = 1
+    if mode == "deff":
+        ph[:, 5, :] = 0
+    a, b = (hip.Solver19(ph, _params(hip, mode, 1)) for _ in range(2))
+    assert a.blocks(steps)[0] >= 3
+    c0 = torch.rand(a.shape, generator=torch.Generator().manual_seed(2))
+    for s in (a, b):
+        s.set_initial_concentration(c0)
+    a.step(steps)
+    for _ in range(steps):
+        b.step(1)
+    assert torch.equal(a.populations(), b.populations())
+    assert a.measure().as_dict() == b.measure().as_dict()
