@@ -438,7 +438,7 @@ struct lbm19_solver {
         nblocks = block_steps = 1;
         if (zstart.empty()) return;
         const int64_t bytes = nf * (2 * 4 * kQ + 8) + nent * (int64_t)sizeof(D19Rec);
-        const int64_t block = int64_t(210) << 20, n = (bytes + block - 1) / block;
+        const int64_t block = int64_t(210) << 20, n = std::max<int64_t>(1, (bytes + block - 1) / block);
         const int round = std::min<int>(12, (int)(P.nz / n / 4));
         const int64_t whole = int64_t(round < 8 ? 320 : 240) << 20;
         if (bytes <= whole || round < kMinRound) return;
