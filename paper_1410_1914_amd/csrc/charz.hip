@@ -294,6 +294,8 @@ __global__ __launch_bounds__(kSheetThreads) void k_pore_sheet(const uint8_t *__r
     }
 }
 
+int64_t sheet_line_words(int64_t nx, int64_t rows) { return sheet_words(nx) * rows + ring_words(rows) * nx; }
+
 size_t sheet_lds(int64_t nx, int64_t rows) {
     return 4 * (size_t)(sheet_words(nx) * (3 * rows + 32) + ring_words(rows) * nx) + 4 * kSheetThreads;
 }
@@ -313,12 +315,29 @@ hipError_t launch_pore_sheet(const uint8_t *pore, int nx, int ny, int nz, const 
     const size_t lds = sheet_lds(nx, g.rows);
     const hipError_t e = allow_lds(reinterpret_cast<const void *>(k_pore_sheet<KIND>), kMaxLds);
     if (e != hipSuccess) return e;
-    // Few sheets leave CUs idle: two or three workgroups then share one, each laying out all
-    // of its lines (25 us of a kind's 85-140 us at 256^3).  128^3: 158 us with one, 124 with
-    // two; 64^3: 70 with one, 62 with three; 256^3: 441 with one, 508 with two.
-    const int sheets = KIND == 0 ? nz : KIND == 1 ? ny : gcd, share = std::min({3, std::max(1, 256 / sheets), g.rows});
+    // Few sheets leave CUs idle: several workgroups then share one, each laying out all of its
+    // lines (25 us of a kind's 85-140 us at 256^3) and counting four rows or more.  128^3: 158
+    // us with one, 124 with two; 64^3: 70 with one, 59 with four; 256^3: 441 with one, 508 with
+    // two; 48 x 50 x 50 (two sheets of 1200 rows): 182 with three, 136 with 128.
+    const int sheets = KIND == 0 ? nz : KIND == 1 ? ny : gcd, share = std::max(1, std::min(256 / sheets, g.rows / 4));
     hipLaunchKernelGGL(k_pore_sheet<KIND>, dim3(sheets, share), dim3(kSheetThreads), lds, st, pore, g, D, dp);
     return hipGetLastError();
+}
+
+// Whether the pore size is counted by sheets: they have to fit LDS, and the lines that a
+// workgroup lays out for itself, about 4.5 ns a word of them, must not take longer than
+// walking.  yz diagonals that close late make a few very long sheets, which each workgroup
+// on them lays out whole.  Walking takes about 85 us and 1 us for 8000 voxels in grown
+// structures (58 us and 1 us for 10500 in random maps of 45% pore), the four launches by
+// sheets 45 us and the lines.  us walked / by sheets: 50^3 97 / 56, 40 x 50 x 50 (ten sheets
+// of 200 rows) 93 / 66, 48 x 60 x 64 93 / 70, 16 x 24 x 240 96 / 75, 80 x 100 x 64 157 / 93;
+// 48 x 50 x 50 (two of 1200) 93 / 136, 32 x 31 x 100 (one of 992) 99 / 181, 3 x 300 x 100 104
+// / 103; random maps 62 / 56, 61 / 66, 64 / 70, 59 / 74, 97 / 97; 62 / 136, 59 / 181, 57 / 103.
+bool by_sheets(int64_t nx, int64_t ny, int64_t nz) {
+    const int64_t ring = std::lcm(ny, nz);
+    if (sheet_lds(nx, std::max({ny, nz, ring})) > kMaxLds) return false;
+    const int64_t words = sheet_line_words(nx, ny) + sheet_line_words(nx, nz) + 2 * sheet_line_words(nx, ring);
+    return 0.0045 * (double)words <= 40.0 + (double)(nx * ny * nz) / 8000.0;
 }
 
 // Seeds of the reach: pass voxels on the selected x faces.
@@ -742,7 +761,7 @@ int lbm_pore_size_device(const uint8_t *pore_dev, int32_t nx, int32_t ny, int32_
     hipStream_t st = static_cast<hipStream_t>(stream);
     (void)hipGetLastError();
     hipError_t e = hipSuccess;
-    if (sheet_lds(nx, std::max({(int64_t)ny, (int64_t)nz, std::lcm((int64_t)ny, (int64_t)nz)})) <= kMaxLds) {
+    if (by_sheets(nx, ny, nz)) {
         e = launch_pore_sheet<1>(pore_dev, nx, ny, nz, D, dp_dev, st);
         if (e == hipSuccess) e = launch_pore_sheet<2>(pore_dev, nx, ny, nz, D, dp_dev, st);
         if (e == hipSuccess) e = launch_pore_sheet<3>(pore_dev, nx, ny, nz, D, dp_dev, st);

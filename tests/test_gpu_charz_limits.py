@@ -46,3 +46,44 @@ def test_threads_with_different_sizes(hip):
     for t in threads:
         t.join()
     assert not errors, errors
+
+
+def _us(f):
+    """Microseconds of a call, the best of five rounds of ten."""
+    import time
+
+    import torch
+
+    f()
+    best = float("inf")
+    for _ in range(5):
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        for _ in range(10):
+            f()
+        torch.cuda.synchronize()
+        best = min(best, time.perf_counter() - t)
+    return best * 1e5
+
+
+@pytest.mark.parametrize("shape", [(52, 50, 50), (48, 50, 50), (32, 31, 100), (1, 200, 200), (3, 300, 100)])
+def test_pore_size_of_long_rings_takes_no_longer_than_of_a_cube(hip, shape):
+    """A few rings of many rows (their y and z edges have a small common divisor, or one of
+    them is short) are not laid out by a few workgroups; these maps have no more voxels than
+    the cube, which takes both routes about as long."""
+    import torch
+
+    def pore(s):
+        return (torch.rand(s, generator=torch.Generator("cuda").manual_seed(1), device="cuda") < 0.45).to(torch.uint8)
+
+    cube, m = pore((51, 51, 50)), pore(shape)
+    assert np.array_equal(hip.pore_size_device(m).cpu().numpy(), O.pore_chords(m.cpu().numpy().astype(bool)))
+    assert _us(lambda: hip.pore_size_device(m)) <= 1.6 * _us(lambda: hip.pore_size_device(cube))
+
+
+@pytest.mark.parametrize("shape", [(40, 50, 50), (16, 24, 240), (2, 100, 100), (10, 100, 64), (12, 30, 33), (7, 14, 300)])
+@pytest.mark.parametrize("share", [0.05, 0.5])
+def test_pore_size_with_several_workgroups_to_a_sheet(hip, shape, share):
+    m = np.random.default_rng(sum(shape)).random(shape) >= share
+    m[shape[0] // 2] = True
+    assert np.array_equal(hip.pore_size_device(m).cpu().numpy(), O.pore_chords(m))
