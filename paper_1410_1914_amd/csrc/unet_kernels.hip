@@ -1619,9 +1619,17 @@ int unet_conv3d_wgrad(const uint16_t *x, int32_t ldx, int32_t offx, const uint16
     if (cin % 16 || cout % 16 || ldx % 8 || offx % 8 || lddy % 8 || offdy % 8) return -1;
     const int64_t nvox = (int64_t)nz * ny * nx;
     const int64_t xplane = 2 * (int64_t)ny * nx * ldx, dplane = 2 * (int64_t)ny * nx * lddy;
+    // The marching form but for rows that fill little of its tiles of 32 (us there and in the
+    // general form, 512 x 512 rows: 1 voxel 138 / 83 (16 -> 16 channels), 751 / 180 (32 -> 64);
+    // 2: 138 / 160, 750 / 361; 3: 139 / 230, 751 / 568; 4: 139 / 317, 749 / 706; 6: 139 / 455, 750 /
+    // 1133), and for grids of up to 1024 voxels, which keep to two runs of planes (two sums
+    // have no order; the general form has two workgroups per sum there), of more than 16
+    // planes (8 x 8 x 15: 15.5 / 23, 22 / 26; 20 planes of 7 x 7 17 / 23, 24 / 26; 60 of 4 x 4 30 /
+    // 23, 42 / 26; 1000 of one voxel 227 / 22).
+    const int two = cout % 32 == 0 ? 2 : 1;
+    const bool few = nvox <= 1024;
     if (((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(dy)) & 15) == 0 && xplane * nz <= kMaxX &&
-        dplane * nz <= kMaxX) {
-        const int two = cout % 32 == 0 ? 2 : 1;
+        dplane * nz <= kMaxX && nx >= (two == 2 ? 5 : 3) && !(few && nz > 16)) {
         const int64_t tiles = (int64_t)((nx + kWX - 1) / kWX) * ((ny + kWY - 1) / kWY) * (cin / 16) * (cout / (16 * two));
         // Runs per tile: about one workgroup per CU, up to two where the runs stay 24 planes
         // long (a run copies two planes beyond its own and adds its sums atomically).  The 14
@@ -1629,7 +1637,7 @@ int unet_conv3d_wgrad(const uint16_t *x, int32_t ldx, int32_t offx, const uint16
         // 768 workgroups each; the 48 -> 16 layer alone 115 / 78 / 56 / 74 / 61.
         const int64_t runs = std::max(std::max<int64_t>(1, 256 / tiles), std::min<int64_t>(512 / tiles, nz / 24));
         int64_t zr = (nz + runs - 1) / runs;
-        if (nx <= kWX && ny <= kWY) zr = std::max<int64_t>(zr, (nz + 1) / 2);  // two runs: their sum has no order
+        if (few) zr = std::max<int64_t>(zr, (nz + 1) / 2);
         const int64_t blocks = tiles * ((nz + zr - 1) / zr);
         if (blocks <= 0x7fffffff) {
             const WgradArgs a{x, dy, dw, db, ldx, offx, lddy, offdy, nz, ny, nx, cin, cout, kpad_of(cin), (int)zr,
