@@ -101,7 +101,6 @@ constexpr int kRawBuffer = 0x00020000;
 constexpr int64_t kMaxX = ((int64_t)1 << 31) - 16;
 constexpr uint32_t kNoOff = 0x80000000u;
 
-constexpr int kSX = 16, kSBX = kSX + 2;  // voxels of a tile's row, halo included
 constexpr int kCC = 16;                  // input channels per stage
 constexpr int kVS = 16;  // LDS elements per voxel: the 16 channels, unpadded.  A 32-byte voxel
                          // stride reads at the full LDS rate on gfx950 (the lanes' 16-byte
@@ -121,9 +120,9 @@ constexpr int kWaitVmcnt0 = wait_vmcnt(0);
 struct ConvTile {
     int x0, y0, zc, slice;
 };
-template <int TY>
+template <int TX, int TY>
 __device__ __forceinline__ ConvTile conv_tile(int nx) {
-    const int nxt = (nx + kSX - 1) / kSX;
+    const int nxt = (nx + TX - 1) / TX;
     const int nblk = (int)(gridDim.x * gridDim.y * gridDim.z);
     const int b = (int)(blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z));
     const int xcd = b % 8, per = nblk / 8, extra = nblk % 8;
@@ -135,8 +134,19 @@ __device__ __forceinline__ ConvTile conv_tile(int nx) {
     const int band = rem / (nxt * kYB * nzc), in_band = rem % (nxt * kYB * nzc);
     const int h = min(kYB, nyt - band * kYB);
     const int xt = in_band % nxt, yin = (in_band / nxt) % h, zc = in_band / (nxt * h);
-    return ConvTile{xt * kSX, (band * kYB + yin) * TY, zc, slice};
+    return ConvTile{xt * TX, (band * kYB + yin) * TY, zc, slice};
 }
+
+// A workgroup's tile: S channel slices times 4 / S waves of four rows of 16 voxels each, XG
+// of them side by side in x and the others on top of each other in y.
+template <int S, int XG>
+struct Tile {
+    static constexpr int TX = 16 * XG, TY = 16 / (S * XG);
+    static constexpr int BX = TX + 2, PLANE = BX * (TY + 2);  // an input plane, halo included
+    int x, y, slice;  // this wave's first voxel in the tile, and its slice of the workgroup's
+    __device__ __forceinline__ explicit Tile(int wave)
+        : x(16 * (wave % XG)), y(4 * (wave % (4 / S) / XG)), slice(wave / (4 / S)) {}
+};
 
 __device__ __forceinline__ bf16x8 lane_select(bool second, bf16x8 x, bf16x8 y) {
     const uint4 a = __builtin_bit_cast(uint4, x), b = __builtin_bit_cast(uint4, y);
@@ -150,38 +160,42 @@ __device__ __forceinline__ bf16x8 lane_select(bool second, bf16x8 x, bf16x8 y) {
 struct Frags {
     bf16x8 a[6], b[6], c[7], p[4];
 };
-// where a lane reads them (LDS elements from the plane's start)
+// where a lane reads them (LDS elements from the plane's start); BX: voxels of a halo row
+template <int BX>
 struct FragAt {
     int a, c, d;
-    __device__ __forceinline__ FragAt(int row, int m, int kb) {
+    __device__ __forceinline__ FragAt(int row, int x, int kb) {
         const int chan = 8 * (kb & 1), g = kb >> 1;
-        a = (row * kSBX + m + g) * kVS + chan;
-        c = (g ? (row + 1) * kSBX + m : row * kSBX + m + 2) * kVS + chan;
-        d = (row * kSBX + m) * kVS + chan;
+        a = (row * BX + x + g) * kVS + chan;
+        c = (g ? (row + 1) * BX + x : row * BX + x + 2) * kVS + chan;
+        d = (row * BX + x) * kVS + chan;
     }
 };
 __device__ __forceinline__ bf16x8 frag(const uint16_t *p, int voxel) {
     return __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4 *>(p + voxel * kVS));
 }
-__device__ __forceinline__ void read_a(Frags &F, const uint16_t *plane, const FragAt &at) {
+template <int BX>
+__device__ __forceinline__ void read_a(Frags &F, const uint16_t *plane, const FragAt<BX> &at) {
 #pragma unroll
-    for (int r = 0; r < 6; ++r) F.a[r] = frag(plane + at.a, r * kSBX);
+    for (int r = 0; r < 6; ++r) F.a[r] = frag(plane + at.a, r * BX);
 }
-__device__ __forceinline__ void read_b(Frags &F, const uint16_t *plane, const FragAt &at) {
+template <int BX>
+__device__ __forceinline__ void read_b(Frags &F, const uint16_t *plane, const FragAt<BX> &at) {
 #pragma unroll
-    for (int r = 0; r < 6; ++r) F.b[r] = frag(plane + at.a, r * kSBX + 1);
+    for (int r = 0; r < 6; ++r) F.b[r] = frag(plane + at.a, r * BX + 1);
 }
-__device__ __forceinline__ void read_c(Frags &F, const uint16_t *plane, const FragAt &at) {
+template <int BX>
+__device__ __forceinline__ void read_c(Frags &F, const uint16_t *plane, const FragAt<BX> &at) {
     F.c[0] = frag(plane + at.d, 0);
 #pragma unroll
-    for (int r = 0; r < 5; ++r) F.c[r + 1] = frag(plane + at.c, r * kSBX);
-    F.c[6] = frag(plane + at.d, 5 * kSBX + 2);
+    for (int r = 0; r < 5; ++r) F.c[r + 1] = frag(plane + at.c, r * BX);
+    F.c[6] = frag(plane + at.d, 5 * BX + 2);
 }
 // The products of one input plane: chunks 0 .. 3 of the output plane above it (D0), 4 .. 8
 // of the one at its height (D1), 9 .. 13 of the one below (D2).  Expects a and c read;
 // next_a() and next_c() run once a and c are no longer needed.
-template <bool D0, bool D1, bool D2, class NextA, class NextC>
-__device__ __forceinline__ void plane_products(Frags &F, const uint16_t *plane, const FragAt &at, bool second,
+template <bool D0, bool D1, bool D2, int BX, class NextA, class NextC>
+__device__ __forceinline__ void plane_products(Frags &F, const uint16_t *plane, const FragAt<BX> &at, bool second,
                                                const bf16x8 (&B)[kKC], f32x4 (&above)[4], f32x4 (&level)[4],
                                                f32x4 (&below)[4], NextA next_a, NextC next_c) {
     auto mm = [&](int q, bf16x8 x, f32x4 &c) { c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(B[q], x, c, 0, 0, 0); };
@@ -229,8 +243,8 @@ __device__ __forceinline__ void plane_products(Frags &F, const uint16_t *plane, 
 }
 // All of them for the ZC + 2 planes of a slab, one stage; next(from, to): the weights of
 // chunks from .. to - 1 are no longer needed.
-template <int I, int ZC, int PLANE, class Next>
-__device__ __forceinline__ void slab_products(Frags &F, const uint16_t *slab, const FragAt &at, bool second,
+template <int I, int ZC, int PLANE, int BX, class Next>
+__device__ __forceinline__ void slab_products(Frags &F, const uint16_t *slab, const FragAt<BX> &at, bool second,
                                               const bf16x8 (&B)[kKC], f32x4 (&acc)[ZC][4], Next next) {
     constexpr bool D0 = I < ZC, D1 = I >= 1 && I <= ZC, D2 = I >= 2;
     const uint16_t *plane = slab + I * PLANE * kVS, *after = plane + PLANE * kVS;
@@ -252,15 +266,15 @@ __device__ __forceinline__ void slab_products(Frags &F, const uint16_t *slab, co
 // with packed weights: 96 -> 32 channels at 96^3 307 -> 144 (1.0 PFLOP/s), 192 -> 64 at 48^3
 // 164 -> 67, 64 -> 64 at 48^3 63 -> 26 (rows of kpad 31), 192 -> 64 at 24^3 57 -> 23,
 // 128 -> 128 at 12^3 39 -> 12.4.
-template <int S, int ZC>
+template <int S, int ZC, int XG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_slab(ConvArgs a) {
-    constexpr int TY = 16 / S, PLANE = kSBX * (TY + 2), NE = 2 * PLANE, PS = (NE + 255) / 256;
+    constexpr int BX = Tile<S, XG>::BX, PLANE = Tile<S, XG>::PLANE, NE = 2 * PLANE, PS = (NE + 255) / 256;
     constexpr int kSlab = (ZC + 2) * PLANE * kVS;
     __shared__ __attribute__((aligned(16))) uint16_t slab[kSlab];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wy = wave % (4 / S), ws = wave / (4 / S);  // rows 4 wy .. 4 wy + 3, channel slice ws of the workgroup's
-    const ConvTile T = conv_tile<TY>(a.nx);
-    const int x0 = T.x0, y0 = T.y0, z0 = T.zc * ZC, co0 = 16 * (T.slice * S + ws);
+    const Tile<S, XG> W(wave);
+    const ConvTile T = conv_tile<Tile<S, XG>::TX, Tile<S, XG>::TY>(a.nx);
+    const int x0 = T.x0, y0 = T.y0, z0 = T.zc * ZC, co0 = 16 * (T.slice * S + W.slice);
     const int m = lane & 15, kb = lane >> 4, chan = 8 * (kb & 1);
     const bool second = kb >> 1;
     f32x4 acc[ZC][4];
@@ -284,7 +298,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
         for (int it = 0; it < PS; ++it) {
             const int e = tid + 256 * it, bv = e >> 1, h = e & 1;
-            const int xx = x0 + bv % kSBX - 1, yy = y0 + bv / kSBX - 1;
+            const int xx = x0 + bv % BX - 1, yy = y0 + bv / BX - 1;
             const bool in = xx >= 0 && xx < a.nx && yy >= 0 && yy < a.ny;
             poff[it] = in ? 2u * (uint32_t)(((yy >> sh) * (a.nx >> sh) + (xx >> sh)) * ld + off + 8 * h) : kNoOff;
         }
@@ -309,7 +323,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             }
         }
     };
-    const FragAt at(4 * wy, m, kb);
+    const FragAt<BX> at(W.y, W.x + m, kb);
     Frags F{};
     bf16x8 B[kKC];
     auto load_weights = [&](int c0, int from, int to) __attribute__((always_inline)) {
@@ -331,7 +345,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             if (c0 + kCC < a.cin) load_weights(c0 + kCC, from, to);
         });
     }
-    const int xx = x0 + m, c = co0 + 4 * kb;
+    const int xx = x0 + W.x + m, c = co0 + 4 * kb;
     if (xx >= a.nx) return;
     float bias[4];
 #pragma unroll
@@ -342,7 +356,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         if (zz >= a.nz) break;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const int yy = y0 + 4 * wy + t;
+            const int yy = y0 + W.y + t;
             if (yy >= a.ny) break;
             const int64_t vm = ((int64_t)zz * a.ny + yy) * a.nx + xx;
             float v[4];
@@ -367,12 +381,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // 48^3 26 and 28, 128 -> 128 at 12^3 12.4 and 14).
 template <int S, int ZC>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_ring(ConvArgs a) {
-    constexpr int TY = 16 / S, PLANE = kSBX * (TY + 2), C = (2 * PLANE + 255) / 256, SLOT = 256 * C * 8;
+    constexpr int XG = 1, BX = Tile<S, XG>::BX, PLANE = Tile<S, XG>::PLANE, C = (2 * PLANE + 255) / 256, SLOT = 256 * C * 8;
     __shared__ __attribute__((aligned(16))) uint16_t slab[(ZC + 2) * SLOT];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wy = wave % (4 / S), ws = wave / (4 / S);  // rows 4 wy .. 4 wy + 3, channel slice ws of the workgroup's
-    const ConvTile T = conv_tile<TY>(a.nx);
-    const int x0 = T.x0, y0 = T.y0, z0 = T.zc * ZC, co0 = 16 * (T.slice * S + ws);
+    const Tile<S, XG> W(wave);
+    const ConvTile T = conv_tile<Tile<S, XG>::TX, Tile<S, XG>::TY>(a.nx);
+    const int x0 = T.x0, y0 = T.y0, z0 = T.zc * ZC, co0 = 16 * (T.slice * S + W.slice);
     const int m = lane & 15, kb = lane >> 4;
     const bool second = kb >> 1;
     f32x4 acc[ZC][4];
@@ -405,7 +419,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
         for (int it = 0; it < C; ++it) {
             const int e = tid + 256 * it, bv = e >> 1, h = e & 1;
-            const int xx = x0 + bv % kSBX - 1, yy = y0 + bv / kSBX - 1;
+            const int xx = x0 + bv % BX - 1, yy = y0 + bv / BX - 1;
             const bool in = bv < PLANE && xx >= 0 && xx < a.nx && yy >= 0 && yy < a.ny;
             poff[it] = in ? 2u * (uint32_t)(((yy >> sh) * (a.nx >> sh) + (xx >> sh)) * ld + off + 8 * h) : kNoOff;
         }
@@ -426,7 +440,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             __builtin_amdgcn_raw_ptr_buffer_load_lds(from2 ? rx2 : rx, (lds_void *)to, 16, off, zoff, 0, 0);
         }
     };
-    const FragAt at(4 * wy, m, kb);
+    const FragAt<BX> at(W.y, W.x + m, kb);
     Frags F{};
     source_offsets(false);
     load_weights(0, 0, kKC);
@@ -474,7 +488,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         if constexpr (ZC >= 3) step(std::integral_constant<int, 4>{}, c0, last);
         if constexpr (ZC >= 4) step(std::integral_constant<int, 5>{}, c0, last);
     }
-    const int xx = x0 + m, c = co0 + 4 * kb;
+    const int xx = x0 + W.x + m, c = co0 + 4 * kb;
     if (xx >= a.nx) return;
     float bias[4];
 #pragma unroll
@@ -485,7 +499,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         if (zz >= a.nz) break;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const int yy = y0 + 4 * wy + t;
+            const int yy = y0 + W.y + t;
             if (yy >= a.ny) break;
             const int64_t vm = ((int64_t)zz * a.ny + yy) * a.nx + xx;
             float v[4];
@@ -539,16 +553,16 @@ __device__ __forceinline__ float head_of_rows(const uint2 (&o)[4], const float (
 // applied in the epilogue and only its FP32 output is stored.  MASK: a.m is not null.
 // Before (4 x 64 tiles, fragments read per product) and now: 16 -> 16 at 192^3 176 -> 108 us,
 // at 96^3 37 -> 20; 16 -> 32 at 96^3 56 -> 31.
-template <int S, bool HEAD, bool MASK>
+template <int S, bool HEAD, bool MASK, int XG>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_conv_march(ConvArgs a, int zr) {
-    constexpr int TY = 16 / S, PLANE = kSBX * (TY + 2), NE = 2 * PLANE, PS = (NE + 255) / 256;
+    constexpr int BX = Tile<S, XG>::BX, PLANE = Tile<S, XG>::PLANE, NE = 2 * PLANE, PS = (NE + 255) / 256;
     __shared__ __attribute__((aligned(16))) uint16_t s0[PLANE * kVS], s1[PLANE * kVS], s2[PLANE * kVS], s3[PLANE * kVS];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wy = wave % (4 / S), ws = wave / (4 / S);
-    const ConvTile T = conv_tile<TY>(a.nx);
-    const int x0 = T.x0, y0 = T.y0, z0 = T.zc * zr, co0 = 16 * (T.slice * S + ws);
+    const Tile<S, XG> W(wave);
+    const ConvTile T = conv_tile<Tile<S, XG>::TX, Tile<S, XG>::TY>(a.nx);
+    const int x0 = T.x0, y0 = T.y0, z0 = T.zc * zr, co0 = 16 * (T.slice * S + W.slice);
     const int n = min(zr, a.nz - z0);
-    const int m = lane & 15, kb = lane >> 4, c = co0 + 4 * kb, xx = x0 + m, yw = y0 + 4 * wy;
+    const int m = lane & 15, kb = lane >> 4, c = co0 + 4 * kb, xx = x0 + W.x + m, yw = y0 + W.y;
     const bool second = kb >> 1;
     const __amdgpu_buffer_rsrc_t rw =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(a.w), (short)0, (int)a.wbytes, kRawBuffer);
@@ -577,7 +591,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 #pragma unroll
     for (int it = 0; it < PS; ++it) {
         const int e = tid + 256 * it, bv = e >> 1, h = e & 1;
-        const int xq = x0 + bv % kSBX - 1, yq = y0 + bv / kSBX - 1;
+        const int xq = x0 + bv % BX - 1, yq = y0 + bv / BX - 1;
         const bool in = xq >= 0 && xq < a.nx && yq >= 0 && yq < a.ny;
         poff[it] = in ? 2u * (uint32_t)((yq * a.nx + xq) * a.ldx + a.offx + 8 * h) : kNoOff;
     }
@@ -613,12 +627,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         i &= 3;
         return i == 0 ? s0 : i == 1 ? s1 : i == 2 ? s2 : s3;
     };
-    const FragAt at(4 * wy, m, kb);
+    const FragAt<BX> at(W.y, W.x + m, kb);
     Frags F{};
     f32x4 above[4], level[4], below[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) above[t] = level[t] = below[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    const bool full = yw + 4 <= a.ny;
+    const bool full = yw + 4 <= a.ny && x0 + W.x < a.nx;  // this wave stores all four rows
     constexpr int kMinCopies = NE / 256, kStores = HEAD ? 1 : 4;  // of every wave for a plane
     copy_plane(z0 - 1, s0);
     copy_plane(z0, s1);
@@ -632,7 +646,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             const int i = i0 + k;
             if (i >= n + 2) break;
             // this wave's copies of this plane have landed: in the steady state two planes'
-            // copies (at least 2 or 1 per wave each) and two planes' stores are younger
+            // copies (at least kMinCopies per wave each) and two planes' stores are younger
             if (i < n && i >= 5 && full)
                 __builtin_amdgcn_s_waitcnt(wait_vmcnt(2 * kStores + 2 * kMinCopies));
             else if (i < n)
@@ -1501,13 +1515,29 @@ static int slab_planes(int64_t tiles, int nz, int s, bool packed) {
     return best;
 }
 
-template <int S>
+template <int S, int XG>
 static void launch_slab(int zc, dim3 g, hipStream_t st, const ConvArgs &a) {
     const dim3 blk(256);
-    if (zc == 1) hipLaunchKernelGGL((k_conv_slab<S, 1>), g, blk, 0, st, a);
-    else if (zc == 2) hipLaunchKernelGGL((k_conv_slab<S, 2>), g, blk, 0, st, a);
-    else if (zc == 3) hipLaunchKernelGGL((k_conv_slab<S, 3>), g, blk, 0, st, a);
-    else hipLaunchKernelGGL((k_conv_slab<S, 4>), g, blk, 0, st, a);
+    if (zc == 1) hipLaunchKernelGGL((k_conv_slab<S, 1, XG>), g, blk, 0, st, a);
+    else if (zc == 2) hipLaunchKernelGGL((k_conv_slab<S, 2, XG>), g, blk, 0, st, a);
+    else if (zc == 3) hipLaunchKernelGGL((k_conv_slab<S, 3, XG>), g, blk, 0, st, a);
+    else hipLaunchKernelGGL((k_conv_slab<S, 4, XG>), g, blk, 0, st, a);
+}
+
+// Workgroups in a plane for s channel slices each; flat: with their waves side by side in x
+// (tiles of 4 rows of 64 / s voxels) instead of on top of each other (16 / s rows of 16).
+static int64_t tiles_xy(int nx, int ny, int s, bool flat) {
+    const int tx = flat ? 64 / s : 16, ty = flat ? 4 : 16 / s;
+    return (int64_t)((nx + tx - 1) / tx) * ((ny + ty - 1) / ty);
+}
+
+template <int XG>
+static void launch_march(dim3 g, hipStream_t st, const ConvArgs &a, int s, int zr) {
+    const dim3 blk(256);
+    if (a.hout) hipLaunchKernelGGL((k_conv_march<1, true, false, XG>), g, blk, 0, st, a, zr);
+    else if (a.m) hipLaunchKernelGGL((k_conv_march<1, false, true, XG>), g, blk, 0, st, a, zr);
+    else if (s == 1) hipLaunchKernelGGL((k_conv_march<1, false, false, XG>), g, blk, 0, st, a, zr);
+    else hipLaunchKernelGGL((k_conv_march<2, false, false, XG == 4 ? 2 : 1>), g, blk, 0, st, a, zr);
 }
 
 extern "C" {
@@ -1539,37 +1569,41 @@ static int launch_conv(ConvArgs a, int64_t nx2, int64_t ny2, int64_t nz2, void *
     a.wbytes = (uint32_t)wbytes;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const dim3 blk(256);
-    auto tiles_xy = [&](int s) { return (int64_t)((nx + kSX - 1) / kSX) * ((ny + 16 / s - 1) / (16 / s)); };
     // slices per workgroup: as many as share the copies evenly
     int s = tiles % 4 == 0 ? 4 : tiles % 2 == 0 ? 2 : 1;
-    if (tiles_xy(s) > 0x7fffffff) return -1;
+    // Few rows leave the upper waves of a tile without any: tiles lie flat where that saves a
+    // quarter of them.  us upright / flat at 512 planes of rows of 512: 16 -> 16 channels, 4 rows
+    // 49 / 22.5, 8 51 / 34.5, 12 55 / 47.5, 16 58 / 60, 20 107 / 80, 28 (an eighth saved) 120 / 112;
+    // 48 -> 16 148 / 60, 154 / 112, 188 / 189, 232 / 258, 414 / 328, 433 / 453.
+    auto flat = [&](int sl) { return sl < 4 && 3 * tiles_xy(nx, ny, sl, false) >= 4 * tiles_xy(nx, ny, sl, true); };
+    if (tiles_xy(nx, ny, s, flat(s)) > 0x7fffffff) return -1;
     (void)hipGetLastError();
     // One stage: march where a chip full of workgroups (two per CU) has at least five planes
     // each.  Below that the run's first two planes cost more than they save (16 -> 32 at 48^3,
-    // 1.7 planes: 10.0 us against 7.5 in slabs; 16 -> 16 at 96^3, 6.8: 20.4 against 22.9).
+    // 1.7 planes: 10.0 us against 7.5 in slabs; 16 -> 16 at 96^3, 6.8: 20.4 against 22.9), as on
+    // grids of fewer planes than that (512 x 512 rows, 16 -> 48: one plane 42 against 34, four 72.3
+    // against 70.1, six 96 against 116; 16 -> 16 four 27 against 24.4, six 33 against 37).
     const int sm = s > 1 && !a.m && !a.hout ? 2 : 1;
-    if (cin == kCC && a.cin1 == cin && (a.hout || tiles_xy(sm) * (tiles / sm) * nz >= 5 * kConvSlots)) {
-        const int zr = march_planes(tiles_xy(sm) * (tiles / sm), nz);
-        const dim3 g((unsigned)tiles_xy(sm), (unsigned)((nz + zr - 1) / zr), (unsigned)(tiles / sm));
-        if (a.hout)
-            hipLaunchKernelGGL((k_conv_march<1, true, false>), g, blk, 0, st, a, zr);
-        else if (a.m)
-            hipLaunchKernelGGL((k_conv_march<1, false, true>), g, blk, 0, st, a, zr);
-        else if (sm == 1)
-            hipLaunchKernelGGL((k_conv_march<1, false, false>), g, blk, 0, st, a, zr);
-        else
-            hipLaunchKernelGGL((k_conv_march<2, false, false>), g, blk, 0, st, a, zr);
+    const int64_t tm = tiles_xy(nx, ny, sm, flat(sm));
+    if (cin == kCC && a.cin1 == cin && (a.hout || (nz >= 5 && tm * (tiles / sm) * nz >= 5 * kConvSlots))) {
+        const int zr = march_planes(tm * (tiles / sm), nz);
+        const dim3 g((unsigned)tm, (unsigned)((nz + zr - 1) / zr), (unsigned)(tiles / sm));
+        if (flat(sm)) launch_march<4>(g, st, a, sm, zr);
+        else launch_march<1>(g, st, a, sm, zr);
         return status(hipGetLastError());
     }
-    const int64_t t = tiles_xy(s) * (tiles / s);
+    const bool f = flat(s);
+    const int64_t txy = tiles_xy(nx, ny, s, f), t = txy * (tiles / s);
     // 16 output channels and eight rounds of workgroups: see k_conv_ring
-    const bool ring = s == 1 && t * ((nz + 3) / 4) >= 8 * kConvSlots;
+    const bool ring = s == 1 && !f && t * ((nz + 3) / 4) >= 8 * kConvSlots;
     const int zc = ring ? 4 : slab_planes(t, nz, s, a.packed);
-    const dim3 g((unsigned)tiles_xy(s), (unsigned)((nz + zc - 1) / zc), (unsigned)(tiles / s));
+    const dim3 g((unsigned)txy, (unsigned)((nz + zc - 1) / zc), (unsigned)(tiles / s));
     if (ring) hipLaunchKernelGGL((k_conv_ring<1, 4>), g, blk, 0, st, a);
-    else if (s == 4) launch_slab<4>(zc, g, st, a);
-    else if (s == 2) launch_slab<2>(zc, g, st, a);
-    else launch_slab<1>(zc, g, st, a);
+    else if (s == 4) launch_slab<4, 1>(zc, g, st, a);
+    else if (s == 2 && f) launch_slab<2, 2>(zc, g, st, a);
+    else if (s == 2) launch_slab<2, 1>(zc, g, st, a);
+    else if (f) launch_slab<1, 4>(zc, g, st, a);
+    else launch_slab<1, 1>(zc, g, st, a);
     return status(hipGetLastError());
 }
 
