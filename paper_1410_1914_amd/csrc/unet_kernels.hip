@@ -110,6 +110,12 @@ constexpr int kKC = 14;  // K chunks of 32 per stage: 27 taps x 16 channels, the
 // s_waitcnt vmcnt(n), the other counters not waited for (gfx9 encoding)
 constexpr int wait_vmcnt(int n) { return 0x0F70 | (n & 15) | (n >> 4) << 14; }
 constexpr int kWaitVmcnt0 = wait_vmcnt(0);
+// Around a wait whose count says which of this wave's copies, stores and loads may still be
+// out: nothing is moved from one side of it to the other, or the count would not hold.
+__device__ __forceinline__ void pin() {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
 
 // The tile of this workgroup: x and y origin, chunk of planes and group of channel slices.
 // The grid is (x-y tiles, chunks, groups).  Workgroups reach the 8 XCDs round-robin by
@@ -454,6 +460,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         // came first), or what is left of this stage's copies in the last
         constexpr int kYounger = ZC * C, kTail = ZC > s ? (ZC - s) * C : 0;
         constexpr int kWeights = (s + 1 <= ZC - 1 ? 4 : 0) + (s + 1 <= ZC ? 5 : 0) + (s + 1 <= ZC + 1 ? 5 : 0);
+        pin();
         if (last)
             __builtin_amdgcn_s_waitcnt(wait_vmcnt(kTail));
         else if (c0 == 0)
@@ -461,7 +468,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         else
             __builtin_amdgcn_s_waitcnt(wait_vmcnt(kYounger + kWeights));
         __builtin_amdgcn_s_barrier();  // everyone's have, and everyone is done with the plane before
-        asm volatile("" ::: "memory");
+        pin();
         if (s == 0) {
             copy_plane(c0, ZC + 1);
         } else if (!last) {
@@ -647,6 +654,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             if (i >= n + 2) break;
             // this wave's copies of this plane have landed: in the steady state two planes'
             // copies (at least kMinCopies per wave each) and two planes' stores are younger
+            pin();
             if (i < n && i >= 5 && full)
                 __builtin_amdgcn_s_waitcnt(wait_vmcnt(2 * kStores + 2 * kMinCopies));
             else if (i < n)
@@ -654,7 +662,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             else
                 __builtin_amdgcn_s_waitcnt(kWaitVmcnt0);
             __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
+            pin();
             const int pz = z0 + i - 2;  // the output plane this step completes
             float hbase = 0.f;
             uint2 mask[4];
