@@ -83,9 +83,8 @@ struct D19Args {
     int react_outlet;                   // 1: zero-gradient outlet (no open links at x = nx - 1)
     int open_inlet;                     // 1: open links at x = 0 (0 for the potential problem)
     int reverse;                        // 1: each XCD walks its part of the records backwards
-    // A step without measurement: XCD x walks ranges[x] (in device memory: arguments of
-    // several lines make the steps of small grids longer) or, where null, an eighth of the
-    // records.
+    // A step of a block of planes: XCD x walks ranges[x] (in device memory: arguments of
+    // several lines make the steps of small grids longer).  Null: every record.
     const cl::StepRange *__restrict__ ranges;
 };
 
@@ -150,18 +149,16 @@ template <bool REACT, bool MEASURE>
 __global__ __launch_bounds__(kBlock) void k_d3q19(D19Args a) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // lb: the logical block of a measured step, which also indexes the partial sums, so
-    // that it sums the same blocks in the same order in either direction
+    // lb: the logical block of a whole step, which also indexes a measured one's partial sums,
+    // so that it sums the same blocks in the same order in either direction
     int64_t lb = 0, e;
     bool some;
-    if constexpr (MEASURE) {
+    if (MEASURE || !a.ranges) {
         lb = a.reverse ? xcd_block_reversed(blockIdx.x, a.nblk) : xcd_block(blockIdx.x, a.nblk);
         e = lb * (kBlock / 64) + wave;
         some = e < a.nent;
     } else {
-        const int x = (int)blockIdx.x & 7, q = (int)a.nent >> 3, more = (int)a.nent & 7;
-        cl::StepRange r{q * x + min(x, more), q + (x < more ? 1 : 0), 0, 0};
-        if (a.ranges) r = a.ranges[x];
+        const cl::StepRange r = a.ranges[blockIdx.x & 7];
         const int n = r.n0 + r.n1;
         int k = (int)(blockIdx.x >> 3) * (kBlock / 64) + wave;
         some = k < n;
@@ -425,14 +422,14 @@ struct lbm19_solver {
     // reactive (1.24 GB) 292.8, 292.2 / 273.0 / 273.8 in 5 / 6 / 7; 160^3 Pt D_eff
     // (433 MB) 96.0, 81.3 / 87.0 in 2 / 3; 144^3 (310 MB) 73.1, 64.1 in 2; 128^3 (217 MB,
     // cached) 38.2, 41.1 in 2.  Rounds of 8 to 16 steps differ by 1-2%, of 20 by up to 5%.
-    // Rounds of fewer than five steps cost more launches of part of the chip's work than they
+    // Rounds of fewer than four steps cost more launches of part of the chip's work than they
     // save (whole over cut at 2, 3, 4, 5, 6, 8 steps 0.88, 0.96, 1.02, 1.06, 1.08, 1.12 at
-    // 192^3 in 4 blocks, 0.89, 0.98, 1.02, 1.05, 0.98, 1.02 at 64 x 400 x 256 in 3 with 6 and
-    // 8 in two rounds): shorter calls and rounds walk the whole grid, as do grids of fewer
-    // than 20 planes to a block (24 x 400 x 300 in 2: 0.87), grids that nearly fit the cache
-    // and would take rounds of fewer than eight (40 x 300 x 256, 273 MiB: 0.98), and slabs of
-    // uneven size (500 x 9 x 700: 0.94 to 0.99).
-    static constexpr int kMinRound = 5;
+    // 192^3 in 4 blocks, 0.94, 1.04, 1.10, 1.14, 1.17, 1.21 at 150 x 160 x 170 in 2, 0.89, 0.98,
+    // 1.02, 1.05, 0.98, 1.02 at 64 x 400 x 256 in 3 with 6 and 8 in two rounds): shorter calls and
+    // rounds walk the whole grid, as do grids of fewer than 20 planes to a block (24 x 400 x 300
+    // in 2: 0.87), grids that nearly fit the cache and would take rounds of fewer than eight
+    // (40 x 300 x 256, 273 MiB: 0.98), and slabs of uneven size (500 x 9 x 700: 0.94 to 0.99).
+    static constexpr int kMinRound = 4, kMinPlanes = 20;
     static constexpr double kMaxUneven = 1.2;
     void plan_blocks() {
         nblocks = block_steps = 1;
@@ -441,7 +438,7 @@ struct lbm19_solver {
         const int64_t block = int64_t(210) << 20, n = std::max<int64_t>(1, (bytes + block - 1) / block);
         const int round = std::min<int>(12, (int)(P.nz / n / 4));
         const int64_t whole = int64_t(round < 8 ? 320 : 240) << 20;
-        if (bytes <= whole || round < kMinRound) return;
+        if (bytes <= whole || P.nz / n < kMinPlanes) return;
         nblocks = (int)n;
         block_steps = round;
         tabulate_blocks();
@@ -490,7 +487,7 @@ struct lbm19_solver {
         hipError_t e = hipSuccess;
         if (!blocked(n)) {
             for (; n > 0 && e == hipSuccess; --n) {
-                e = launch_step(args(false), grid_of((int)((nent + 7) / 8)));
+                e = launch_step(args(false), nblk);
                 cur ^= 1;
                 ++steps;
             }

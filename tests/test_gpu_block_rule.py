@@ -70,7 +70,7 @@ def test_d3q19_short_calls_thin_blocks_and_uneven_slabs_walk_the_whole_grid(hip)
     most = min(12, 90 // n // 4)
     for k in range(1, 3 * most):
         rounds = -(-k // most)
-        assert s.blocks(k) == ((n, -(-k // rounds)) if k // rounds >= 5 else (1, 1))
+        assert s.blocks(k) == ((n, -(-k // rounds)) if k // rounds >= 4 else (1, 1))
     s.close()
     for shape in ((16, 350, 400), (300, 9, 800), (50, 50, 50)):
         s = hip.Solver19(_map(shape, 2), _params(hip, "deff", 1))
