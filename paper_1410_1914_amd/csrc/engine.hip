@@ -612,8 +612,8 @@ struct Engine {
         return hipSuccess;
     }
 
-    // One check window: `reps` replays of a captured graph of K0 steps, then the
-    // FP64 reductions (which also refresh the concentration snapshot).  When K0
+    // One check window: `reps` replays of a captured graph of K0 steps (or the steps
+    // themselves, see below), then the FP64 reductions (which also refresh the concentration snapshot).  When K0
     // steps take an odd number of launches (the two-step form with K0/2 odd), each
     // replay ends on the other lattice, so replays alternate between the graphs
     // captured from either lattice.
@@ -625,20 +625,31 @@ struct Engine {
             }
             return measure_enqueue(1);
         }
-        if (!g_valid) {
-            drop_graphs();
-            g_valid = true;
-        }
+        // Blocks of planes are launched as they come: each launch is tens of microseconds of
+        // work, so the host stays ahead, and a graph of several nodes per step costs the first
+        // window what a graph saves small grids (first window of 200 steps at 256^3 22.6 ->
+        // 21.6 ms, at 150 x 400^2 in 6 blocks 35.0 -> 33.4; later ones 20.9 and 32.2 either way).
+        const bool direct = !two_step() && blocked(K0);
         const bool fl = flips(K0) != 0;
-        for (int k = 0; k < ((fl && reps > 1) ? 2 : 1); ++k) {
-            const int from = cur ^ k;
-            if (!g_slot[from] || g_k[from] != K0) {
-                hipError_t e = capture(K0, from);
-                if (e != hipSuccess) return e;
+        if (!direct) {
+            if (!g_valid) {
+                drop_graphs();
+                g_valid = true;
+            }
+            for (int k = 0; k < ((fl && reps > 1) ? 2 : 1); ++k) {
+                const int from = cur ^ k;
+                if (!g_slot[from] || g_k[from] != K0) {
+                    hipError_t e = capture(K0, from);
+                    if (e != hipSuccess) return e;
+                }
             }
         }
         hipError_t e = note(hipEventRecord(ev0, st), "hipEventRecord");
         for (int64_t r = 0; r < reps && e == hipSuccess; ++r) {
+            if (direct) {
+                e = note(steps(K0), "k_step launch");
+                continue;
+            }
             e = note(hipGraphLaunch(gexec[cur], st), "hipGraphLaunch");
             if (fl) cur ^= 1;
         }

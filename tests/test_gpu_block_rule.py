@@ -97,3 +97,24 @@ def test_d3q19_middle_blocks_and_empty_planes(hip, shape, mode, steps):
         b.step(1)
     assert torch.equal(a.populations(), b.populations())
     assert a.measure().as_dict() == b.measure().as_dict()
+
+
+@pytest.mark.parametrize("every", [20, 34])
+def test_windows_of_a_cut_grid(hip, every):
+    """Check windows, of even and uneven rounds, equal single steps; the time of their launches is
+    reported as for small grids."""
+    import torch
+
+    ph = _map((90, 300, 300), 6)
+    p = hip.lbm_params_default(check_every=every, tol_flux=0.0, max_steps=1 << 40)
+    a, b = (hip.Solver(ph, p, device_prep=True) for _ in range(2))
+    assert a.blocks(every)[0] >= 3
+    c0 = torch.rand(a.shape, generator=torch.Generator().manual_seed(3))
+    for s in (a, b):
+        s.set_initial_concentration(c0)
+    for _ in range(2):
+        _, info = a.advance(3 * every)
+    for _ in range(6 * every):
+        b.step(1)
+    assert torch.equal(a.populations(), b.populations())
+    assert info.steps == 6 * every and info.kernel_launches == 6 * every and info.kernel_ms > 0
