@@ -294,8 +294,6 @@ __global__ __launch_bounds__(kSheetThreads) void k_pore_sheet(const uint8_t *__r
     }
 }
 
-int64_t sheet_line_words(int64_t nx, int64_t rows) { return sheet_words(nx) * rows + ring_words(rows) * nx; }
-
 size_t sheet_lds(int64_t nx, int64_t rows) {
     return 4 * (size_t)(sheet_words(nx) * (3 * rows + 32) + ring_words(rows) * nx) + 4 * kSheetThreads;
 }
@@ -324,20 +322,25 @@ hipError_t launch_pore_sheet(const uint8_t *pore, int nx, int ny, int nz, const 
     return hipGetLastError();
 }
 
-// Whether the pore size is counted by sheets: they have to fit LDS, and the lines that a
-// workgroup lays out for itself, about 4.5 ns a word of them, must not take longer than
-// walking.  yz diagonals that close late make a few very long sheets, which each workgroup
-// on them lays out whole.  Walking takes about 85 us and 1 us for 8000 voxels in grown
-// structures (58 us and 1 us for 10500 in random maps of 45% pore), the four launches by
-// sheets 45 us and the lines.  us walked / by sheets: 50^3 97 / 56, 40 x 50 x 50 (ten sheets
-// of 200 rows) 93 / 66, 48 x 60 x 64 93 / 70, 16 x 24 x 240 96 / 75, 80 x 100 x 64 157 / 93;
-// 48 x 50 x 50 (two of 1200) 93 / 136, 32 x 31 x 100 (one of 992) 99 / 181, 3 x 300 x 100 104
-// / 103; random maps 62 / 56, 61 / 66, 64 / 70, 59 / 74, 97 / 97; 62 / 136, 59 / 181, 57 / 103.
+// Whether the pore size is counted by sheets.  They have to fit LDS, and the lines that a
+// workgroup lays out for itself must not take longer than walking: yz diagonals that close
+// late make a few very long sheets, which each workgroup on them lays out whole.  By sheets:
+// the four launches take 45 us, the lines 6.5 ns a word along x and the diagonals and 2 a
+// word of a column (within 15% over the sizes below).  Walking: about 57 us and 1 us for
+// 10500 voxels in random maps of 45% pore, 85 us and 1 us for 8000 in grown structures, whose
+// runs are longer; the line lies between the two, and lower where rows are so short that no
+// run along x is long.  us by sheets / walked, grown and random: 50^3 56 / 97, 62; 40 x 50 x 50
+// (ten sheets of 200 rows) 66 / 93, 61; 48 x 60 x 64 70 / 93, 64; 16 x 24 x 240 74 / 96, 59; 80 x
+// 100 x 64 97 / 157, 97; 55 x 60 x 57 (five of 660) 100 / -, 58; 3 x 300 x 100 103 / 104, 57; 48 x
+// 50 x 50 (two of 1200) 136 / 93, 62; 32 x 31 x 100 (one of 992) 181 / 99, 59.  Random, short
+// rows: 8^3 48 / 48, 39 x 4 x 8 57 / 46, 7 x 10 x 1 48 / 26.
 bool by_sheets(int64_t nx, int64_t ny, int64_t nz) {
     const int64_t ring = std::lcm(ny, nz);
     if (sheet_lds(nx, std::max({ny, nz, ring})) > kMaxLds) return false;
-    const int64_t words = sheet_line_words(nx, ny) + sheet_line_words(nx, nz) + 2 * sheet_line_words(nx, ring);
-    return 0.0045 * (double)words <= 40.0 + (double)(nx * ny * nz) / 8000.0;
+    const int64_t lines = sheet_words(nx) * (ny + nz + 2 * ring);
+    const int64_t columns = nx * (ring_words(ny) + ring_words(nz) + 2 * ring_words(ring));
+    const double walk = (70.0 + (double)(nx * ny * nz) / 9000.0) * std::min(1.0, 0.3 + 0.7 * (double)nx / 15.0);
+    return 45.0 + 0.0065 * (double)lines + 0.002 * (double)columns <= walk;
 }
 
 // Seeds of the reach: pass voxels on the selected x faces.
