@@ -1661,43 +1661,43 @@ int unet_conv3d_wgrad(const uint16_t *x, int32_t ldx, int32_t offx, const uint16
     if (cin % 16 || cout % 16 || ldx % 8 || offx % 8 || lddy % 8 || offdy % 8) return -1;
     const int64_t nvox = (int64_t)nz * ny * nx;
     const int64_t xplane = 2 * (int64_t)ny * nx * ldx, dplane = 2 * (int64_t)ny * nx * lddy;
-    // The marching form but for rows that fill little of its tiles of 32 (us there and in the
-    // general form, 512 x 512 rows: 1 voxel 138 / 83 (16 -> 16 channels), 751 / 180 (32 -> 64);
-    // 2: 138 / 160, 750 / 361; 3: 139 / 230, 751 / 568; 4: 139 / 317, 749 / 706; 6: 139 / 455, 750 /
-    // 1133), and for grids of up to 1024 voxels, which keep to two runs of planes (two sums
-    // have no order; the general form has two workgroups per sum there), of more than 16
-    // planes (8 x 8 x 15: 15.5 / 23, 22 / 26; 20 planes of 7 x 7 17 / 23, 24 / 26; 60 of 4 x 4 30 /
-    // 23, 42 / 26; 1000 of one voxel 227 / 22).
+    // The marching form, in runs of planes: about one workgroup per CU, up to two where the runs
+    // stay 24 planes long (a run copies two planes beyond its own and adds its sums
+    // atomically).  The 14 layers of a 96^3 step: 514 / 444 / 477 / 515 / 675 us with 128 / 256 /
+    // 384 / 512 / 768 workgroups each; the 48 -> 16 layer alone 115 / 78 / 56 / 74 / 61.
     const int two = cout % 32 == 0 ? 2 : 1;
-    const bool few = nvox <= 1024;
+    const int64_t tiles = (int64_t)((nx + kWX - 1) / kWX) * ((ny + kWY - 1) / kWY) * (cin / 16) * (cout / (16 * two));
+    const int64_t runs = std::max(std::max<int64_t>(1, 256 / tiles), std::min<int64_t>(512 / tiles, nz / 24));
+    int64_t zr = (nz + runs - 1) / runs;
+    // Tiny grids of one tile keep to two runs, whose two sums have no order; the general form
+    // has as many there.
+    const bool few = nvox <= 1024 && nx <= kWX && ny <= kWY;
+    if (few) zr = std::max<int64_t>(zr, (nz + 1) / 2);
+    // Not where long runs go through tiles that are mostly empty (us there / in the general
+    // form, 512 x 512 rows: 1 voxel 138 / 83 (16 -> 16 channels), 750 / 180 (32 -> 64); 2: 138 / 160,
+    // 750 / 361; 3: 139 / 230, 751 / 568; 4: 139 / 317, 749 / 706; 6: 139 / 455, 750 / 1133; runs of
+    // 1 to 5 planes of 28 x 106 rows of 1 16 / 23, 13 x 73 of 4 22 / 28), nor where the two
+    // runs of a tiny grid are long (planes of 8 x 8: 15 of them 15.5 / 23, 22 / 26; 20 of 7 x 7 17 /
+    // 23, 24 / 26; 60 of 4 x 4 30 / 23, 42 / 26; 1000 of one voxel 227 / 22).
+    const bool thin = nx < (two == 2 ? 5 : 3);
+    const int64_t blocks = tiles * ((nz + zr - 1) / zr);
     if (((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(dy)) & 15) == 0 && xplane * nz <= kMaxX &&
-        dplane * nz <= kMaxX && nx >= (two == 2 ? 5 : 3) && !(few && nz > 16)) {
-        const int64_t tiles = (int64_t)((nx + kWX - 1) / kWX) * ((ny + kWY - 1) / kWY) * (cin / 16) * (cout / (16 * two));
-        // Runs per tile: about one workgroup per CU, up to two where the runs stay 24 planes
-        // long (a run copies two planes beyond its own and adds its sums atomically).  The 14
-        // layers of a 96^3 step: 514 / 444 / 477 / 515 / 675 us with 128 / 256 / 384 / 512 /
-        // 768 workgroups each; the 48 -> 16 layer alone 115 / 78 / 56 / 74 / 61.
-        const int64_t runs = std::max(std::max<int64_t>(1, 256 / tiles), std::min<int64_t>(512 / tiles, nz / 24));
-        int64_t zr = (nz + runs - 1) / runs;
-        if (few) zr = std::max<int64_t>(zr, (nz + 1) / 2);
-        const int64_t blocks = tiles * ((nz + zr - 1) / zr);
-        if (blocks <= 0x7fffffff) {
-            const WgradArgs a{x, dy, dw, db, ldx, offx, lddy, offdy, nz, ny, nx, cin, cout, kpad_of(cin), (int)zr,
-                              (uint32_t)(xplane * nz), (uint32_t)xplane, (uint32_t)(dplane * nz), (uint32_t)dplane};
-            (void)hipGetLastError();
-            if (two == 2)
-                hipLaunchKernelGGL(k_wgrad_zm<2>, dim3((unsigned)blocks), dim3(256), 0, static_cast<hipStream_t>(stream), a);
-            else
-                hipLaunchKernelGGL(k_wgrad_zm<1>, dim3((unsigned)blocks), dim3(256), 0, static_cast<hipStream_t>(stream), a);
-            return status(hipGetLastError());
-        }
+        dplane * nz <= kMaxX && blocks <= 0x7fffffff && (!thin || zr <= 6) && (!few || zr <= 10)) {
+        const WgradArgs a{x, dy, dw, db, ldx, offx, lddy, offdy, nz, ny, nx, cin, cout, kpad_of(cin), (int)zr,
+                          (uint32_t)(xplane * nz), (uint32_t)xplane, (uint32_t)(dplane * nz), (uint32_t)dplane};
+        (void)hipGetLastError();
+        if (two == 2)
+            hipLaunchKernelGGL(k_wgrad_zm<2>, dim3((unsigned)blocks), dim3(256), 0, static_cast<hipStream_t>(stream), a);
+        else
+            hipLaunchKernelGGL(k_wgrad_zm<1>, dim3((unsigned)blocks), dim3(256), 0, static_cast<hipStream_t>(stream), a);
+        return status(hipGetLastError());
     }
     const int nco = cout % 64 == 0 ? 4 : (cout % 32 == 0 ? 2 : 1);
     // enough workgroups to fill the device: the voxel range per workgroup shrinks
     // for layers with few (k, channel) tiles
-    const int64_t tiles = (int64_t)((27 * cin + kWgK - 1) / kWgK) * (cout / (16 * nco));
+    const int64_t slices = (int64_t)((27 * cin + kWgK - 1) / kWgK) * (cout / (16 * nco));
     int64_t vper = 4096;
-    while (vper > 512 && tiles * ((nvox + vper - 1) / vper) < 2048) vper >>= 1;
+    while (vper > 512 && slices * ((nvox + vper - 1) / vper) < 2048) vper >>= 1;
     const dim3 g((unsigned)((27 * cin + kWgK - 1) / kWgK), (unsigned)((nvox + vper - 1) / vper),
                  (unsigned)(cout / (16 * nco)));
     (void)hipGetLastError();

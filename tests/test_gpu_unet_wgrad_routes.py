@@ -11,7 +11,7 @@ from test_gpu_unet_wgrad import _data, _reference, _run
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("shape", [(300, 8, 32), (40, 8, 20), (17, 7, 7), (16, 8, 8), (64, 8, 8), (90, 2, 5), (33, 9, 3),
+@pytest.mark.parametrize("shape", [(300, 8, 32), (11, 77, 1), (9, 38, 3), (19, 1, 28), (40, 8, 20), (17, 7, 7), (16, 8, 8), (64, 8, 8), (90, 2, 5), (33, 9, 3),
                                    (20, 5, 4), (1000, 1, 1)])
 @pytest.mark.parametrize("cin,cout", [(16, 16), (32, 64)])
 def test_values_on_thin_grids(hip, shape, cin, cout):
@@ -24,7 +24,8 @@ def test_values_on_thin_grids(hip, shape, cin, cout):
 
 
 @pytest.mark.parametrize("shape", [(2000, 8, 32), (100, 8, 32), (64, 8, 8), (200, 4, 16), (2000, 1, 1), (1000, 1, 1),
-                                   (256, 256, 1), (256, 256, 2), (60, 4, 4), (2000, 1, 8), (500, 2, 6)])
+                                   (256, 256, 1), (256, 256, 2), (60, 4, 4), (2000, 1, 8), (500, 2, 6),
+                                   (11, 77, 1), (5, 38, 3), (19, 1, 28)])
 @pytest.mark.parametrize("cin,cout", [(16, 16), (32, 64)])
 def test_no_slower_than_the_general_form(hip, shape, cin, cout):
     import time
