@@ -46,7 +46,7 @@ def test_arguments_of_a_step_fill_one_line(tmp_path):
     """Steps of a small grid are bound by their launches, and every 64-byte line of arguments
     fetched after the first makes one longer."""
     steps = {k: v for k, v in _kernels("_liblbm.so", tmp_path).items() if "6k_stepI" in k}
-    assert len(steps) == 96  # 4 x 3 tilings, 2 x 2 problems, one or several instances
+    assert len(steps) == 144  # 4 x 3 tilings, 2 x 2 problems, whole, in blocks of planes, several instances
     assert {int(v["kernarg_segment_size"]) for v in steps.values()} == {64}
 
 
