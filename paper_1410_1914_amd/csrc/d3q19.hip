@@ -478,7 +478,7 @@ struct lbm19_solver {
 
     // whether n steps are taken in blocks of planes, and the first round's steps
     bool blocked(int64_t n) const {
-        return nblocks > 1 && n / ((n + block_steps - 1) / block_steps) >= kMinRound;
+        return nblocks > 1 && n >= kMinRound && n / ((n + block_steps - 1) / block_steps) >= kMinRound;
     }
     int round_steps(int64_t n) const {
         const int64_t rounds = (n + block_steps - 1) / block_steps;

@@ -509,7 +509,7 @@ struct Engine {
     }
     // whether n steps are taken in blocks of planes
     bool blocked(int64_t n) const {
-        return nblocks > 1 && xcd && n / ((n + block_steps - 1) / block_steps) >= kMinRound;
+        return nblocks > 1 && xcd && n >= kMinRound && n / ((n + block_steps - 1) / block_steps) >= kMinRound;
     }
 
     bool two_step() const { return t2_by > 0 && ninst == 1; }

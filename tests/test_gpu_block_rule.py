@@ -118,3 +118,28 @@ def test_windows_of_a_cut_grid(hip, every):
         b.step(1)
     assert torch.equal(a.populations(), b.populations())
     assert info.steps == 6 * every and info.kernel_launches == 6 * every and info.kernel_ms > 0
+
+
+def test_no_steps_on_a_cut_grid(hip):
+    """A call of no steps, and the none that are left after steps taken two to a launch."""
+    import torch
+
+    ph = _map((90, 300, 300), 7)
+    s = hip.Solver(ph, _params(hip, "deff", 0), device_prep=True)
+    assert s.blocks(200)[0] >= 3
+    f = s.populations()
+    s.step(0)
+    assert torch.equal(s.populations(), f)
+    s.set_temporal(6, 16)
+    s.step(8)
+    two = s.populations()
+    s.set_temporal(0)
+    s.set_populations(f)
+    s.step(8)
+    assert torch.equal(s.populations(), two)
+    s.close()
+    s = hip.Solver19(_map((90, 210, 220), 7), _params(hip, "deff", 1))
+    assert s.blocks(200)[0] >= 3
+    f = s.populations()
+    s.step(0)
+    assert torch.equal(s.populations(), f)
