@@ -345,7 +345,8 @@ void lbm_batch_destroy(lbm_batch *b);
  * or the x = nx - 1 face (faces & 2); 0 elsewhere.  This is lbm_create's
  * simulated-voxel mask when pass is the transport phase and faces are the
  * Dirichlet faces.  *cycles (may be NULL) receives the number of sweep cycles
- * (the grid swept along all three axes each) until nothing changed. */
+ * up to and with the first that changed nothing (each goes over every z plane and
+ * every y plane, or along the three axes where those planes do not fit on chip). */
 int lbm_pore_size_device(const uint8_t *pore_dev, int32_t nx, int32_t ny, int32_t nz, double *dp_dev, void *stream);
 int lbm_reach_device(const uint8_t *pass_dev, int32_t nx, int32_t ny, int32_t nz, int32_t faces, uint8_t *hit_dev,
                      int32_t *cycles, void *stream);
@@ -358,9 +359,9 @@ int lbm_reach_device(const uint8_t *pass_dev, int32_t nx, int32_t ny, int32_t nz
  * device, held until the process ends) instead of freshly allocated pinned host
  * memory; it does not grow with the grid, so every grid lbm_reach_device accepts
  * is accepted.  The array holds one flag for each of the sweep cycles issued between
- * two waits (up to two); a kernel clears each flag at the start of its cycle, and
- * all are read back with a copy into host memory followed by a synchronisation of
- * stream.  Calls that overlap on one device (other host threads,
+ * two waits (up to two); one kernel clears them all before the first of these
+ * cycles, and all are read back with a copy into host memory followed by a
+ * synchronisation of stream.  Calls that overlap on one device (other host threads,
  * other streams) share that flag and race: serialise them. */
 int lbm_reach_device_static(const uint8_t *pass_dev, int32_t nx, int32_t ny, int32_t nz, int32_t faces,
                             uint8_t *hit_dev, int32_t *cycles, void *stream);
