@@ -1679,10 +1679,13 @@ int unet_conv3d_wgrad(const uint16_t *x, int32_t ldx, int32_t offx, const uint16
     // 1 to 5 planes of 28 x 106 rows of 1 16 / 23, 13 x 73 of 4 22 / 28), nor where the two
     // runs of a tiny grid are long (planes of 8 x 8: 15 of them 15.5 / 23, 22 / 26; 20 of 7 x 7 17 /
     // 23, 24 / 26; 60 of 4 x 4 30 / 23, 42 / 26; 1000 of one voxel 227 / 22).
-    const bool thin = nx < (two == 2 ? 5 : 3);
+    // Nor long runs, or very many of them, of a few voxels a plane (2000 of 1 x 8 32 -> 64: 32 /
+    // 25; 500 of 2 x 6 15 / 24; 2000 of 3 x 5 16 -> 16 in 250 runs: 29 / 24).
+    const bool thin = nx < (two == 2 ? 5 : 3), sliver = (int64_t)nx * ny <= 16;
     const int64_t blocks = tiles * ((nz + zr - 1) / zr);
     if (((reinterpret_cast<uintptr_t>(x) | reinterpret_cast<uintptr_t>(dy)) & 15) == 0 && xplane * nz <= kMaxX &&
-        dplane * nz <= kMaxX && blocks <= 0x7fffffff && (!thin || zr <= 6) && (!few || zr <= 10)) {
+        dplane * nz <= kMaxX && blocks <= 0x7fffffff && (!thin || zr <= 6) && (!sliver || zr <= (two == 2 ? 16 : 6)) &&
+        (!few || zr <= 10)) {
         const WgradArgs a{x, dy, dw, db, ldx, offx, lddy, offdy, nz, ny, nx, cin, cout, kpad_of(cin), (int)zr,
                           (uint32_t)(xplane * nz), (uint32_t)xplane, (uint32_t)(dplane * nz), (uint32_t)dplane};
         (void)hipGetLastError();

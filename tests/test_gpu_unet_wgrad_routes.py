@@ -25,7 +25,7 @@ def test_values_on_thin_grids(hip, shape, cin, cout):
 
 @pytest.mark.parametrize("shape", [(2000, 8, 32), (100, 8, 32), (64, 8, 8), (200, 4, 16), (2000, 1, 1), (1000, 1, 1),
                                    (256, 256, 1), (256, 256, 2), (60, 4, 4), (2000, 1, 8), (500, 2, 6),
-                                   (11, 77, 1), (5, 38, 3), (19, 1, 28)])
+                                   (11, 77, 1), (5, 38, 3), (19, 1, 28), (3000, 1, 5), (2000, 3, 5)])
 @pytest.mark.parametrize("cin,cout", [(16, 16), (32, 64)])
 def test_no_slower_than_the_general_form(hip, shape, cin, cout):
     import time
