@@ -24,6 +24,7 @@
 #include <cstdint>
 #include <cstring>
 #include <memory>
+#include <type_traits>
 #include <vector>
 
 #include "kernels.h"
@@ -83,10 +84,13 @@ struct D19Args {
     int react_outlet;                   // 1: zero-gradient outlet (no open links at x = nx - 1)
     int open_inlet;                     // 1: open links at x = 0 (0 for the potential problem)
     int reverse;                        // 1: each XCD walks its part of the records backwards
-    // A step without measurement: XCD x walks ranges[x] (in device memory: arguments of
-    // several lines make the steps of small grids longer) or, where null, an eighth of the
-    // records, to the record and not to a block of four (211 x 36 x 12 10.4 against 10.9 us).
-    const cl::StepRange *__restrict__ ranges;
+};
+// A step of a block of planes: XCD x walks ranges[x].  Whole steps, also those of small grids,
+// do without these two lines of arguments and the choice between the two (32^3 4.73 -> 4.58 us);
+// a table in device memory instead is one more trip at the front of every wave (256^3 reactive
+// 306.5 against 303.6 us a step, 192^3 D_eff 131.6 against 129.6).
+struct D19CutArgs : D19Args {
+    cl::StepRange ranges[8];
 };
 
 // Blocks are dealt round-robin to the 8 XCDs; give XCD k the k-th contiguous
@@ -146,8 +150,10 @@ __device__ __forceinline__ bool bit64(uint64_t m, int l) { return ((m >> l) & 1u
 // the face plane it passes (the source row's voxel at that face) is simulated.
 // MEASURE also sums the fluxes of the links just crossed and the C, k n C of the
 // new state.
-template <bool REACT, bool MEASURE>
-__global__ __launch_bounds__(kBlock) void k_d3q19(D19Args a) {
+// Without it XCD x walks an eighth of the records, to the record and not to a block of four
+// (211 x 36 x 12 10.4 against 10.9 us), or its planes of a block (D19CutArgs).
+template <bool REACT, bool MEASURE, class Args>
+__global__ __launch_bounds__(kBlock) void k_d3q19(Args a) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     // lb: the logical block of a measured step, which also indexes the partial sums, so
@@ -161,7 +167,7 @@ __global__ __launch_bounds__(kBlock) void k_d3q19(D19Args a) {
     } else {
         const int x = (int)blockIdx.x & 7, q = (int)a.nent >> 3, more = (int)a.nent & 7;
         cl::StepRange r{q * x + min(x, more), q + (x < more ? 1 : 0), 0, 0};
-        if (a.ranges) r = a.ranges[x];
+        if constexpr (std::is_same_v<Args, D19CutArgs>) r = a.ranges[x];
         const int n = r.n0 + r.n1;
         int k = (int)(blockIdx.x >> 3) * (kBlock / 64) + wave;
         some = k < n;
@@ -361,7 +367,7 @@ struct lbm19_solver {
     std::vector<float> om_c, kn_c; // compact 1/tau and k n
     // workspace carve-up
     size_t off_f[2] = {0, 0}, off_mask = 0, off_cidx = 0, off_rec = 0, off_om = 0, off_kn = 0,
-           off_cs = 0, off_part = 0, off_red = 0, off_ranges = 0, need = 0;
+           off_cs = 0, off_part = 0, off_red = 0, need = 0;
     char *ws = nullptr;
     hipStream_t st = nullptr;
     int device = 0;
@@ -467,12 +473,13 @@ struct lbm19_solver {
         block_ranges.clear();
     }
 
-    hipError_t launch_step(const D19Args &a, int grid) {
+    template <class Args>
+    hipError_t launch_step(const Args &a, int grid) {
         if (grid <= 0) return hipSuccess;
         if (react)
-            k_d3q19<true, false><<<grid, kBlock, 0, st>>>(a);
+            k_d3q19<true, false, Args><<<grid, kBlock, 0, st>>>(a);
         else
-            k_d3q19<false, false><<<grid, kBlock, 0, st>>>(a);
+            k_d3q19<false, false, Args><<<grid, kBlock, 0, st>>>(a);
         return hipGetLastError();
     }
 
@@ -501,8 +508,8 @@ struct lbm19_solver {
             for (int c = 0; c < nblocks && e == hipSuccess; ++c)
                 for (int t = 0; t < T && e == hipSuccess; ++t) {
                     const size_t k = (size_t)c * block_steps + t;
-                    D19Args a = args(false);
-                    a.ranges = at<cl::StepRange>(off_ranges) + 8 * k;
+                    D19CutArgs a{args(false), {}};
+                    std::copy_n(block_ranges.data() + 8 * k, 8, a.ranges);
                     a.reverse = t & 1;
                     if (t & 1) {
                         a.fin = at<float>(off_f[cur ^ 1]);
@@ -522,9 +529,9 @@ struct lbm19_solver {
         const D19Args a = args(true);
         if (nblk > 0) {
             if (react)
-                k_d3q19<true, true><<<nblk, kBlock, 0, st>>>(a);
+                k_d3q19<true, true, D19Args><<<nblk, kBlock, 0, st>>>(a);
             else
-                k_d3q19<false, true><<<nblk, kBlock, 0, st>>>(a);
+                k_d3q19<false, true, D19Args><<<nblk, kBlock, 0, st>>>(a);
         }
         hipError_t e = hipGetLastError();
         if (e == hipSuccess) {
@@ -742,7 +749,6 @@ static int create19(const lbm_grid *g, const uint8_t *phase, const lbm_params *p
         s->off_cs = take(4 * (size_t)std::max<int64_t>(nf, 1));
         s->off_part = take(sizeof(double) * kRed * (size_t)std::max(s->nblk, 1));
         s->off_red = take(sizeof(double) * kRed);
-        s->off_ranges = take(sizeof(cl::StepRange) * s->block_ranges.size());
         s->need = o;
         *out = s.release();
         return LBM_OK;
@@ -1091,7 +1097,6 @@ int lbm19_bind(lbm19_solver *s, void *ws, size_t bytes, void *stream) {
     up(s->off_mask, s->mask.data(), 4 * s->mask.size());
     up(s->off_cidx, s->cidx.data(), 4 * s->cidx.size());
     up(s->off_rec, s->rec.data(), sizeof(D19Rec) * s->rec.size());
-    up(s->off_ranges, s->block_ranges.data(), sizeof(cl::StepRange) * s->block_ranges.size());
     up(s->off_om, s->om_c.data(), 4 * s->om_c.size());
     if (s->react) up(s->off_kn, s->kn_c.data(), 4 * s->kn_c.size());
     if (e == hipSuccess) e = hipStreamSynchronize(s->st);

@@ -50,6 +50,14 @@ def test_arguments_of_a_step_fill_one_line(tmp_path):
     assert {int(v["kernarg_segment_size"]) for v in steps.values()} == {64}
 
 
+def test_whole_d3q19_steps_take_no_ranges(tmp_path):
+    """The 8 ranges of a block of planes (16 bytes each) are arguments of its steps alone."""
+    steps = {k: int(v["kernarg_segment_size"]) for k, v in _kernels("_liblbm.so", tmp_path).items() if "k_d3q19I" in k}
+    cut = [n for k, n in steps.items() if "D19CutArgs" in k]
+    assert len(steps) == 6 and len(cut) == 2  # 2 problems: whole, measured, in blocks of planes
+    assert {n + 128 for k, n in steps.items() if "D19CutArgs" not in k} == set(cut)
+
+
 def test_the_reach_leaves_room_for_its_own_lds(tmp_path):
     """A sheet may take 160 KB but for a kilobyte, which the kernel's own LDS has to fit."""
     sheets = [v for k, v in _kernels("_liblbm.so", tmp_path).items() if "13k_reach_sheetI" in k]
