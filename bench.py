@@ -169,7 +169,7 @@ def headline(args, lbm, structgen):
     sha = kernel_source_hash()
     tb = traffic_from_profiles(sha, workload) if spl == 1 else None
     kname = (f"k_step2<{temporal[0]},true,true> (two steps per launch, Knudsen, reactive)" if spl == 2 else
-             f"k_step<{tiling[1]},{tiling[0]},true,true,true> (fused pull stream-collide, Knudsen, reactive)")
+             f"k_step<{tiling[1]},{tiling[0]},true,true> (fused pull stream-collide, Knudsen, reactive)")
     roof = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4),
             "traffic": (round(tb / per_launch_s / 1e9, 1) if tb else None),
